@@ -38,13 +38,9 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int FT = 128;                         // tile edge
 constexpr int FNT = 512;                        // threads per workgroup: 8 waves, 2 (rows) x 4 (cols)
-constexpr int TPITCH = FT + 1;                  // transpose buffer pitch (elements)
 constexpr int DIAG_SLOTS = FT * (FT + 1) / 2;   // residues of a diagonal task
 constexpr int OFF_SLOTS = FT * FT;              // residues of an off-diagonal task
 constexpr int FTT = 8;                          // trial energies per epilogue pass (at most)
-// a diagonal task's transposition buffer (after the main loop, over the stage buffers): rows
-// 0..63 at byte 0, rows 64..127 at TR_HALF
-constexpr int TR_HALF = (FT / 2) * TPITCH * 8;
 
 template <int PREC> struct FTr;
 // k per stage, planes, row bytes per plane and stages in the ring: a stage holds four operand
@@ -79,6 +75,7 @@ struct FArgs {
     int nsc;                                    // targets of this launch
     const int *tsel;                            // [nsc] target slot (row block of Bsel)
     int nTA, nTB, nPA, nPB;                     // tiles and tile pairs of parts A and B
+    int nLA, nLB;                               // tile pairs per fixed index in this launch
     int64_t tpt;                                // tasks per target
     int64_t sizeA, sizeB;                       // residue entries per virtual a / occupied i
     int64_t nres;                               // residue entries per target
@@ -110,28 +107,46 @@ __device__ __forceinline__ void pair_tiles(int p, int n, int &TR, int &TC)
     TC = r + p;
 }
 
+// the p-th tile pair of a launch over n tiles -> tiles and pair index: the diagonal pairs, or the
+// others in row-major upper-triangle order
+template <bool DG>
+__device__ __forceinline__ void launch_pair(int p, int n, Task &k)
+{
+    int r = 0;
+    if constexpr (DG) {
+        k.TR = k.TC = r = p;
+    } else {
+        while (p >= n - 1 - r) {
+            p -= n - 1 - r;
+            ++r;
+        }
+        k.TR = r;
+        k.TC = r + 1 + p;
+    }
+    k.pair = r * n - r * (r - 1) / 2 + (k.TC - k.TR);
+}
+
 // launch order: part B tasks by (target, pair, i), then part A tasks by (target, pair, a): runs of
 // tasks that share the P operand slices (rows of Bsel for one target) and differ only in the Q rows
+template <bool DG>
 __device__ __forceinline__ Task task_of_launch(const FArgs &a, int64_t t)
 {
     Task k;
-    const int64_t nB = (int64_t)a.nocc * a.nsc * a.nPB;
+    const int64_t nB = (int64_t)a.nocc * a.nsc * a.nLB;
     if (t < nB) {
         k.fam = 1;
         k.idx = (int)(t % a.nocc);
         const int64_t rem = t / a.nocc;
-        k.pair = (int)(rem % a.nPB);
-        k.sl = (int)(rem / a.nPB);
-        pair_tiles(k.pair, a.nTB, k.TR, k.TC);
+        k.sl = (int)(rem / a.nLB);
+        launch_pair<DG>((int)(rem % a.nLB), a.nTB, k);
         k.tin = (int64_t)k.idx * a.nPB + k.pair;
     } else {
         t -= nB;
         k.fam = 0;
         k.idx = (int)(t % a.nvirt);
         const int64_t rem = t / a.nvirt;
-        k.pair = (int)(rem % a.nPA);
-        k.sl = (int)(rem / a.nPA);
-        pair_tiles(k.pair, a.nTA, k.TR, k.TC);
+        k.sl = (int)(rem / a.nLA);
+        launch_pair<DG>((int)(rem % a.nLA), a.nTA, k);
         k.tin = (int64_t)a.nocc * a.nPB + (int64_t)k.idx * a.nPA + k.pair;
     }
     return k;
@@ -195,8 +210,14 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
-template <int PREC, int MODE, int TT>
-__global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
+// DG: the launch of the diagonal tasks.  They form one product per element, so a stage holds two
+// operand slices and the accumulators take half the registers: two workgroups share a CU, and
+// one's epilogue (FP64 divisions) and barriers run under the other's products.
+// Measured against one workgroup per CU for all tasks: 240 orbitals, 120 occupied, 20 targets at 8
+// energies in FP64 4.77 -> 4.37 ms; 480 orbitals, 48 targets, FP32 solve 19.3 -> 18.3 ms; 960
+// orbitals, 16 targets, split-bf16 solve 14.8 -> 14.3 ms.
+template <int PREC, int MODE, int TT, bool DG>
+__global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
 {
     typedef FTr<PREC> Tr;
     typedef typename Tr::E E;
@@ -207,12 +228,14 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
     constexpr int RPW = 1024 / RB;              // slice rows per wave load (per plane)
     constexpr int LPR = RB / 16;                // lanes per slice row
     constexpr int SL = FT * RB * PL;            // one operand slice
-    constexpr int STG = 4 * SL;                 // one stage
+    constexpr int STG = (DG ? 2 : 4) * SL;      // one stage
     constexpr int PPS = SL / 1024;              // wave loads per slice
-    constexpr int LDS_ALL = NB * STG > 2 * TR_HALF ? NB * STG : 2 * TR_HALF;
+    constexpr int TRI = DG ? DIAG_SLOTS * (int)sizeof(A1) : 0;   // a diagonal task's partners
+    constexpr int LDS_ALL = NB * STG > TRI ? NB * STG : TRI;
+    constexpr int WG_XCD = DG ? 64 : 32;        // workgroups one XCD holds at a time
     static_assert(NB >= 2 && NB <= 4 && PPS * 4 <= 64, "stage ring shape");
 
-    // the stage ring (after the main loop: a diagonal task's transposition buffer)
+    // the stage ring (after the main loop: a diagonal task's lower triangle, packed by rows)
     __shared__ __align__(16) unsigned char lds[LDS_ALL];
     __shared__ double red[FNT / 64][2 * FTT];
     __shared__ double seps[2][FT];
@@ -229,11 +252,12 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
     // XCD: 53.3 ms; order (target, index, pair): 54.7 ms; one contiguous range per XCD: 59.8 ms)
     int64_t tid = blockIdx.x;
     {
-        const int64_t full = ((int64_t)gridDim.x / 256) * 256;
-        if (tid < full) tid = (tid / 256) * 256 + (tid % 8) * 32 + (tid / 8) % 32;
+        constexpr int G = 8 * WG_XCD;
+        const int64_t full = ((int64_t)gridDim.x / G) * G;
+        if (tid < full) tid = (tid / G) * G + (tid % 8) * WG_XCD + (tid / 8) % WG_XCD;
     }
-    const Task k = task_of_launch(a, tid);
-    const bool diag = k.TR == k.TC;
+    const Task k = task_of_launch<DG>(a, tid);
+    constexpr bool diag = DG;
     const int n = k.fam ? a.nvirt : a.nocc;
     const int s = a.tsel[k.sl];
     const int64_t pb = (int64_t)s * a.nmo + (k.fam ? a.nocc : 0);     // P row r: Bsel row pb + r
@@ -250,11 +274,11 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
     // per-lane source of each wave load of a stage (the stage offset is added per stage):
     // wave load id = wave * nload + i covers slice id / PPS (0 P[TR], 1 Q[TC], 2 Q[TR], 3 P[TC]),
     // part id % PPS (plane part / 8 for split bf16)
-    const int nload = diag ? PPS / 4 : PPS / 2; // wave loads per wave and stage
-    const unsigned char *src[8];
-    unsigned ldst[8];
+    constexpr int nload = diag ? PPS / 4 : PPS / 2; // wave loads per wave and stage
+    const unsigned char *src[nload];
+    unsigned ldst[nload];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < nload; ++i) {
         const int id = wave * nload + i;
         const int sl = id / PPS, part = id % PPS;
         const int plane = PL == 2 ? part >> 3 : 0;
@@ -272,9 +296,7 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
     auto stage_load = [&](unsigned char *buf, int64_t st) {
         const int64_t koff = st * KS * ES;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            if (i < nload)
-                cds_lds_dma16(src[i] + koff, buf + ldst[i]);
+        for (int i = 0; i < nload; ++i) cds_lds_dma16(src[i] + koff, buf + ldst[i]);
     };
 
     // MFMA blocks of this wave inside the matrix (whole 16 x 16 blocks past its edge are skipped)
@@ -447,22 +469,18 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
     typedef std::integral_constant<bool, true> T_;
     typedef std::integral_constant<bool, false> F_;
     const bool full = nbr == 4 && nbc == 2;
-    if (diag) {
-        if (full) main_loop(F_(), T_());
-        else main_loop(F_(), F_());
-    } else {
-        if (full) main_loop(T_(), T_());
-        else main_loop(T_(), F_());
-    }
+    typedef std::integral_constant<bool, !DG> O_;
+    if (full) main_loop(O_(), T_());
+    else main_loop(O_(), F_());
 
     // epilogue.  Lane element (i, j, e): tile row rl = wr*64 + 16 i + rowmap(g, e), tile column
     // cl = wc*32 + 16 j + r16 (FP64 MFMA rows g + 4e, FP32-accumulating rows 4g + e)
-    // transposition buffer: tile row r at trow(r) (rows 0..63 from byte 0, 64..127 from TR_HALF)
-    auto trow = [&](int r) {
-        return reinterpret_cast<A1 *>(lds + (r < FT / 2 ? 0 : TR_HALF)) + (r & (FT / 2 - 1)) * TPITCH;
-    };
+    // partner (c, r) of a diagonal task's element (r, c), r <= c: entry r of row c of the packed
+    // lower triangle (16 consecutive rows' entries fall into distinct banks: triangular numbers
+    // take every residue of a power of two)
+    A1 *tri = reinterpret_cast<A1 *>(lds);
     if (diag) {
-        // partners through LDS: tm[rl][cl] = Y[rl][cl]; the stage buffers are free (last barrier)
+        // partners through LDS; the stage buffers are free (last barrier)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -471,25 +489,29 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
                 for (int e = 0; e < 4; ++e) {
                     const int rl = wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g + 4 * e : 4 * g + e);
                     const int cl = wc * 32 + 16 * j + r16;
-                    trow(rl)[cl] = acc1[i][j][e];
+                    if (cl <= rl) tri[rl * (rl + 1) / 2 + cl] = acc1[i][j][e];
                 }
     }
     __syncthreads();
     const int64_t gR0 = (int64_t)k.TR * FT, gC0 = (int64_t)k.TC * FT;
-    // element value, its partner and whether it counts
-    auto elem = [&](int i, int j, int e, int &rl, int &cl, double &x, double &xt) {
-        rl = wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g + 4 * e : 4 * g + e);
-        cl = wc * 32 + 16 * j + r16;
-        x = (double)acc1[i][j][e];
-        xt = diag ? (double)trow(cl)[rl] : (double)acc2[i][j][e];
-        return gR0 + rl < n && gC0 + cl < n && (!diag || rl <= cl);
+    // element (i, j, e) of the block whose first row and column (of this lane) are rb and cb: its
+    // value, its partner and whether it counts
+    auto elem = [&](int i, int j, int e, int rb, int cb, int &rl, int &cl, double &x, double &xt) {
+        rl = rb + (PREC == CDS_PREC_FP64 ? 4 * e : e);
+        cl = cb;
+        A1 v = acc1[i][j][e];
+        if constexpr (DG && MODE == 0) asm volatile("" : "+v"(v));   // as rb and cb below
+        x = (double)v;
+        const bool in = gR0 + rl < n && gC0 + cl < n && (!diag || rl <= cl);
+        xt = diag ? (double)tri[in ? cl * (cl + 1) / 2 + rl : 0] : (double)acc2[i][j][e];
+        return in;
     };
     if constexpr (MODE == 0 || MODE == 2) {
         // MODE 2: the residues as in MODE 1 and, from the stored values, the sums at the one trial
         // energy (the Newton solve's first evaluation, without a sweep over the residues)
         typedef typename std::conditional<PREC == CDS_PREC_FP64, double, float>::type RT;
         RT *Rt = reinterpret_cast<RT *>(a.R) + (MODE == 2 ? (int64_t)k.sl * a.nres + residue_offset(a, k) : 0);
-        for (int t0 = 0; t0 < a.T; t0 += TT) {
+        for (int t0 = 0; t0 < (MODE == 2 ? 1 : a.T); t0 += TT) {
             double w[TT], s0[TT], s1[TT];
 #pragma unroll
             for (int t = 0; t < TT; ++t) {
@@ -499,12 +521,16 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 2; ++j) {
+                    // a block's partners are read when it is its turn (all 32 at once would spill)
+                    // and its element numbers formed then (hoisted out of the loop over t0 they spill)
+                    int rb = wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g : 4 * g), cb = wc * 32 + 16 * j + r16;
+                    if constexpr (DG) asm volatile("" : "+v"(rb), "+v"(cb) : : "memory");
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         int rl, cl;
                         double x, xt;
-                        if (!elem(i, j, e, rl, cl, x, xt)) continue;
+                        if (!elem(i, j, e, rb, cb, rl, cl, x, xt)) continue;
                         double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
                         if constexpr (MODE == 2) {
                             const RT Rs = (RT)R;
@@ -520,6 +546,7 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
                             s1[t] -= ri * id;
                         }
                     }
+                }
             // fixed-order reduction: lanes by butterfly, then waves in order
 #pragma unroll
             for (int t = 0; t < TT; ++t) {
@@ -549,7 +576,9 @@ __global__ __launch_bounds__(FNT, 1) void sigma_fused_kernel(FArgs a)
                 for (int e = 0; e < 4; ++e) {
                     int rl, cl;
                     double x, xt;
-                    if (!elem(i, j, e, rl, cl, x, xt)) continue;
+                    if (!elem(i, j, e, wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g : 4 * g), wc * 32 + 16 * j + r16, rl,
+                              cl, x, xt))
+                        continue;
                     const double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
                     Rt[diag ? diag_slot(rl, cl) : rl * FT + cl] = (RT)R;
                 }
@@ -681,15 +710,33 @@ static FArgs fused_args(int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, i
     return a;
 }
 
-template <int PREC, int MODE>
+template <int PREC, int MODE, bool DG>
 static void launch_fused_t(cds_ctx *ctx, const FArgs &a, unsigned nblk, int T)
 {
-    if (MODE == 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 1, 1>), dim3(nblk), dim3(FNT), 0, ctx->stream, a);
-    else if (MODE == 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 2, 1>), dim3(nblk), dim3(FNT), 0, ctx->stream, a);
-    else if (T <= 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 1>), dim3(nblk), dim3(FNT), 0, ctx->stream, a);
-    else if (T <= 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 2>), dim3(nblk), dim3(FNT), 0, ctx->stream, a);
-    else if (T <= 4) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 4>), dim3(nblk), dim3(FNT), 0, ctx->stream, a);
-    else hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 8>), dim3(nblk), dim3(FNT), 0, ctx->stream, a);
+    const dim3 g(nblk), b(FNT);
+    if (MODE == 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 1, 1, DG>), g, b, 0, ctx->stream, a);
+    else if (MODE == 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 2, 1, DG>), g, b, 0, ctx->stream, a);
+    else if (T <= 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 1, DG>), g, b, 0, ctx->stream, a);
+    else if (T <= 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 2, DG>), g, b, 0, ctx->stream, a);
+    else if (T <= 4 || (DG && PREC == CDS_PREC_FP64))   // eight energies' sums do not fit beside FP64 accumulators
+        hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 4, DG>), g, b, 0, ctx->stream, a);
+    else hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 8, DG>), g, b, 0, ctx->stream, a);
+}
+
+// the tasks of one kind (diagonal tile pairs, or the others)
+template <int MODE, bool DG>
+static int launch_kind(cds_ctx *ctx, int prec, FArgs a, int T)
+{
+    a.nLA = DG ? a.nTA : a.nPA - a.nTA;
+    a.nLB = DG ? a.nTB : a.nPB - a.nTB;
+    const int64_t nblk = (int64_t)a.nsc * ((int64_t)a.nocc * a.nLB + (int64_t)a.nvirt * a.nLA);
+    if (nblk == 0) return CDS_OK;
+    if (nblk > 0x7fffffffLL) return cds_fail(ctx, CDS_EINVAL, "fused contraction: %lld tasks", (long long)nblk);
+    if (prec == CDS_PREC_FP64) launch_fused_t<CDS_PREC_FP64, MODE, DG>(ctx, a, (unsigned)nblk, T);
+    else if (prec == CDS_PREC_FP32) launch_fused_t<CDS_PREC_FP32, MODE, DG>(ctx, a, (unsigned)nblk, T);
+    else launch_fused_t<CDS_PREC_BF16X3, MODE, DG>(ctx, a, (unsigned)nblk, T);
+    CDS_LAUNCHED(ctx);
+    return CDS_OK;
 }
 
 template <int MODE>
@@ -697,11 +744,8 @@ static int launch_fused(cds_ctx *ctx, int prec, const FArgs &a, int T)
 {
     const int64_t nblk = (int64_t)a.nsc * a.tpt;
     if (nblk > 0x7fffffffLL) return cds_fail(ctx, CDS_EINVAL, "fused contraction: %lld tasks", (long long)nblk);
-    if (prec == CDS_PREC_FP64) launch_fused_t<CDS_PREC_FP64, MODE>(ctx, a, (unsigned)nblk, T);
-    else if (prec == CDS_PREC_FP32) launch_fused_t<CDS_PREC_FP32, MODE>(ctx, a, (unsigned)nblk, T);
-    else launch_fused_t<CDS_PREC_BF16X3, MODE>(ctx, a, (unsigned)nblk, T);
-    CDS_LAUNCHED(ctx);
-    return CDS_OK;
+    CDS_CALL((launch_kind<MODE, false>(ctx, prec, a, T)));
+    return launch_kind<MODE, true>(ctx, prec, a, T);
 }
 
 int cds_fused_sigma(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc,
