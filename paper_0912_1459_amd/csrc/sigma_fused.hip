@@ -18,8 +18,8 @@
 // straight from global memory into a ring of LDS stages (global_load_lds_dwordx4; four stages of
 // 32 KB in FP64 and FP32, two of 64 KB in split bf16), one barrier per stage, the 16-byte chunks
 // of a row XOR-swizzled so the fragment reads of consecutive rows hit distinct banks; 16 x 16
-// MFMA blocks entirely past the matrix edge are skipped.  Tasks are ordered so that those sharing their P
-// operand slices run at the same time on one XCD.
+// MFMA blocks entirely past the matrix edge are skipped.  Tasks are ordered so that those sharing their
+// operand slices (P: the target, Q: the fixed index) run at the same time on one XCD.
 //
 // SIGMA mode: each workgroup sums R / d and -R / d^2 over its elements at T trial energies in
 // FP64 (fixed order) and writes one partial per trial energy; a second kernel adds the partials
@@ -37,9 +37,13 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 constexpr int FT = 128;                         // tile edge
-constexpr int FNT = 512;                        // threads per workgroup: 8 waves, 2 (rows) x 4 (cols)
 constexpr int DIAG_SLOTS = FT * (FT + 1) / 2;   // residues of a diagonal task
 constexpr int OFF_SLOTS = FT * FT;              // residues of an off-diagonal task
+constexpr int NWC = 4, WP = 2 * NWC;            // waves across a product's columns; waves per product
+constexpr int fused_threads(bool dg) { return (dg ? WP : 2 * WP) * 64; }
+// targets of a group of tasks that run together on an XCD.  960 orbitals, 16 targets: whole
+// split-bf16 solve 14.4 ms with a group of one, 13.0 (2), 12.5 (4), 13.3 (8), 13.8 ms (16)
+constexpr int TGS = 4;
 constexpr int FTT = 8;                          // trial energies per epilogue pass (at most)
 
 template <int PREC> struct FTr;
@@ -126,29 +130,36 @@ __device__ __forceinline__ void launch_pair(int p, int n, Task &k)
     k.pair = r * n - r * (r - 1) / 2 + (k.TC - k.TR);
 }
 
-// launch order: part B tasks by (target, pair, i), then part A tasks by (target, pair, a): runs of
-// tasks that share the P operand slices (rows of Bsel for one target) and differ only in the Q rows
+// launch order: part B tasks, then part A tasks; within a part by (pair, group of TGS targets,
+// fixed index, target in the group), so the tasks that one XCD runs at a time are a few fixed
+// indices times TGS targets and share both the P slices (rows of Bsel: pair and target) and the
+// Q slices (rows of Bvo: pair and fixed index)
 template <bool DG>
 __device__ __forceinline__ Task task_of_launch(const FArgs &a, int64_t t)
 {
     Task k;
     const int64_t nB = (int64_t)a.nocc * a.nsc * a.nLB;
-    if (t < nB) {
-        k.fam = 1;
-        k.idx = (int)(t % a.nocc);
-        const int64_t rem = t / a.nocc;
-        k.sl = (int)(rem / a.nLB);
-        launch_pair<DG>((int)(rem % a.nLB), a.nTB, k);
-        k.tin = (int64_t)k.idx * a.nPB + k.pair;
+    k.fam = t < nB;
+    if (!k.fam) t -= nB;
+    const int nidx = k.fam ? a.nocc : a.nvirt;
+    const int64_t per = (int64_t)a.nsc * nidx;
+    const int pl = (int)(t / per);
+    int64_t u = t - pl * per;
+    const int full = a.nsc / TGS * TGS;         // targets in whole groups
+    int s0 = 0, sz = TGS;
+    if (u < (int64_t)full * nidx) {
+        const int grp = (int)(u / ((int64_t)TGS * nidx));
+        s0 = grp * TGS;
+        u -= (int64_t)s0 * nidx;
     } else {
-        t -= nB;
-        k.fam = 0;
-        k.idx = (int)(t % a.nvirt);
-        const int64_t rem = t / a.nvirt;
-        k.sl = (int)(rem / a.nLA);
-        launch_pair<DG>((int)(rem % a.nLA), a.nTA, k);
-        k.tin = (int64_t)a.nocc * a.nPB + (int64_t)k.idx * a.nPA + k.pair;
+        s0 = full;
+        sz = a.nsc - full;
+        u -= (int64_t)full * nidx;
     }
+    k.idx = (int)(u / sz);
+    k.sl = s0 + (int)(u - (int64_t)k.idx * sz);
+    launch_pair<DG>(pl, k.fam ? a.nTB : a.nTA, k);
+    k.tin = k.fam ? (int64_t)k.idx * a.nPB + k.pair : (int64_t)a.nocc * a.nPB + (int64_t)k.idx * a.nPA + k.pair;
     return k;
 }
 
@@ -210,46 +221,47 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
-// DG: the launch of the diagonal tasks.  They form one product per element, so a stage holds two
-// operand slices and the accumulators take half the registers: two workgroups share a CU, and
-// one's epilogue (FP64 divisions) and barriers run under the other's products.
-// Measured against one workgroup per CU for all tasks: 240 orbitals, 120 occupied, 20 targets at 8
-// energies in FP64 4.77 -> 4.37 ms; 480 orbitals, 48 targets, FP32 solve 19.3 -> 18.3 ms; 960
-// orbitals, 16 targets, split-bf16 solve 14.8 -> 14.3 ms.
+// DG: the launch of the diagonal tasks.  They form one product per element and a stage holds two
+// operand slices, so two workgroups share a CU, and one's epilogue (FP64 divisions) and barriers
+// run under the other's products.  An off-diagonal task's two products go to two sets of waves:
+// four waves per SIMD in FP64 and FP32, each with one product's accumulators.
 template <int PREC, int MODE, int TT, bool DG>
-__global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
+__global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs a)
 {
     typedef FTr<PREC> Tr;
     typedef typename Tr::E E;
     typedef typename Tr::A1 A1;
     typedef typename Tr::Acc Acc;
     constexpr int KS = Tr::KS, RB = Tr::RB, PL = Tr::PL, NB = Tr::NB;
+    constexpr int NWV = DG ? WP : 2 * WP;       // waves
+    constexpr int NT = NWV * 64;
+    constexpr int CW = FT / NWC, J = CW / 16;   // columns and 16-column blocks per wave
     constexpr int ES = (int)sizeof(E);
     constexpr int RPW = 1024 / RB;              // slice rows per wave load (per plane)
     constexpr int LPR = RB / 16;                // lanes per slice row
     constexpr int SL = FT * RB * PL;            // one operand slice
     constexpr int STG = (DG ? 2 : 4) * SL;      // one stage
     constexpr int PPS = SL / 1024;              // wave loads per slice
-    constexpr int TRI = DG ? DIAG_SLOTS * (int)sizeof(A1) : 0;   // a diagonal task's partners
-    constexpr int LDS_ALL = NB * STG > TRI ? NB * STG : TRI;
+    // after the main loop: a diagonal task's lower triangle, or the blocks the two products of an
+    // off-diagonal task hand each other (half a tile each)
+    constexpr int XCH = (DG ? DIAG_SLOTS : FT * FT) * (int)sizeof(A1);
+    constexpr int LDS_ALL = NB * STG > XCH ? NB * STG : XCH;
     constexpr int WG_XCD = DG ? 64 : 32;        // workgroups one XCD holds at a time
     static_assert(NB >= 2 && NB <= 4 && PPS * 4 <= 64, "stage ring shape");
 
-    // the stage ring (after the main loop: a diagonal task's lower triangle, packed by rows)
+    // the stage ring
     __shared__ __align__(16) unsigned char lds[LDS_ALL];
-    __shared__ double red[FNT / 64][2 * FTT];
+    __shared__ double red[NWV][2 * FTT];
     __shared__ double seps[2][FT];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
-    const int wr = wave >> 2, wc = wave & 3;
-    // workgroups are dealt to the 8 XCDs in turn; each group of 256 consecutive workgroups takes
-    // 256 consecutive tasks, 32 per XCD, so the 32 tasks one XCD runs at a time read the same P
-    // slices (one target, one tile pair) from its L2 and differ only in their Q rows.  Large
-    // workload, FP64 residues: 57.0 ms in the order (index, target, pair) dealt round robin, 53.9
-    // ms in the order (target, pair, index) dealt round robin, 53.3 ms with 32 per XCD (64 per
-    // XCD: 53.3 ms; order (target, index, pair): 54.7 ms; one contiguous range per XCD: 59.8 ms)
+    const int prod = wave / WP, wp = wave % WP;   // product (0: Y[TR][TC], 1: Y[TC][TR]^T), wave within
+    const int wr = wp / NWC, wc = wp % NWC;
+    // workgroups are dealt to the 8 XCDs in turn; each run of 8 WG_XCD consecutive workgroups takes
+    // that many consecutive tasks, WG_XCD per XCD, so the tasks one XCD runs at a time are
+    // consecutive and read the same slices from its L2
     int64_t tid = blockIdx.x;
     {
         constexpr int G = 8 * WG_XCD;
@@ -265,8 +277,8 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
     const int64_t qs = k.fam ? a.nocc : 1;                            // Q row c: Bvo row qb + c qs
     const int ebase = k.fam ? a.nocc : 0;
     const double e0 = a.eps[k.fam ? k.idx : a.nocc + k.idx];
-    if (threadIdx.x < 2 * FT) {
-        const int side = threadIdx.x / FT, rr = threadIdx.x % FT;
+    for (int q = threadIdx.x; q < 2 * FT; q += NT) {
+        const int side = q / FT, rr = q % FT;
         const int gr = min((side ? k.TC : k.TR) * FT + rr, n - 1);
         seps[side][rr] = a.eps[ebase + gr];
     }
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
     // per-lane source of each wave load of a stage (the stage offset is added per stage):
     // wave load id = wave * nload + i covers slice id / PPS (0 P[TR], 1 Q[TC], 2 Q[TR], 3 P[TC]),
     // part id % PPS (plane part / 8 for split bf16)
-    constexpr int nload = diag ? PPS / 4 : PPS / 2; // wave loads per wave and stage
+    constexpr int nload = (DG ? 2 : 4) * PPS / NWV; // wave loads per wave and stage
     const unsigned char *src[nload];
     unsigned ldst[nload];
 #pragma unroll
@@ -300,122 +312,78 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
     };
 
     // MFMA blocks of this wave inside the matrix (whole 16 x 16 blocks past its edge are skipped)
-    const int r0 = k.TR * FT + wr * 64, c0 = k.TC * FT + wc * 32;
+    const int r0 = k.TR * FT + wr * 64, c0 = k.TC * FT + wc * CW;
     const int nbr = __builtin_amdgcn_readfirstlane(max(0, min(4, (n - r0 + 15) / 16)));
-    const int nbc = __builtin_amdgcn_readfirstlane(max(0, min(2, (n - c0 + 15) / 16)));
+    const int nbc = __builtin_amdgcn_readfirstlane(max(0, min(J, (n - c0 + 15) / 16)));
 
-    Acc acc1[4][2], acc2[4][2];
+    Acc acc[4][J];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < J; ++j)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc1[i][j][e] = acc2[i][j][e] = 0;
+            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0;
 
     // fragment address of slice sl, slice row rr, logical chunk lc (plane pl)
     auto frag = [&](const unsigned char *buf, int sl, int pl, int rr, int lc) {
         return buf + sl * SL + pl * 8192 + rr * RB + chunk_pos<RB>(lc, rr) * 16;
     };
-    // one stage of products: acc1 += P[TR] Q[TC]^T, and off the diagonal acc2 += Q[TR] P[TC]^T.
+    // one stage of this wave's product: P[TR] Q[TC]^T (slices 0, 1), or Q[TR] P[TC]^T (slices 2, 3).
     // Consecutive MFMAs go to different accumulators (each k slot over all blocks in turn).
-    auto compute = [&](const unsigned char *buf, auto OFFc, auto FULLc) {
-        constexpr bool off = decltype(OFFc)::value;
+    const int slA = 2 * prod, slB = 2 * prod + 1;
+    auto compute = [&](const unsigned char *buf, auto FULLc) {
         constexpr bool full = decltype(FULLc)::value;
         auto on = [&](int i, int j) { return full || (i < nbr && j < nbc); };
-        if constexpr (PREC == CDS_PREC_FP64) {
-#pragma unroll
-            for (int h = 0; h < RB / 64; ++h) {
-                const int lc = g + 4 * h;
-                double2 fa[4], fb[2], ga[4], gb[2];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    fa[i] = *reinterpret_cast<const double2 *>(frag(buf, 0, 0, wr * 64 + 16 * i + r16, lc));
-                    if (off) ga[i] = *reinterpret_cast<const double2 *>(frag(buf, 2, 0, wr * 64 + 16 * i + r16, lc));
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    fb[j] = *reinterpret_cast<const double2 *>(frag(buf, 1, 0, wc * 32 + 16 * j + r16, lc));
-                    if (off) gb[j] = *reinterpret_cast<const double2 *>(frag(buf, 3, 0, wc * 32 + 16 * j + r16, lc));
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        if (on(i, j)) {
-                            acc1[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i].x, fb[j].x, acc1[i][j], 0, 0, 0);
-                            if (off) acc2[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[i].x, gb[j].x, acc2[i][j], 0, 0, 0);
-                        }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        if (on(i, j)) {
-                            acc1[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i].y, fb[j].y, acc1[i][j], 0, 0, 0);
-                            if (off) acc2[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ga[i].y, gb[j].y, acc2[i][j], 0, 0, 0);
-                        }
-            }
-        } else if constexpr (PREC == CDS_PREC_FP32) {
-#pragma unroll
-            for (int h = 0; h < RB / 64; ++h) {
-                const int lc = g + 4 * h;
-                float4 fa[4], fb[2], ga[4], gb[2];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    fa[i] = *reinterpret_cast<const float4 *>(frag(buf, 0, 0, wr * 64 + 16 * i + r16, lc));
-                    if (off) ga[i] = *reinterpret_cast<const float4 *>(frag(buf, 2, 0, wr * 64 + 16 * i + r16, lc));
-                }
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    fb[j] = *reinterpret_cast<const float4 *>(frag(buf, 1, 0, wc * 32 + 16 * j + r16, lc));
-                    if (off) gb[j] = *reinterpret_cast<const float4 *>(frag(buf, 3, 0, wc * 32 + 16 * j + r16, lc));
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < 2; ++j)
-                            if (on(i, j)) {
-                                acc1[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc1[i][j], 0, 0, 0);
-                                if (off) acc2[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ga[i][q], gb[j][q], acc2[i][j], 0, 0, 0);
-                            }
-            }
-        } else {
-            bf16x8 ah[4], al[4], bh[2], bl[2], gh[4], gl[4], hh[2], hl[2];
+        if constexpr (PREC == CDS_PREC_BF16X3) {
+            bf16x8 ah[4], al[4], bh[J], bl[J];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int rr = wr * 64 + 16 * i + r16;
-                ah[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, 0, 0, rr, g));
-                al[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, 0, 1, rr, g));
-                if (off) {
-                    gh[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, 2, 0, rr, g));
-                    gl[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, 2, 1, rr, g));
-                }
+                ah[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, slA, 0, rr, g));
+                al[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, slA, 1, rr, g));
             }
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int rr = wc * 32 + 16 * j + r16;
-                bh[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, 1, 0, rr, g));
-                bl[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, 1, 1, rr, g));
-                if (off) {
-                    hh[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, 3, 0, rr, g));
-                    hl[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, 3, 1, rr, g));
-                }
+            for (int j = 0; j < J; ++j) {
+                const int rr = wc * CW + 16 * j + r16;
+                bh[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, slB, 0, rr, g));
+                bl[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, slB, 1, rr, g));
             }
 #pragma unroll
             for (int q = 0; q < 3; ++q)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-                        if (on(i, j)) {
-                            // lo*hi, hi*lo, then hi*hi (smallest terms first)
-                            acc1[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q == 0 ? al[i] : ah[i], q == 1 ? bl[j] : bh[j],
-                                                                                 acc1[i][j], 0, 0, 0);
-                            if (off)
-                                acc2[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q == 0 ? gl[i] : gh[i], q == 1 ? hl[j] : hh[j],
-                                                                                     acc2[i][j], 0, 0, 0);
-                        }
+                    for (int j = 0; j < J; ++j)
+                        if (on(i, j))   // lo*hi, hi*lo, then hi*hi (smallest terms first)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q == 0 ? al[i] : ah[i], q == 1 ? bl[j] : bh[j],
+                                                                                acc[i][j], 0, 0, 0);
+        } else {
+            typedef typename std::conditional<PREC == CDS_PREC_FP64, double2, float4>::type V;
+            constexpr int NV = 16 / ES;
+#pragma unroll
+            for (int h = 0; h < RB / 64; ++h) {
+                const int lc = g + 4 * h;
+                V fa[4], fb[J];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    fa[i] = *reinterpret_cast<const V *>(frag(buf, slA, 0, wr * 64 + 16 * i + r16, lc));
+#pragma unroll
+                for (int j = 0; j < J; ++j)
+                    fb[j] = *reinterpret_cast<const V *>(frag(buf, slB, 0, wc * CW + 16 * j + r16, lc));
+#pragma unroll
+                for (int q = 0; q < NV; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int j = 0; j < J; ++j)
+                            if (on(i, j)) {
+                                if constexpr (PREC == CDS_PREC_FP64)
+                                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(q ? fa[i].y : fa[i].x, q ? fb[j].y : fb[j].x,
+                                                                                     acc[i][j], 0, 0, 0);
+                                else
+                                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+                            }
+            }
         }
     };
 
@@ -424,9 +392,8 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
     // have landed and every wave is done with stage st-1) the freed buffer takes stage st+NB-1.
     // With two stages (split bf16) the next stage's loads are issued before the barrier instead,
     // and a second barrier frees the buffer read (measured faster there).
-    auto main_loop = [&](auto OFFc, auto FULLc) {
-        constexpr bool off = decltype(OFFc)::value;
-        constexpr int NL = off ? PPS / 2 : PPS / 4;   // wave loads per wave and stage
+    auto main_loop = [&](auto FULLc) {
+        constexpr int NL = nload;
         const int64_t ns = a.ns;
         if constexpr (NB == 2) {
             auto step = [&](unsigned char *cur, unsigned char *nxt, int64_t st) {
@@ -437,7 +404,7 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
                     wait_vm<0>();
                 }
                 __builtin_amdgcn_s_barrier();         // ... and every wave's
-                compute(cur, OFFc, FULLc);
+                compute(cur, FULLc);
                 __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS reads are done
                 __builtin_amdgcn_s_barrier();         // cur may be refilled
             };
@@ -460,7 +427,7 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");            // no LDS read moves above the barrier
             if (st + NB - 1 < ns) stage_load(lds + ((st + NB - 1) % NB) * STG, st + NB - 1);
-            compute(lds + (st % NB) * STG, OFFc, FULLc);
+            compute(lds + (st % NB) * STG, FULLc);
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): this wave's LDS reads are done
         __builtin_amdgcn_s_barrier();                 // ... and every wave's: the ring is free
@@ -468,44 +435,57 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
     };
     typedef std::integral_constant<bool, true> T_;
     typedef std::integral_constant<bool, false> F_;
-    const bool full = nbr == 4 && nbc == 2;
-    typedef std::integral_constant<bool, !DG> O_;
-    if (full) main_loop(O_(), T_());
-    else main_loop(O_(), F_());
+    if (nbr == 4 && nbc == J) main_loop(T_());
+    else main_loop(F_());
 
     // epilogue.  Lane element (i, j, e): tile row rl = wr*64 + 16 i + rowmap(g, e), tile column
-    // cl = wc*32 + 16 j + r16 (FP64 MFMA rows g + 4e, FP32-accumulating rows 4g + e)
-    // partner (c, r) of a diagonal task's element (r, c), r <= c: entry r of row c of the packed
-    // lower triangle (16 consecutive rows' entries fall into distinct banks: triangular numbers
-    // take every residue of a power of two)
+    // cl = wc*CW + 16 j + r16 (FP64 MFMA rows g + 4e, FP32-accumulating rows 4g + e).
+    // A diagonal task's partner (c, r) of element (r, c), r <= c: entry r of row c of its lower
+    // triangle, packed in LDS (16 consecutive rows' entries fall into distinct banks: triangular
+    // numbers take every residue of a power of two).  The two products of an off-diagonal task
+    // hold both partners in the same lane of two waves: product 0's waves take the blocks
+    // i = 0, 1 and product 1's the blocks i = 2, 3, each handing the other the blocks it does not
+    // take (R is symmetric in the two).
     A1 *tri = reinterpret_cast<A1 *>(lds);
-    if (diag) {
-        // partners through LDS; the stage buffers are free (last barrier)
+    Acc *xch = reinterpret_cast<Acc *>(lds);    // [product][wave][2][J][lane]
+    constexpr int NI = DG ? 4 : 2;              // block rows this wave takes, from i0
+    const int i0 = DG ? 0 : 2 * prod;
+    if constexpr (DG) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < J; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int rl = wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g + 4 * e : 4 * g + e);
-                    const int cl = wc * 32 + 16 * j + r16;
-                    if (cl <= rl) tri[rl * (rl + 1) / 2 + cl] = acc1[i][j][e];
+                    const int cl = wc * CW + 16 * j + r16;
+                    if (cl <= rl) tri[rl * (rl + 1) / 2 + cl] = acc[i][j][e];
                 }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                xch[(((prod * WP + wp) * 2 + i) * J + j) * 64 + lane] = prod ? acc[i][j] : acc[i + 2][j];
+                if (prod) acc[i][j] = acc[i + 2][j];
+            }
     }
     __syncthreads();
     const int64_t gR0 = (int64_t)k.TR * FT, gC0 = (int64_t)k.TC * FT;
-    // element (i, j, e) of the block whose first row and column (of this lane) are rb and cb: its
-    // value, its partner and whether it counts
-    auto elem = [&](int i, int j, int e, int rb, int cb, int &rl, int &cl, double &x, double &xt) {
+    // element (i, j, e) (block row i0 + i) of the block whose first row and column (of this lane)
+    // are rb and cb: its value, its partner and whether it counts
+    auto elem = [&](int i, int j, int e, int rb, int cb, const Acc &oth, int &rl, int &cl, double &x, double &xt) {
         rl = rb + (PREC == CDS_PREC_FP64 ? 4 * e : e);
         cl = cb;
-        A1 v = acc1[i][j][e];
-        if constexpr (DG && MODE == 0) asm volatile("" : "+v"(v));   // as rb and cb below
+        A1 v = acc[i][j][e];
+        if constexpr (MODE == 0) asm volatile("" : "+v"(v));   // as rb and cb below
         x = (double)v;
         const bool in = gR0 + rl < n && gC0 + cl < n && (!diag || rl <= cl);
-        xt = diag ? (double)tri[in ? cl * (cl + 1) / 2 + rl : 0] : (double)acc2[i][j][e];
+        xt = diag ? (double)tri[in ? cl * (cl + 1) / 2 + rl : 0] : (double)oth[e];
         return in;
     };
+    auto first_row = [&](int i) { return wr * 64 + 16 * (i0 + i) + (PREC == CDS_PREC_FP64 ? g : 4 * g); };
+    auto other = [&](int i, int j) { return DG ? Acc{} : xch[((((1 - prod) * WP + wp) * 2 + i) * J + j) * 64 + lane]; };
     if constexpr (MODE == 0 || MODE == 2) {
         // MODE 2: the residues as in MODE 1 and, from the stored values, the sums at the one trial
         // energy (the Newton solve's first evaluation, without a sweep over the residues)
@@ -519,18 +499,19 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
                 s0[t] = s1[t] = 0.0;
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < NI; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
+                for (int j = 0; j < J; ++j) {
                     // a block's partners are read when it is its turn (all 32 at once would spill)
                     // and its element numbers formed then (hoisted out of the loop over t0 they spill)
-                    int rb = wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g : 4 * g), cb = wc * 32 + 16 * j + r16;
-                    if constexpr (DG) asm volatile("" : "+v"(rb), "+v"(cb) : : "memory");
+                    int rb = first_row(i), cb = wc * CW + 16 * j + r16;
+                    asm volatile("" : "+v"(rb), "+v"(cb) : : "memory");
+                    const Acc oth = other(i, j);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         int rl, cl;
                         double x, xt;
-                        if (!elem(i, j, e, rb, cb, rl, cl, x, xt)) continue;
+                        if (!elem(i, j, e, rb, cb, oth, rl, cl, x, xt)) continue;
                         double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
                         if constexpr (MODE == 2) {
                             const RT Rs = (RT)R;
@@ -560,7 +541,7 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
             if (threadIdx.x < 2 * TT && t0 + (int)threadIdx.x / 2 < a.T) {
                 double v = 0.0;
 #pragma unroll
-                for (int w8 = 0; w8 < FNT / 64; ++w8) v += red[w8][threadIdx.x];
+                for (int w8 = 0; w8 < NWV; ++w8) v += red[w8][threadIdx.x];
                 a.part[(((int64_t)k.sl * a.tpt + k.tin) * a.T + t0) * 2 + threadIdx.x] = v;
             }
             __syncthreads();
@@ -569,19 +550,19 @@ __global__ __launch_bounds__(FNT, DG ? 4 : 1) void sigma_fused_kernel(FArgs a)
         typedef typename std::conditional<PREC == CDS_PREC_FP64, double, float>::type RT;
         RT *Rt = reinterpret_cast<RT *>(a.R) + (int64_t)k.sl * a.nres + residue_offset(a, k);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < J; ++j) {
+                const Acc oth = other(i, j);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     int rl, cl;
                     double x, xt;
-                    if (!elem(i, j, e, wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g : 4 * g), wc * 32 + 16 * j + r16, rl,
-                              cl, x, xt))
-                        continue;
+                    if (!elem(i, j, e, first_row(i), wc * CW + 16 * j + r16, oth, rl, cl, x, xt)) continue;
                     const double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
                     Rt[diag ? diag_slot(rl, cl) : rl * FT + cl] = (RT)R;
                 }
+            }
     }
 }
 
@@ -713,7 +694,7 @@ static FArgs fused_args(int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, i
 template <int PREC, int MODE, bool DG>
 static void launch_fused_t(cds_ctx *ctx, const FArgs &a, unsigned nblk, int T)
 {
-    const dim3 g(nblk), b(FNT);
+    const dim3 g(nblk), b(fused_threads(DG));
     if (MODE == 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 1, 1, DG>), g, b, 0, ctx->stream, a);
     else if (MODE == 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 2, 1, DG>), g, b, 0, ctx->stream, a);
     else if (T <= 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 1, DG>), g, b, 0, ctx->stream, a);
