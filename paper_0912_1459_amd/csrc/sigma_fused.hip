@@ -39,7 +39,7 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 constexpr int FT = 128;                         // tile edge
 constexpr int DIAG_SLOTS = FT * (FT + 1) / 2;   // residues of a diagonal task
 constexpr int OFF_SLOTS = FT * FT;              // residues of an off-diagonal task
-constexpr int NWC = 4, WP = 2 * NWC;            // waves across a product's columns; waves per product
+constexpr int WP = 8;                           // waves per product
 constexpr int fused_threads(bool dg) { return (dg ? WP : 2 * WP) * 64; }
 // targets of a group of tasks that run together on an XCD.  960 orbitals, 16 targets: whole
 // split-bf16 solve 14.4 ms with a group of one, 13.0 (2), 12.5 (4), 13.3 (8), 13.8 ms (16)
@@ -235,7 +235,6 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
     constexpr int KS = Tr::KS, RB = Tr::RB, PL = Tr::PL, NB = Tr::NB;
     constexpr int NWV = DG ? WP : 2 * WP;       // waves
     constexpr int NT = NWV * 64;
-    constexpr int CW = FT / NWC, J = CW / 16;   // columns and 16-column blocks per wave
     constexpr int ES = (int)sizeof(E);
     constexpr int RPW = 1024 / RB;              // slice rows per wave load (per plane)
     constexpr int LPR = RB / 16;                // lanes per slice row
@@ -258,7 +257,6 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
     const int prod = wave / WP, wp = wave % WP;   // product (0: Y[TR][TC], 1: Y[TC][TR]^T), wave within
-    const int wr = wp / NWC, wc = wp % NWC;
     // workgroups are dealt to the 8 XCDs in turn; each run of 8 WG_XCD consecutive workgroups takes
     // that many consecutive tasks, WG_XCD per XCD, so the tasks one XCD runs at a time are
     // consecutive and read the same slices from its L2
@@ -311,79 +309,80 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
         for (int i = 0; i < nload; ++i) cds_lds_dma16(src[i] + koff, buf + ldst[i]);
     };
 
-    // MFMA blocks of this wave inside the matrix (whole 16 x 16 blocks past its edge are skipped)
-    const int r0 = k.TR * FT + wr * 64, c0 = k.TC * FT + wc * CW;
-    const int nbr = __builtin_amdgcn_readfirstlane(max(0, min(4, (n - r0 + 15) / 16)));
-    const int nbc = __builtin_amdgcn_readfirstlane(max(0, min(J, (n - c0 + 15) / 16)));
+    // The product's nr x nc blocks of 16 x 16 that reach into the matrix, dealt to its 8 waves:
+    // 2 x 4 waves of up to 4 x 2 blocks each, the rows and columns shared out evenly, or (strip) a
+    // row of blocks per wave, whichever gives the busiest wave fewer.  With fixed 64 x 32 parts a
+    // tile of 72 columns cost as much as a whole one (840 virtuals: 6 of 21 off-diagonal pairs;
+    // the whole FP64 step of 960 orbitals, 16 targets: 84.4 -> 82.1 ms).
+    const int nr = __builtin_amdgcn_readfirstlane(min(8, (n - k.TR * FT + 15) / 16));
+    const int nc = __builtin_amdgcn_readfirstlane(min(8, (n - k.TC * FT + 15) / 16));
+    const int rs = (nr + 1) / 2, cs = (nc + 3) / 4;
+    const bool strip = nc < rs * cs;
+    const int rb0 = strip ? wp : (wp >> 2) * rs, cb0 = strip ? 0 : (wp & 3) * cs;   // first block row, column
+    const int nbr = strip ? (wp < nr ? 1 : 0) : max(0, min(rs, nr - rb0));
+    const int nbc = strip ? nc : max(0, min(cs, nc - cb0));
 
-    Acc acc[4][J];
+    // block b of the wave: row rb0 + b / 2 and column cb0 + b % 2, or (strip) row rb0, column b
+    Acc acc[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int b = 0; b < 8; ++b)
 #pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i][j][e] = 0;
+        for (int e = 0; e < 4; ++e) acc[b][e] = 0;
+    auto mine = [&](int b) { return strip ? (nbr && b < nbc) : ((b >> 1) < nbr && (b & 1) < nbc); };
 
-    // fragment address of slice sl, slice row rr, logical chunk lc (plane pl)
-    auto frag = [&](const unsigned char *buf, int sl, int pl, int rr, int lc) {
-        return buf + sl * SL + pl * 8192 + rr * RB + chunk_pos<RB>(lc, rr) * 16;
-    };
-    // one stage of this wave's product: P[TR] Q[TC]^T (slices 0, 1), or Q[TR] P[TC]^T (slices 2, 3).
-    // Consecutive MFMAs go to different accumulators (each k slot over all blocks in turn).
-    const int slA = 2 * prod, slB = 2 * prod + 1;
-    auto compute = [&](const unsigned char *buf, auto FULLc) {
+    // this wave's fragments of a stage: 16 rows x 16 bytes per lane group g of block rows rb0 .. of
+    // P[TR] (slice 0) against Q[TC] (slice 1), or Q[TR] (slice 2) against P[TC] (slice 3)
+    const int fo = r16 * RB + chunk_pos<RB>(g, r16) * 16;
+    const int fA = 2 * prod * SL + rb0 * 16 * RB + fo, fB = (2 * prod + 1) * SL + cb0 * 16 * RB + fo;
+    // one stage of products, NA x NJ blocks per wave (4 x 2, or 1 x 8 in strips).  Consecutive
+    // MFMAs go to different accumulators (each k slot over all blocks in turn).
+    auto compute = [&](const unsigned char *buf, auto NAc, auto FULLc) {
+        constexpr int NA = decltype(NAc)::value, NJ = 8 / NA;
         constexpr bool full = decltype(FULLc)::value;
         auto on = [&](int i, int j) { return full || (i < nbr && j < nbc); };
         if constexpr (PREC == CDS_PREC_BF16X3) {
-            bf16x8 ah[4], al[4], bh[J], bl[J];
+            bf16x8 ah[NA], al[NA], bh[NJ], bl[NJ];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int rr = wr * 64 + 16 * i + r16;
-                ah[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, slA, 0, rr, g));
-                al[i] = *reinterpret_cast<const bf16x8 *>(frag(buf, slA, 1, rr, g));
+            for (int i = 0; i < NA; ++i) {
+                ah[i] = *reinterpret_cast<const bf16x8 *>(buf + fA + i * 16 * RB);
+                al[i] = *reinterpret_cast<const bf16x8 *>(buf + fA + 8192 + i * 16 * RB);
             }
 #pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int rr = wc * CW + 16 * j + r16;
-                bh[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, slB, 0, rr, g));
-                bl[j] = *reinterpret_cast<const bf16x8 *>(frag(buf, slB, 1, rr, g));
+            for (int j = 0; j < NJ; ++j) {
+                bh[j] = *reinterpret_cast<const bf16x8 *>(buf + fB + j * 16 * RB);
+                bl[j] = *reinterpret_cast<const bf16x8 *>(buf + fB + 8192 + j * 16 * RB);
             }
 #pragma unroll
             for (int q = 0; q < 3; ++q)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < NA; ++i)
 #pragma unroll
-                    for (int j = 0; j < J; ++j)
+                    for (int j = 0; j < NJ; ++j)
                         if (on(i, j))   // lo*hi, hi*lo, then hi*hi (smallest terms first)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q == 0 ? al[i] : ah[i], q == 1 ? bl[j] : bh[j],
-                                                                                acc[i][j], 0, 0, 0);
+                            acc[i * NJ + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                q == 0 ? al[i] : ah[i], q == 1 ? bl[j] : bh[j], acc[i * NJ + j], 0, 0, 0);
         } else {
             typedef typename std::conditional<PREC == CDS_PREC_FP64, double2, float4>::type V;
             constexpr int NV = 16 / ES;
+            V fa[NA], fb[NJ];
 #pragma unroll
-            for (int h = 0; h < RB / 64; ++h) {
-                const int lc = g + 4 * h;
-                V fa[4], fb[J];
+            for (int i = 0; i < NA; ++i) fa[i] = *reinterpret_cast<const V *>(buf + fA + i * 16 * RB);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    fa[i] = *reinterpret_cast<const V *>(frag(buf, slA, 0, wr * 64 + 16 * i + r16, lc));
+            for (int j = 0; j < NJ; ++j) fb[j] = *reinterpret_cast<const V *>(buf + fB + j * 16 * RB);
 #pragma unroll
-                for (int j = 0; j < J; ++j)
-                    fb[j] = *reinterpret_cast<const V *>(frag(buf, slB, 0, wc * CW + 16 * j + r16, lc));
+            for (int q = 0; q < NV; ++q)
 #pragma unroll
-                for (int q = 0; q < NV; ++q)
+                for (int i = 0; i < NA; ++i)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int j = 0; j < J; ++j)
-                            if (on(i, j)) {
-                                if constexpr (PREC == CDS_PREC_FP64)
-                                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(q ? fa[i].y : fa[i].x, q ? fb[j].y : fb[j].x,
-                                                                                     acc[i][j], 0, 0, 0);
-                                else
-                                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
-                            }
-            }
+                    for (int j = 0; j < NJ; ++j)
+                        if (on(i, j)) {
+                            if constexpr (PREC == CDS_PREC_FP64)
+                                acc[i * NJ + j] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                    q ? fa[i].y : fa[i].x, q ? fb[j].y : fb[j].x, acc[i * NJ + j], 0, 0, 0);
+                            else
+                                acc[i * NJ + j] =
+                                    __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], acc[i * NJ + j], 0, 0, 0);
+                        }
         }
     };
 
@@ -392,7 +391,7 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
     // have landed and every wave is done with stage st-1) the freed buffer takes stage st+NB-1.
     // With two stages (split bf16) the next stage's loads are issued before the barrier instead,
     // and a second barrier frees the buffer read (measured faster there).
-    auto main_loop = [&](auto FULLc) {
+    auto main_loop = [&](auto NAc, auto FULLc) {
         constexpr int NL = nload;
         const int64_t ns = a.ns;
         if constexpr (NB == 2) {
@@ -404,7 +403,7 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
                     wait_vm<0>();
                 }
                 __builtin_amdgcn_s_barrier();         // ... and every wave's
-                compute(cur, FULLc);
+                compute(cur, NAc, FULLc);
                 __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS reads are done
                 __builtin_amdgcn_s_barrier();         // cur may be refilled
             };
@@ -427,7 +426,7 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");            // no LDS read moves above the barrier
             if (st + NB - 1 < ns) stage_load(lds + ((st + NB - 1) % NB) * STG, st + NB - 1);
-            compute(lds + (st % NB) * STG, FULLc);
+            compute(lds + (st % NB) * STG, NAc, FULLc);
         }
         __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): this wave's LDS reads are done
         __builtin_amdgcn_s_barrier();                 // ... and every wave's: the ring is free
@@ -435,57 +434,58 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
     };
     typedef std::integral_constant<bool, true> T_;
     typedef std::integral_constant<bool, false> F_;
-    if (nbr == 4 && nbc == J) main_loop(T_());
-    else main_loop(F_());
+    typedef std::integral_constant<int, 4> R4_;
+    typedef std::integral_constant<int, 1> R1_;
+    if (strip) main_loop(R1_(), F_());
+    else if (nbr == 4 && nbc == 2) main_loop(R4_(), T_());
+    else main_loop(R4_(), F_());
 
-    // epilogue.  Lane element (i, j, e): tile row rl = wr*64 + 16 i + rowmap(g, e), tile column
-    // cl = wc*CW + 16 j + r16 (FP64 MFMA rows g + 4e, FP32-accumulating rows 4g + e).
+    // epilogue.  Lane element (b, e): tile row rl = 16 (block row) + rowmap(g, e), tile column
+    // cl = 16 (block column) + r16 (FP64 MFMA rows g + 4e, FP32-accumulating rows 4g + e).
     // A diagonal task's partner (c, r) of element (r, c), r <= c: entry r of row c of its lower
     // triangle, packed in LDS (16 consecutive rows' entries fall into distinct banks: triangular
     // numbers take every residue of a power of two).  The two products of an off-diagonal task
-    // hold both partners in the same lane of two waves: product 0's waves take the blocks
-    // i = 0, 1 and product 1's the blocks i = 2, 3, each handing the other the blocks it does not
-    // take (R is symmetric in the two).
+    // hold both partners in the same lane of two waves: product 0's waves take the blocks b < 4
+    // and product 1's the others, each handing the other the blocks it does not take (R is
+    // symmetric in the two).
     A1 *tri = reinterpret_cast<A1 *>(lds);
-    Acc *xch = reinterpret_cast<Acc *>(lds);    // [product][wave][2][J][lane]
-    constexpr int NI = DG ? 4 : 2;              // block rows this wave takes, from i0
-    const int i0 = DG ? 0 : 2 * prod;
+    Acc *xch = reinterpret_cast<Acc *>(lds);    // [product][wave][4][lane]
+    constexpr int NE = DG ? 8 : 4;              // blocks this wave takes, from be0
+    const int be0 = DG ? 0 : 4 * prod;
+    auto first_row = [&](int b) { return 16 * (strip ? rb0 : rb0 + (b >> 1)) + (PREC == CDS_PREC_FP64 ? g : 4 * g); };
+    auto first_col = [&](int b) { return 16 * (strip ? b : cb0 + (b & 1)) + r16; };
     if constexpr (DG) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int b = 0; b < 8; ++b) {
+            if (!mine(b)) continue;
 #pragma unroll
-            for (int j = 0; j < J; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int rl = wr * 64 + 16 * i + (PREC == CDS_PREC_FP64 ? g + 4 * e : 4 * g + e);
-                    const int cl = wc * CW + 16 * j + r16;
-                    if (cl <= rl) tri[rl * (rl + 1) / 2 + cl] = acc[i][j][e];
-                }
+            for (int e = 0; e < 4; ++e) {
+                const int rl = first_row(b) + (PREC == CDS_PREC_FP64 ? 4 * e : e), cl = first_col(b);
+                if (cl <= rl) tri[rl * (rl + 1) / 2 + cl] = acc[b][e];
+            }
+        }
     } else {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                xch[(((prod * WP + wp) * 2 + i) * J + j) * 64 + lane] = prod ? acc[i][j] : acc[i + 2][j];
-                if (prod) acc[i][j] = acc[i + 2][j];
-            }
+        for (int b = 0; b < 4; ++b) {
+            xch[((prod * WP + wp) * 4 + b) * 64 + lane] = prod ? acc[b] : acc[b + 4];
+            if (prod) acc[b] = acc[b + 4];
+        }
     }
     __syncthreads();
     const int64_t gR0 = (int64_t)k.TR * FT, gC0 = (int64_t)k.TC * FT;
-    // element (i, j, e) (block row i0 + i) of the block whose first row and column (of this lane)
-    // are rb and cb: its value, its partner and whether it counts
-    auto elem = [&](int i, int j, int e, int rb, int cb, const Acc &oth, int &rl, int &cl, double &x, double &xt) {
+    // element e of block be0 + b, whose first row and column (of this lane) are rb and cb: its
+    // value, its partner and whether it counts
+    auto elem = [&](int b, int e, int rb, int cb, const Acc &oth, int &rl, int &cl, double &x, double &xt) {
         rl = rb + (PREC == CDS_PREC_FP64 ? 4 * e : e);
         cl = cb;
-        A1 v = acc[i][j][e];
+        A1 v = acc[b][e];
         if constexpr (MODE == 0) asm volatile("" : "+v"(v));   // as rb and cb below
         x = (double)v;
         const bool in = gR0 + rl < n && gC0 + cl < n && (!diag || rl <= cl);
         xt = diag ? (double)tri[in ? cl * (cl + 1) / 2 + rl : 0] : (double)oth[e];
         return in;
     };
-    auto first_row = [&](int i) { return wr * 64 + 16 * (i0 + i) + (PREC == CDS_PREC_FP64 ? g : 4 * g); };
-    auto other = [&](int i, int j) { return DG ? Acc{} : xch[((((1 - prod) * WP + wp) * 2 + i) * J + j) * 64 + lane]; };
+    auto other = [&](int b) { return DG ? Acc{} : xch[(((1 - prod) * WP + wp) * 4 + b) * 64 + lane]; };
     if constexpr (MODE == 0 || MODE == 2) {
         // MODE 2: the residues as in MODE 1 and, from the stored values, the sums at the one trial
         // energy (the Newton solve's first evaluation, without a sweep over the residues)
@@ -499,35 +499,34 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
                 s0[t] = s1[t] = 0.0;
             }
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
+            for (int b = 0; b < NE; ++b) {
+                if (!mine(be0 + b)) continue;
+                // a block's partners are read when it is its turn (all 32 at once would spill)
+                // and its element numbers formed then (hoisted out of the loop over t0 they spill)
+                int rb = first_row(be0 + b), cb = first_col(be0 + b);
+                asm volatile("" : "+v"(rb), "+v"(cb) : : "memory");
+                const Acc oth = other(b);
 #pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    // a block's partners are read when it is its turn (all 32 at once would spill)
-                    // and its element numbers formed then (hoisted out of the loop over t0 they spill)
-                    int rb = first_row(i), cb = wc * CW + 16 * j + r16;
-                    asm volatile("" : "+v"(rb), "+v"(cb) : : "memory");
-                    const Acc oth = other(i, j);
+                for (int e = 0; e < 4; ++e) {
+                    int rl, cl;
+                    double x, xt;
+                    if (!elem(b, e, rb, cb, oth, rl, cl, x, xt)) continue;
+                    double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
+                    if constexpr (MODE == 2) {
+                        const RT Rs = (RT)R;
+                        Rt[diag ? diag_slot(rl, cl) : rl * FT + cl] = Rs;
+                        R = (double)Rs;
+                    }
+                    const double dd = -seps[0][rl] - seps[1][cl];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        int rl, cl;
-                        double x, xt;
-                        if (!elem(i, j, e, rb, cb, oth, rl, cl, x, xt)) continue;
-                        double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
-                        if constexpr (MODE == 2) {
-                            const RT Rs = (RT)R;
-                            Rt[diag ? diag_slot(rl, cl) : rl * FT + cl] = Rs;
-                            R = (double)Rs;
-                        }
-                        const double dd = -seps[0][rl] - seps[1][cl];
-#pragma unroll
-                        for (int t = 0; t < TT; ++t) {
-                            const double id = 1.0 / (w[t] + dd);
-                            const double ri = R * id;
-                            s0[t] += ri;
-                            s1[t] -= ri * id;
-                        }
+                    for (int t = 0; t < TT; ++t) {
+                        const double id = 1.0 / (w[t] + dd);
+                        const double ri = R * id;
+                        s0[t] += ri;
+                        s1[t] -= ri * id;
                     }
                 }
+            }
             // fixed-order reduction: lanes by butterfly, then waves in order
 #pragma unroll
             for (int t = 0; t < TT; ++t) {
@@ -550,19 +549,18 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
         typedef typename std::conditional<PREC == CDS_PREC_FP64, double, float>::type RT;
         RT *Rt = reinterpret_cast<RT *>(a.R) + (int64_t)k.sl * a.nres + residue_offset(a, k);
 #pragma unroll
-        for (int i = 0; i < NI; ++i)
+        for (int b = 0; b < NE; ++b) {
+            if (!mine(be0 + b)) continue;
+            const Acc oth = other(b);
 #pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const Acc oth = other(i, j);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    int rl, cl;
-                    double x, xt;
-                    if (!elem(i, j, e, first_row(i), wc * CW + 16 * j + r16, oth, rl, cl, x, xt)) continue;
-                    const double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
-                    Rt[diag ? diag_slot(rl, cl) : rl * FT + cl] = (RT)R;
-                }
+            for (int e = 0; e < 4; ++e) {
+                int rl, cl;
+                double x, xt;
+                if (!elem(b, e, first_row(be0 + b), first_col(be0 + b), oth, rl, cl, x, xt)) continue;
+                const double R = (diag && rl == cl) ? x * x : 2.0 * (x * x + xt * xt - x * xt);
+                Rt[diag ? diag_slot(rl, cl) : rl * FT + cl] = (RT)R;
             }
+        }
     }
 }
 
