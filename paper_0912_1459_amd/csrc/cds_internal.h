@@ -194,6 +194,9 @@ struct GemmDesc {
     int big;                 // BF16X3 only: 0 = 256 x 256 tiles when M and N are both >= 512,
                              // 1 = never, 2 = whenever the operands allow (a choice that must not
                              // depend on how a caller batches its rows)
+    int64_t nblk, sCblk;     // nblk > 0: column n of C lies at (n / nblk) sCblk + (n % nblk) sCn
+    int64_t tri;             // tri > 0: tiles whose every column block n / tri is below its every
+                             // row block m / tri are not formed (the lower block triangle)
 };
 // prec of A/B/C: FP64 -> double, FP32/BF16X3 -> float storage
 int cds_gemm(cds_ctx *ctx, int prec, const GemmDesc &d);

@@ -44,7 +44,23 @@ struct Args {
     double alpha, beta;
     int fastA, fastB;              // K-contiguous, 16-byte aligned rows, K % KB == 0
     int big;                       // GemmDesc::big
+    int64_t nblk, sCblk;           // GemmDesc::nblk, sCblk
+    int64_t tri;                   // GemmDesc::tri
 };
+
+// element offset of C column n within a row
+__device__ __forceinline__ int64_t col_off(const Args &a, int64_t n)
+{
+    if (a.nblk == 0) return n * a.sCn;
+    const unsigned q = (unsigned)n / (unsigned)a.nblk, r = (unsigned)n - q * (unsigned)a.nblk;
+    return q * a.sCblk + r * a.sCn;
+}
+
+// a tile wholly below the block diagonal (GemmDesc::tri) is not formed
+__device__ __forceinline__ bool below(const Args &a, int64_t m0, int64_t n_last)
+{
+    return a.tri && (n_last < a.N ? n_last : a.N - 1) / a.tri < m0 / a.tri;
+}
 
 template <int PREC> struct Tr;
 template <> struct Tr<CDS_PREC_FP64> {
@@ -157,6 +173,7 @@ __global__ __launch_bounds__(NT, PREC == CDS_PREC_FP64 ? 1 : 2) void gemm_kernel
     const int64_t n0 = (int64_t)blockIdx.x * BN;
     const int64_t m0 = (int64_t)blockIdx.y * BM;
     const int64_t batch = blockIdx.z;
+    if (below(a, m0, n0 + BN - 1)) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
     const int g = lane >> 4, r16 = lane & 15;
@@ -253,6 +270,7 @@ __global__ __launch_bounds__(NT, PREC == CDS_PREC_FP64 ? 1 : 2) void gemm_kernel
         for (int j = 0; j < 4; ++j) {
             const int64_t n = n0 + wn + 16 * j + r16;
             if (n >= a.N) continue;
+            const int64_t no = col_off(a, n);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 // f32/bf16 MFMA: lane group g holds rows 4g..4g+3; f64: rows g, g+4, g+8, g+12
@@ -260,11 +278,11 @@ __global__ __launch_bounds__(NT, PREC == CDS_PREC_FP64 ? 1 : 2) void gemm_kernel
                 if (m >= a.M) continue;
                 if constexpr (PREC == CDS_PREC_BF16X3) {
                     if (a.Clo) {
-                        split_store(a, batch * a.sCb + m * a.sCm + n * a.sCn, (float)(a.alpha * (double)acc[i][j][e]));
+                        split_store(a, batch * a.sCb + m * a.sCm + no, (float)(a.alpha * (double)acc[i][j][e]));
                         continue;
                     }
                 }
-                O *dst = C + m * a.sCm + n * a.sCn;
+                O *dst = C + m * a.sCm + no;
                 double v = a.alpha * (double)acc[i][j][e];
                 if (a.beta != 0.0) v += a.beta * (double)(*dst);
                 *dst = (O)v;
@@ -335,6 +353,7 @@ __global__ __launch_bounds__(GB_NT, 1) void gemm_bf16x3_big_kernel(Args a, int64
     const int64_t gm = min((int64_t)GB_GM, tiles_m - grp * GB_GM);
     const int64_t tm = grp * GB_GM + rem % gm, tn = rem / gm;
     const int64_t m0 = tm * GB_M, n0 = tn * GB_N;
+    if (below(a, m0, n0 + GB_N - 1)) return;
     const int64_t ns = a.K / GB_K;
 
     floatx4 acc[8][4];
@@ -397,15 +416,16 @@ __global__ __launch_bounds__(GB_NT, 1) void gemm_bf16x3_big_kernel(Args a, int64
         for (int jj = 0; jj < 4; ++jj) {
             const int64_t n = n0 + wn + 16 * jj + r16;
             if (n >= a.N) continue;
+            const int64_t no = col_off(a, n);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int64_t m = m0 + wm + 16 * i + 4 * g + e;
                 if (m >= a.M) continue;
                 if (a.Clo) {
-                    split_store(a, batch * a.sCb + m * a.sCm + n * a.sCn, (float)(a.alpha * (double)acc[i][jj][e]));
+                    split_store(a, batch * a.sCb + m * a.sCm + no, (float)(a.alpha * (double)acc[i][jj][e]));
                     continue;
                 }
-                float *dst = C + m * a.sCm + n * a.sCn;
+                float *dst = C + m * a.sCm + no;
                 double v = a.alpha * (double)acc[i][jj][e];
                 if (a.beta != 0.0) v += a.beta * (double)(*dst);
                 *dst = (float)v;
@@ -418,38 +438,37 @@ bool fast_ok(const void *p, int64_t srow, int64_t sk, int64_t K, int kb, size_t 
     return sk == 1 && K % kb == 0 && cds_aligned(p, 16) && (srow * (int64_t)esz) % 16 == 0;
 }
 
-// ---- FP64 GEMM with direct-to-LDS operand stages -------------------------------------------
-// For K-contiguous FP64 operands (rows 16-byte aligned, K % 16 == 0): 128 x 128 tile per
-// 512-thread workgroup, 8 waves in 2 x 4 with 64 x 32 each (v_mfma_f64_16x16x4f64, 8 blocks),
-// 16-k stages of both operands (128 rows x 128 bytes each) loaded straight from global memory
-// into LDS with global_load_lds_dwordx4, G64_NB stages in the ring (G64_NB - 1 in flight), the
-// 16-byte chunks of a row XOR-swizzled by row & 7 so the fragment reads of 8 consecutive rows hit
-// distinct banks.  Two stages of 32 KB and two workgroups per CU (measured on the large workload:
-// adjoint of the solve 154 ms against 169 / 164 ms for one workgroup with three / four stages;
-// the 128 x 128 register-staged kernel took 222 ms).  Each output takes its K terms in the same
-// order as in gemm_kernel's FP64
-// path (stages of 16 in order, within a stage k pairs (2c, 2c+1) for chunk c in the order
-// c = g, g + 4 of the lane groups), so the two kernels agree bit for bit.
-constexpr int G64_NT = 512, G64_KS = 16, G64_SLICE = 16384, G64_STAGE = 2 * G64_SLICE, G64_NB = 2;
+// ---- FP64 / FP32 GEMM with direct-to-LDS operand stages ------------------------------------
+// For K-contiguous operands (rows 16-byte aligned, K a multiple of the stage): 128 x 128 tile per
+// 512-thread workgroup of 8 waves, stages of 128 bytes of k per row (16 FP64, 32 FP32) of both
+// operands loaded straight from global memory into two 32 KB LDS stages with
+// global_load_lds_dwordx4, the 16-byte chunks of a row XOR-swizzled by row & 7 so the fragment
+// reads of 8 consecutive rows hit distinct banks.  Two workgroups share a CU (measured on the
+// adjoint of the solve, 960 orbitals, 16 targets: 154 ms against 169 / 164 ms for one workgroup
+// with three / four stages).  The tile's 16 x 16 blocks that reach into C are dealt evenly to the
+// waves: 2 x 4 waves of up to 4 x 2 blocks, or a row or a column of blocks per wave where that
+// gives the busiest wave fewer (an edge of one block row costs one block, not four).  Each output
+// takes its K terms in the same order as in gemm_kernel (stages in order, chunk g then g + 4 of
+// the lane groups, the elements of a chunk in turn), so the two kernels agree bit for bit.
+// FP32 went through gemm_kernel's registers before: 240 orbitals, 1662 vectors, the transform's
+// products 833 us, here 750 us (bound there by re-reading the unpacked vectors).
+constexpr int GD_NT = 512, GD_SLICE = 16384, GD_STAGE = 2 * GD_SLICE;
 
-static_assert(G64_NB >= 2 && G64_NB <= 4, "the stage waits cover rings of 2 to 4 stages");
-
-template <int N>
-__device__ __forceinline__ void g64_wait_vm()
+template <int PREC>
+__global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a)
 {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-__global__ __launch_bounds__(G64_NT, 2) void gemm64_dma_kernel(Args a)
-{
-    __shared__ __align__(16) unsigned char lds[G64_NB * G64_STAGE];
+    typedef typename Tr<PREC>::E E;
+    constexpr bool F64 = PREC == CDS_PREC_FP64;
+    typedef typename std::conditional<F64, doublex4, floatx4>::type Acc;
+    typedef typename std::conditional<F64, double2, float4>::type V;
+    constexpr int ES = (int)sizeof(E);
+    __shared__ __align__(16) unsigned char lds[2 * GD_STAGE];
+    const int64_t n0 = (int64_t)blockIdx.x * BN, m0 = (int64_t)blockIdx.y * BM, batch = blockIdx.z;
+    if (below(a, m0, n0 + BN - 1)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
-    const int wr = wave >> 2, wc = wave & 3;
-    const int64_t n0 = (int64_t)blockIdx.x * BN, m0 = (int64_t)blockIdx.y * BM, batch = blockIdx.z;
-    const int64_t ns = a.K / G64_KS;
+    const int64_t ns = a.K / Tr<PREC>::KB;
     // this wave's four loads per stage: slice sl (0 A, 1 B), rows 8 q + lane / 8 for q in
     // [4 (wave & 3), 4 (wave & 3) + 4), position lane % 8 holding the swizzled logical chunk
     const int sl = wave >> 2;
@@ -462,70 +481,93 @@ __global__ __launch_bounds__(G64_NT, 2) void gemm64_dma_kernel(Args a)
     for (int q = 0; q < 4; ++q) {
         const int rr = 8 * (4 * (wave & 3) + q) + lrow;
         const int64_t row = min(r0g + rr, nrows - 1);
-        src[q] = mat + ((batch * sb + row * srow) * 8) + ((pc ^ (rr & 7)) * 16);
+        src[q] = mat + ((batch * sb + row * srow) * ES) + ((pc ^ (rr & 7)) * 16);
     }
     auto stage_load = [&](int buf, int64_t st) __attribute__((always_inline)) {
-        unsigned char *dst = lds + buf * G64_STAGE + sl * G64_SLICE + (4 * (wave & 3)) * 1024;
+        unsigned char *dst = lds + buf * GD_STAGE + sl * GD_SLICE + (4 * (wave & 3)) * 1024;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cds_lds_dma16(src[q] + st * G64_KS * 8, dst + q * 1024);
+        for (int q = 0; q < 4; ++q) cds_lds_dma16(src[q] + st * 128, dst + q * 1024);
     };
-    doublex4 acc[4][2];
+
+    // blocks of 16 x 16 inside C and this wave's share: block rows rb0 .. rb0 + nbr, columns cb0 ..
+    const int nr = __builtin_amdgcn_readfirstlane((int)min((int64_t)8, (a.M - m0 + 15) / 16));
+    const int nc = __builtin_amdgcn_readfirstlane((int)min((int64_t)8, (a.N - n0 + 15) / 16));
+    const int rs = (nr + 1) / 2, cs = (nc + 3) / 4;
+    const int deal = rs * cs <= min(nr, nc) ? 0 : (nc <= nr ? 1 : 2);    // 2 x 4, row strips, column strips
+    const int rb0 = deal == 0 ? (wave >> 2) * rs : (deal == 1 ? wave : 0);
+    const int cb0 = deal == 0 ? (wave & 3) * cs : (deal == 1 ? 0 : wave);
+    const int nbr = deal == 2 ? nr : max(0, min(deal == 1 ? 1 : rs, nr - rb0));
+    const int nbc = deal == 1 ? nc : max(0, min(deal == 2 ? 1 : cs, nc - cb0));
+    const int fo = r16 * 128, sw = r16 & 7;
+    Acc acc[8];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int b = 0; b < 8; ++b)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = doublex4{0.0, 0.0, 0.0, 0.0};
-    auto frag = [&](const unsigned char *buf, int slc, int rr, int lc) __attribute__((always_inline)) {
-        return *reinterpret_cast<const double2 *>(buf + slc * G64_SLICE + rr * 128 + ((lc ^ (rr & 7)) * 16));
-    };
-    // prologue: stages 0 .. NB - 2 in flight
+        for (int e = 0; e < 4; ++e) acc[b][e] = 0;
+
+    // all stages with NA x NJ blocks per wave: block (i, j) is acc[i * NJ + j]
+    auto run = [&](auto NAc, auto FULLc) __attribute__((always_inline)) {
+        constexpr int NA = decltype(NAc)::value, NJ = 8 / NA, NV = 16 / ES;
+        constexpr bool full = decltype(FULLc)::value;
+        stage_load(0, 0);
+        for (int64_t st = 0; st < ns; ++st) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's loads of stage st
+            __builtin_amdgcn_s_barrier();                      // every wave's; and stage st - 1 is read
+            asm volatile("" ::: "memory");
+            if (st + 1 < ns) stage_load((int)((st + 1) & 1), st + 1);
+            const unsigned char *cur = lds + (st & 1) * GD_STAGE;
 #pragma unroll
-    for (int i = 0; i < G64_NB - 1; ++i)
-        if (i < ns) stage_load(i, i);
-    for (int64_t st = 0; st < ns; ++st) {
-        const int buf = (int)(st % G64_NB);
-        // this wave's loads of stage st have landed (4 loads per later stage may still be in flight)
-        const int64_t later = min((int64_t)(G64_NB - 2), ns - 1 - st);
-        if (later >= 2) g64_wait_vm<8>();
-        else if (later == 1) g64_wait_vm<4>();
-        else g64_wait_vm<0>();
-        __builtin_amdgcn_s_barrier();                      // every wave's; and stage st - 1 is read
-        if (st + G64_NB - 1 < ns) stage_load((int)((st + G64_NB - 1) % G64_NB), st + G64_NB - 1);
-        const unsigned char *cur = lds + buf * G64_STAGE;
+            for (int h = 0; h < 2; ++h) {
+                const int co = fo + (((g + 4 * h) ^ sw) * 16);
+                V fa[NA], fb[NJ];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int lc = g + 4 * h;
-            double2 fa[4], fb[2];
+                for (int i = 0; i < NA; ++i) fa[i] = *reinterpret_cast<const V *>(cur + (rb0 + i) * 2048 + co);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) fa[i] = frag(cur, 0, wr * 64 + 16 * i + r16, lc);
+                for (int j = 0; j < NJ; ++j)
+                    fb[j] = *reinterpret_cast<const V *>(cur + GD_SLICE + (cb0 + j) * 2048 + co);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = frag(cur, 1, wc * 32 + 16 * j + r16, lc);
+                for (int q = 0; q < NV; ++q)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < NA; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i].x, fb[j].x, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i].y, fb[j].y, acc[i][j], 0, 0, 0);
-                }
-        }
-        __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): this wave's reads are done
-    }
-    double *C = reinterpret_cast<double *>(a.C) + batch * a.sCb;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int64_t n = n0 + wc * 32 + 16 * j + r16;
-            if (n >= a.N) continue;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t m = m0 + wr * 64 + 16 * i + g + 4 * e;
-                if (m >= a.M) continue;
-                double *dst = C + m * a.sCm + n * a.sCn;
-                double v = a.alpha * acc[i][j][e];
-                if (a.beta != 0.0) v += a.beta * (*dst);
-                *dst = v;
+                        for (int j = 0; j < NJ; ++j)
+                            if (full || (i < nbr && j < nbc)) {
+                                Acc &c = acc[i * NJ + j];
+                                if constexpr (F64)
+                                    c = __builtin_amdgcn_mfma_f64_16x16x4f64(q ? fa[i].y : fa[i].x, q ? fb[j].y : fb[j].x, c,
+                                                                             0, 0, 0);
+                                else
+                                    c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[i][q], fb[j][q], c, 0, 0, 0);
+                            }
             }
+            __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): this wave's reads are done
         }
+    };
+    typedef std::integral_constant<bool, true> T_;
+    typedef std::integral_constant<bool, false> F_;
+    if (deal == 1) run(std::integral_constant<int, 1>(), F_());
+    else if (deal == 2) run(std::integral_constant<int, 8>(), F_());
+    else if (nbr == 4 && nbc == 2) run(std::integral_constant<int, 4>(), T_());
+    else run(std::integral_constant<int, 4>(), F_());
+
+    E *C = reinterpret_cast<E *>(a.C) + batch * a.sCb;
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const int i = deal == 0 ? b >> 1 : (deal == 1 ? 0 : b), j = deal == 0 ? b & 1 : (deal == 1 ? b : 0);
+        if (i >= nbr || j >= nbc) continue;
+        const int64_t n = n0 + 16 * (cb0 + j) + r16;
+        if (n >= a.N) continue;
+        const int64_t no = col_off(a, n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t m = m0 + 16 * (rb0 + i) + (F64 ? g + 4 * e : 4 * g + e);
+            if (m >= a.M) continue;
+            E *dst = C + m * a.sCm + no;
+            double v = a.alpha * (double)acc[b][e];
+            if (a.beta != 0.0) v += a.beta * (double)(*dst);
+            *dst = (E)v;
+        }
+    }
 }
 
 template <int PREC>
@@ -555,12 +597,14 @@ int launch(cds_ctx *ctx, Args &a)
             return CDS_OK;
         }
     }
-    if (PREC == CDS_PREC_FP64 && a.fastA && a.fastB && a.K % G64_KS == 0 && cds_aligned(a.A, 16) &&
-        cds_aligned(a.B, 16) && (a.sAb * 8) % 16 == 0 && (a.sBb * 8) % 16 == 0) {
-        hipLaunchKernelGGL(gemm64_dma_kernel, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.batch), dim3(G64_NT), 0,
-                           ctx->stream, a);
-        CDS_LAUNCHED(ctx);
-        return CDS_OK;
+    if constexpr (PREC != CDS_PREC_BF16X3) {
+        // fast operands have K a multiple of the stage and 16-byte aligned rows; so must the batches
+        if (a.fastA && a.fastB && (a.sAb * (int64_t)sizeof(E)) % 16 == 0 && (a.sBb * (int64_t)sizeof(E)) % 16 == 0) {
+            hipLaunchKernelGGL(gemm_dma_kernel<PREC>, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.batch), dim3(GD_NT), 0,
+                               ctx->stream, a);
+            CDS_LAUNCHED(ctx);
+            return CDS_OK;
+        }
     }
     size_t lds = (size_t)2 * Tr<PREC>::PLANES * BM * PITCH;
     hipLaunchKernelGGL(gemm_kernel<PREC>, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.batch), dim3(NT),
@@ -642,6 +686,10 @@ int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, cons
     a.alpha = d.alpha;
     a.beta = d.beta;
     a.big = d.big;
+    a.nblk = d.nblk;
+    a.sCblk = d.sCblk;
+    a.tri = d.tri;
+    if (a.nblk && a.N > 0x7fffffff) return cds_fail(ctx, CDS_EINVAL, "GEMM columns in blocks: N too large");
     if (prec == CDS_PREC_FP64) return launch<CDS_PREC_FP64>(ctx, a);
     if (prec == CDS_PREC_FP32) return launch<CDS_PREC_FP32>(ctx, a);
     if (prec == CDS_PREC_BF16X3) return launch<CDS_PREC_BF16X3>(ctx, a);

@@ -7,11 +7,13 @@
 //   2. GEMM     T[x][K][mu] = sum_nu CX[x][nu] Lu[K][mu][nu]      (batched over K)
 //      with x = the occupied orbitals, then the selected orbitals that are not occupied
 //      (an occupied target's row of T is its occupied row)
-//   3. GEMM     W[a][(i,K)] = sum_mu Ct[nocc+a][mu] T[i][K][mu]     (virt x occ, one product)
-//      GEMM     W[r][(s,K)] = sum_mu Ct[r][mu] T[x_s][K][mu]        (all x sel, one product
+//   3. GEMM     Bvo[a][i][K] = sum_mu Ct[nocc+a][mu] T[i][K][mu]    (virt x occ, one product)
+//      GEMM     Bsel[s][r][K] = sum_mu Ct[r][mu] T[x_s][K][mu]      (all x sel, one product
 //                                                                   per run of consecutive x_s)
-//   4. copy     W -> B[row][K] (K contiguous: each (row, batch) segment is contiguous in W),
-//      converting to the output format (double, float, or bf16 hi/lo planes).
+//      stored by the products themselves in the block layout (K contiguous; double, float or
+//      bf16 hi/lo planes).  240 orbitals, 1662 vectors, FP32: a copy through W[row][K] took 81 us
+//   4. copy     only where the products run in FP64 and the output is narrower, or one product
+//      over all MOs forms both blocks: W -> B[row][K], converting to the output format.
 // Working precision of steps 1-3: FP64 for CDS_PREC_FP64, FP32 for FP32, and
 // split bf16 (3-term products, FP32 accumulation) for BF16X3.
 #include "cds_internal.h"
@@ -144,11 +146,10 @@ __global__ void zero_cols_kernel(unsigned char *base, int64_t nrows, int64_t pit
 }
 
 
-// W (working type) -> out[row*ldk + k0 + kb] in the output format, one thread per (row, kb).
+// W (FP64) -> out[row*ldk + k0 + kb] in the output format, one thread per (row, kb).
 // Rows [0, nvo) = (a, i) go to Bvo from W[(a*nocc + i)*nkb + kb]; rows nvo + s*nmo + r go to
 // Bsel from W[nvo*nkb + r*nsel*nkb + s*nkb + kb].  Reads and writes run along kb.
-template <typename W>
-__global__ __launch_bounds__(256) void copy_out_kernel(const W *__restrict__ Wb, int64_t nvo, int nmo, int nsel,
+__global__ __launch_bounds__(256) void copy_out_kernel(const double *__restrict__ Wb, int64_t nvo, int nmo, int nsel,
                                                        int nkb, int64_t k0, void *Bvo, void *Bsel, int64_t ldk,
                                                        int prec, int64_t plane_vo, int64_t plane_sel)
 {
@@ -158,11 +159,11 @@ __global__ __launch_bounds__(256) void copy_out_kernel(const W *__restrict__ Wb,
     const int64_t row = t / nkb;
     const int kb = (int)(t - row * nkb);
     if (row < nvo) {
-        put(Bvo, prec, row * ldk + k0 + kb, plane_vo, (double)Wb[t]);
+        put(Bvo, prec, row * ldk + k0 + kb, plane_vo, Wb[t]);
     } else {
         const int64_t rs = row - nvo;
         const int sidx = (int)(rs / nmo), r = (int)(rs - (int64_t)sidx * nmo);
-        const double v = (double)Wb[nvo * nkb + ((int64_t)r * nsel + sidx) * nkb + kb];
+        const double v = Wb[nvo * nkb + ((int64_t)r * nsel + sidx) * nkb + kb];
         put(Bsel, prec, rs * ldk + k0 + kb, plane_sel, v);
     }
 }
@@ -214,6 +215,7 @@ struct TrPlan {
     unsigned char *Ct, *CX;
     int32_t *dext, *dxs;
     bool comb;                                // one product over all MOs and all rows of T
+    bool direct;                              // the products store into the blocks themselves
     void *wlu, *wt, *wb;
     float *Tf;
     __bf16 *Ts;
@@ -246,8 +248,8 @@ int tr_alloc_batch(cds_ctx *ctx, TrPlan &p, CdsSlot slu, CdsSlot st, CdsSlot sb)
     CDS_CALL(cds_ws(ctx, slu, (size_t)nLu * es, &p.wlu));
     const int64_t nT = (int64_t)p.kbatch * p.nx * p.np_;
     CDS_CALL(cds_ws(ctx, st, (size_t)nT * es * (p.wp == CDS_PREC_BF16X3 ? 2 : 1), &p.wt));
-    const int64_t wrows = p.comb ? (int64_t)p.nmo * p.nx : p.nrows;
-    CDS_CALL(cds_ws(ctx, sb, (size_t)p.kbatch * wrows * (p.wp == CDS_PREC_FP64 ? 8 : 4), &p.wb));
+    const int64_t wrows = p.comb ? (int64_t)p.nmo * p.nx : p.direct ? 0 : p.nrows;
+    CDS_CALL(cds_ws(ctx, sb, (size_t)p.kbatch * wrows * 8, &p.wb));
     // T: working float output, and (bf16) its two planes after it
     p.Tf = (float *)p.wt;
     p.Ts = (__bf16 *)((unsigned char *)p.wt + (size_t)nT * 4);
@@ -302,6 +304,7 @@ int tr_alloc(cds_ctx *ctx, TrPlan &p, int32_t prec, int32_t nbf, const double *L
     // FP64: one product Ct^T T over every MO and every row of T (one launch that fills the chip)
     // when it computes at most 15 % more than the two blocks need
     p.comb = p.wp == CDS_PREC_FP64 && (int64_t)nmo * p.nx * 100 <= p.nrows * 115;
+    p.direct = !p.comb && p.wp == prec;
     const size_t es = wsize(p.wp);
     // batch: enough 128 x 128 tiles of the virtual-occupied product per launch to fill the
     // chip (that product has one tile group of nvirt x nocc per vector)
@@ -373,7 +376,7 @@ int tr_pad(cds_ctx *ctx, const TrPlan &p, int64_t nvec, int64_t kend)
     return CDS_OK;
 }
 
-// vectors [k0, k0 + nkb), nkb <= kbatch: unpack, three GEMMs, transposed output
+// vectors [k0, k0 + nkb), nkb <= kbatch: unpack, the products, and the copy where one is needed
 int tr_batch(cds_ctx *ctx, const TrPlan &p, int64_t k0, int nkb)
 {
     const int np_ = p.np_, nx = p.nx, nocc = p.nocc, nmo = p.nmo, nsel = p.nsel, nbf = p.nbf;
@@ -405,7 +408,6 @@ int tr_batch(cds_ctx *ctx, const TrPlan &p, int64_t k0, int nkb)
     const unsigned char *Tin = (const unsigned char *)((p.wp == CDS_PREC_BF16X3) ? (const void *)p.Ts : Tout);
     const int64_t planeT = (int64_t)nkb * nx * np_;
     const size_t tes = (p.wp == CDS_PREC_FP64) ? 8 : (p.wp == CDS_PREC_FP32 ? 4 : 2);
-    const size_t wes = (p.wp == CDS_PREC_FP64) ? 8 : 4;
     if (p.comb) {
         // W[r][x*nkb + kb] = sum_mu Ct[r][mu] T[x][kb][mu] for every MO r and row x of T: both
         // blocks from one launch (each entry the same sum as in the two products below)
@@ -426,12 +428,17 @@ int tr_batch(cds_ctx *ctx, const TrPlan &p, int64_t k0, int nkb)
     }
     // the 256 x 256 split-bf16 tiles are chosen from the per-vector shapes only, so that a
     // vector's blocks do not depend on the batching
-    // W[a][i*nkb + kb] = sum_mu Ct[nocc+a][mu] T[i][kb][mu]
+    // B_vo[a][i][k0 + kb] (or W[a][i*nkb + kb]) = sum_mu Ct[nocc+a][mu] T[i][kb][mu]
     GemmDesc g2 = {};
     g2.M = p.nvirt; g2.N = (int64_t)nocc * nkb; g2.K = np_; g2.batch = 1;
     g2.A = p.Ct + (size_t)nocc * np_ * tes; g2.sAm = np_; g2.sAk = 1;
     g2.B = Tin; g2.sBn = np_; g2.sBk = 1;
     g2.C = p.wb; g2.sCm = (int64_t)nocc * nkb; g2.sCn = 1;
+    if (p.direct) {
+        g2.C = (unsigned char *)p.Bvo + (size_t)k0 * tes;
+        if (p.wp == CDS_PREC_BF16X3) g2.Clo = (__bf16 *)g2.C + p.nvo * p.ldk;
+        g2.sCm = nocc * p.ldk; g2.nblk = nkb; g2.sCblk = p.ldk;
+    }
     g2.alpha = 1.0; g2.beta = 0.0;
     g2.big = p.nvirt >= 512 ? 2 : 1;
     if (p.wp == CDS_PREC_BF16X3)
@@ -439,15 +446,21 @@ int tr_batch(cds_ctx *ctx, const TrPlan &p, int64_t k0, int nkb)
                              p.Ts + planeT));
     else
         CDS_CALL(cds_gemm_ex(ctx, gprec, g2, nullptr, nullptr));
-    // W[nvo*nkb + r*nsel*nkb + s*nkb + kb] = sum_mu Ct[r][mu] T[x_s][kb][mu], one product per run
+    // B_sel[s][r][k0 + kb] (or W[nvo*nkb + r*nsel*nkb + s*nkb + kb]) = sum_mu Ct[r][mu] T[x_s][kb][mu],
+    // one product per run
     for (const auto &run : p.runs) {
         const int s0 = run[0], cnt = run[1], x0 = run[2];
         GemmDesc g3 = {};
         g3.M = nmo; g3.N = (int64_t)cnt * nkb; g3.K = np_; g3.batch = 1;
         g3.A = p.Ct; g3.sAm = np_; g3.sAk = 1;
         g3.B = Tin + (size_t)x0 * nkb * np_ * tes; g3.sBn = np_; g3.sBk = 1;
-        g3.C = (unsigned char *)p.wb + ((size_t)p.nvo * nkb + (size_t)s0 * nkb) * wes;
+        g3.C = (double *)p.wb + (size_t)p.nvo * nkb + (size_t)s0 * nkb;
         g3.sCm = (int64_t)nsel * nkb; g3.sCn = 1;
+        if (p.direct) {
+            g3.C = (unsigned char *)p.Bsel + ((size_t)s0 * nmo * p.ldk + k0) * tes;
+            if (p.wp == CDS_PREC_BF16X3) g3.Clo = (__bf16 *)g3.C + p.nselr * p.ldk;
+            g3.sCm = p.ldk; g3.nblk = nkb; g3.sCblk = nmo * p.ldk;
+        }
         g3.alpha = 1.0; g3.beta = 0.0;
         g3.big = nmo >= 512 ? 2 : 1;
         if (p.wp == CDS_PREC_BF16X3)
@@ -456,14 +469,11 @@ int tr_batch(cds_ctx *ctx, const TrPlan &p, int64_t k0, int nkb)
         else
             CDS_CALL(cds_gemm_ex(ctx, gprec, g3, nullptr, nullptr));
     }
+    if (p.direct) return CDS_OK;
     const int64_t nel = p.nrows * nkb;
-    const dim3 cg((unsigned)cds_ceil_div(nel, 256));
-    if (p.wp == CDS_PREC_FP64)
-        hipLaunchKernelGGL(copy_out_kernel<double>, cg, dim3(256), 0, ctx->stream, (const double *)p.wb, p.nvo, nmo,
-                           nsel, nkb, k0, p.Bvo, p.Bsel, p.ldk, p.prec, p.nvo * p.ldk, p.nselr * p.ldk);
-    else
-        hipLaunchKernelGGL(copy_out_kernel<float>, cg, dim3(256), 0, ctx->stream, (const float *)p.wb, p.nvo, nmo,
-                           nsel, nkb, k0, p.Bvo, p.Bsel, p.ldk, p.prec, p.nvo * p.ldk, p.nselr * p.ldk);
+    hipLaunchKernelGGL(copy_out_kernel, dim3((unsigned)cds_ceil_div(nel, 256)), dim3(256), 0, ctx->stream,
+                       (const double *)p.wb, p.nvo, nmo, nsel, nkb, k0, p.Bvo, p.Bsel, p.ldk, p.prec, p.nvo * p.ldk,
+                       p.nselr * p.ldk);
     CDS_LAUNCHED(ctx);
     return CDS_OK;
 }
