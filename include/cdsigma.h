@@ -105,7 +105,7 @@ typedef struct cds_stats {
                                  return at once)                                */
     int64_t n_cd_pass_launch; /* look-ahead pass launches                       */
     double t_mp2_ms;         /* MP2 energies (contraction + reduction)        */
-    double flops_mp2;        /* 2 nvec x rows x columns of the MP2 contractions */
+    double flops_mp2;        /* 2 nvec nocc^2 per pair of virtuals b >= a */
     double t_dyson_ms;       /* self-energy matrices and Dyson pole searches  */
     double t_cd_spec_ms;     /* speculative blocks (with kernel timing on)    */
     int64_t n_cd_spec;       /* Cholesky steps committed by speculative blocks */

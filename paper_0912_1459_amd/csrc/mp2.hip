@@ -9,6 +9,7 @@
 //   R_ij = 2 (x^2 + x'^2 - x x')  (i < j),  R_ii = x^2,   x = X_ab[i][j], x' = X_ab[j][i].
 // Virtuals are processed in chunks [a0, a1): one MFMA GEMM
 //   G[(a - a0) nocc + i][(b - a0) nocc + j] = sum_K Bvo[a][i][K] Bvo[b][j][K],  b >= a0,
+// without its tiles wholly below b = a (they were a ninth of the product with 8 chunks),
 // then one block per (a, b >= a) reduces its X_ab (32 x 32 tile pairs through LDS, as in
 // the self-energy epilogue) to S_ab; a last one-block kernel sums the S_ab in fixed order.
 #include "cds_internal.h"
@@ -168,10 +169,12 @@ extern "C" int cds_mp2(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, in
         d.sCn = 1;
         d.alpha = 1.0;
         d.beta = 0.0;
+        d.tri = nocc;                           // only blocks b >= a are read
         const void *lo = nullptr;
         if (prec == CDS_PREC_BF16X3) lo = (const __bf16 *)Bvo + nvo * ldk + (int64_t)a0 * nocc * ldk;
         CDS_CALL(cds_gemm_ex(ctx, prec, d, lo, lo));
-        ctx->stats.flops_mp2 += 2.0 * (double)nvec * (double)d.M * (double)d.N;
+        // the pairs b >= a of the chunk
+        ctx->stats.flops_mp2 += 2.0 * (double)nvec * nocc * nocc * (0.5 * n_a * (2.0 * (nvirt - a0) - n_a + 1));
         const dim3 grid((unsigned)n_a, (unsigned)(nvirt - a0));
         if (prec == CDS_PREC_FP64)
             hipLaunchKernelGGL(mp2_block_kernel<double>, grid, dim3(MP_NT), 0, ctx->stream, (const double *)Gw,
