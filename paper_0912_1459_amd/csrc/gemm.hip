@@ -56,6 +56,56 @@ __device__ __forceinline__ int64_t col_off(const Args &a, int64_t n)
     return q * a.sCblk + r * a.sCn;
 }
 
+// Order of the tiles of the direct-to-LDS kernels: TG_ROWS tile rows at a time, columns across them
+// (from the block diagonal on, GemmDesc::tri), batch by batch; 8 W consecutive workgroups (dealt
+// to the 8 XCDs in turn) take that many consecutive tiles, W per XCD, the tiles an XCD runs at a
+// time: they share operand rows in its L2.
+constexpr int TG_ROWS = 4;
+
+// first tile column of the group of tile rows from tile row r0 on
+__host__ __device__ __forceinline__ unsigned first_col(int64_t tri, unsigned r0, int th, int tw)
+{
+    return tri ? (unsigned)((int64_t)r0 * th / tri * tri / tw) : 0;
+}
+
+// tiles of one batch entry
+int64_t count_tiles(int64_t tri, unsigned gx, unsigned gy, int th, int tw)
+{
+    int64_t n = 0;
+    for (unsigned r0 = 0; r0 < gy; r0 += TG_ROWS)
+        n += (int64_t)std::min<unsigned>(TG_ROWS, gy - r0) * (gx - first_col(tri, r0, th, tw));
+    return n;
+}
+
+// tile u of a batch entry -> tile row and column
+__device__ __forceinline__ void tile_at(unsigned u, int64_t tri, unsigned gx, unsigned gy, int th, int tw, unsigned &tm,
+                                        unsigned &tn)
+{
+    unsigned r0 = 0, c0 = 0, rows = min((unsigned)TG_ROWS, gy);
+    if (tri) {
+        for (;;) {
+            const unsigned cnt = rows * (gx - c0);
+            if (u < cnt) break;
+            u -= cnt;
+            r0 += TG_ROWS;
+            rows = min((unsigned)TG_ROWS, gy - r0);
+            c0 = first_col(tri, r0, th, tw);
+        }
+    } else {
+        r0 = u / (TG_ROWS * gx) * TG_ROWS;
+        u -= r0 * gx;
+        rows = min((unsigned)TG_ROWS, gy - r0);
+    }
+    tm = r0 + u % rows;
+    tn = c0 + u / rows;
+}
+
+template <int W>
+__device__ __forceinline__ unsigned xcd_order(unsigned t, unsigned n)
+{
+    return t < n / (8 * W) * (8 * W) ? t / (8 * W) * (8 * W) + t % 8 * W + t / 8 % W : t;
+}
+
 // a tile wholly below the block diagonal (GemmDesc::tri) is not formed
 __device__ __forceinline__ bool below(const Args &a, int64_t m0, int64_t n_last)
 {
@@ -299,10 +349,8 @@ __global__ __launch_bounds__(NT, PREC == CDS_PREC_FP64 ? 1 : 2) void gemm_kernel
 // 16-byte k-chunks of a row are stored XOR-swizzled by (row >> 1) & 3 (the swizzle is
 // applied to the global address), so the fragment reads of 8 consecutive rows hit distinct
 // banks.  The stage waits are explicit (vmcnt, then s_barrier without a memory fence, which
-// would also wait for the next stage's loads).  Tiles of one XCD are contiguous in a grouped
-// order (4 tile rows x all tile columns), so tiles that share operand rows run on the same
-// L2.
-constexpr int GB_M = 256, GB_N = 256, GB_K = 32, GB_NT = 512, GB_GM = 4;
+// would also wait for the next stage's loads).
+constexpr int GB_M = 256, GB_N = 256, GB_K = 32, GB_NT = 512;
 constexpr int GB_PLANE = GB_M * GB_K * 2;       // bytes of one operand plane per stage (16 KB)
 constexpr int GB_STAGE = 4 * GB_PLANE;          // A hi, A lo, B hi, B lo (64 KB)
 
@@ -337,7 +385,7 @@ __device__ __forceinline__ void gb_stage(const Args &a, unsigned char *buf, int6
     }
 }
 
-__global__ __launch_bounds__(GB_NT, 1) void gemm_bf16x3_big_kernel(Args a, int64_t tiles_m, int64_t tiles_n)
+__global__ __launch_bounds__(GB_NT, 1) void gemm_bf16x3_big_kernel(Args a, unsigned gx, unsigned gy)
 {
     __shared__ __align__(16) unsigned char lds0[GB_STAGE];
     __shared__ __align__(16) unsigned char lds1[GB_STAGE];
@@ -345,14 +393,9 @@ __global__ __launch_bounds__(GB_NT, 1) void gemm_bf16x3_big_kernel(Args a, int64
     const int g = lane >> 4, r16 = lane & 15;
     const int wm = (wave >> 2) * 128, wn = (wave & 3) * 64;
     const int64_t batch = blockIdx.y;
-    // tile of this workgroup: contiguous ranges per XCD (workgroups go round-robin over the 8)
-    const int64_t T = tiles_m * tiles_n, bid = blockIdx.x;
-    const int64_t q8 = T / 8, r8 = T % 8, xcd = bid % 8, j = bid / 8;
-    const int64_t t = xcd * q8 + min(xcd, r8) + j;
-    const int64_t gsz = GB_GM * tiles_n, grp = t / gsz, rem = t % gsz;
-    const int64_t gm = min((int64_t)GB_GM, tiles_m - grp * GB_GM);
-    const int64_t tm = grp * GB_GM + rem % gm, tn = rem / gm;
-    const int64_t m0 = tm * GB_M, n0 = tn * GB_N;
+    unsigned tm, tn;
+    tile_at(xcd_order<32>(blockIdx.x, gridDim.x), a.tri, gx, gy, GB_M, GB_N, tm, tn);
+    const int64_t m0 = (int64_t)tm * GB_M, n0 = (int64_t)tn * GB_N;
     if (below(a, m0, n0 + GB_N - 1)) return;
     const int64_t ns = a.K / GB_K;
 
@@ -451,11 +494,10 @@ bool fast_ok(const void *p, int64_t srow, int64_t sk, int64_t K, int kb, size_t 
 // takes its K terms in the same order as in gemm_kernel (stages in order, chunk g then g + 4 of
 // the lane groups, the elements of a chunk in turn), so the two kernels agree bit for bit.
 // FP32 went through gemm_kernel's registers before: 240 orbitals, 1662 vectors, the transform's
-// products 833 us, here 750 us (bound there by re-reading the unpacked vectors).
+// products 833 us, here 630 us (short K: the first loads of a tile are not hidden).
 constexpr int GD_NT = 512, GD_SLICE = 16384, GD_STAGE = 2 * GD_SLICE;
-
 template <int PREC>
-__global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a)
+__global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per, unsigned gx, unsigned gy, int th, int tw)
 {
     typedef typename Tr<PREC>::E E;
     constexpr bool F64 = PREC == CDS_PREC_FP64;
@@ -463,8 +505,11 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a)
     typedef typename std::conditional<F64, double2, float4>::type V;
     constexpr int ES = (int)sizeof(E);
     __shared__ __align__(16) unsigned char lds[2 * GD_STAGE];
-    const int64_t n0 = (int64_t)blockIdx.x * BN, m0 = (int64_t)blockIdx.y * BM, batch = blockIdx.z;
-    if (below(a, m0, n0 + BN - 1)) return;
+    const unsigned t = xcd_order<64>(blockIdx.x, gridDim.x), bt = t / per;   // two workgroups on each of 32 CUs
+    unsigned tm, tn;
+    tile_at(t - bt * per, a.tri, gx, gy, th, tw, tm, tn);
+    const int64_t n0 = (int64_t)tn * tw, m0 = (int64_t)tm * th, batch = bt;
+    if (below(a, m0, n0 + tw - 1)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
@@ -476,6 +521,7 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a)
     const unsigned char *mat = sl ? a.B : a.A;
     const int64_t srow = sl ? a.sBn : a.sAm, sb = sl ? a.sBb : a.sAb;
     const int64_t nrows = sl ? a.N : a.M, r0g = sl ? n0 : m0;
+    const int nld = max(0, min(4, ((sl ? tw : th) - 32 * (wave & 3)) / 8));   // loads that reach into the tile
     const unsigned char *src[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -486,12 +532,13 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a)
     auto stage_load = [&](int buf, int64_t st) __attribute__((always_inline)) {
         unsigned char *dst = lds + buf * GD_STAGE + sl * GD_SLICE + (4 * (wave & 3)) * 1024;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cds_lds_dma16(src[q] + st * 128, dst + q * 1024);
+        for (int q = 0; q < 4; ++q)
+            if (q < nld) cds_lds_dma16(src[q] + st * 128, dst + q * 1024);
     };
 
     // blocks of 16 x 16 inside C and this wave's share: block rows rb0 .. rb0 + nbr, columns cb0 ..
-    const int nr = __builtin_amdgcn_readfirstlane((int)min((int64_t)8, (a.M - m0 + 15) / 16));
-    const int nc = __builtin_amdgcn_readfirstlane((int)min((int64_t)8, (a.N - n0 + 15) / 16));
+    const int nr = __builtin_amdgcn_readfirstlane((int)min((int64_t)th / 16, (a.M - m0 + 15) / 16));
+    const int nc = __builtin_amdgcn_readfirstlane((int)min((int64_t)tw / 16, (a.N - n0 + 15) / 16));
     const int rs = (nr + 1) / 2, cs = (nc + 3) / 4;
     const int deal = rs * cs <= min(nr, nc) ? 0 : (nc <= nr ? 1 : 2);    // 2 x 4, row strips, column strips
     const int rb0 = deal == 0 ? (wave >> 2) * rs : (deal == 1 ? wave : 0);
@@ -591,17 +638,27 @@ int launch(cds_ctx *ctx, Args &a)
         cds_aligned(a.A, 16) && cds_aligned(a.Alo, 16) && cds_aligned(a.B, 16) && cds_aligned(a.Blo, 16)) {
         const int64_t tm = cds_ceil_div(a.M, GB_M), tn = cds_ceil_div(a.N, GB_N);
         if (tm * tn <= 0x7fffffff) {
-            hipLaunchKernelGGL(gemm_bf16x3_big_kernel, dim3((unsigned)(tm * tn), (unsigned)a.batch), dim3(GB_NT), 0,
-                               ctx->stream, a, tm, tn);
+            const int64_t n = count_tiles(a.tri, (unsigned)tn, (unsigned)tm, GB_M, GB_N);
+            hipLaunchKernelGGL(gemm_bf16x3_big_kernel, dim3((unsigned)n, (unsigned)a.batch), dim3(GB_NT), 0, ctx->stream,
+                               a, (unsigned)tn, (unsigned)tm);
             CDS_LAUNCHED(ctx);
             return CDS_OK;
         }
     }
     if constexpr (PREC != CDS_PREC_BF16X3) {
         // fast operands have K a multiple of the stage and 16-byte aligned rows; so must the batches
-        if (a.fastA && a.fastB && (a.sAb * (int64_t)sizeof(E)) % 16 == 0 && (a.sBb * (int64_t)sizeof(E)) % 16 == 0) {
-            hipLaunchKernelGGL(gemm_dma_kernel<PREC>, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.batch), dim3(GD_NT), 0,
-                               ctx->stream, a);
+        if (a.fastA && a.fastB && (a.sAb * (int64_t)sizeof(E)) % 16 == 0 && (a.sBb * (int64_t)sizeof(E)) % 16 == 0 &&
+            gx * gy <= 0x7fffffff / a.batch && (!a.tri || a.batch == 1)) {
+            // a last tile of one or two blocks of 16 costs a whole tile's loads: there the blocks are
+            // shared out evenly over the tiles (130 rows are two tiles of 80 and 50, not of 128 and 2)
+            auto edge = [](int64_t n, int64_t tiles) {
+                const int64_t nb = cds_ceil_div(n, 16);
+                return 16 * (int)(nb % 8 == 1 || nb % 8 == 2 ? cds_ceil_div(nb, tiles) : 8);
+            };
+            const int th = edge(a.M, gy), tw = edge(a.N, gx);
+            const unsigned per = (unsigned)count_tiles(a.tri, (unsigned)gx, (unsigned)gy, th, tw);
+            hipLaunchKernelGGL(gemm_dma_kernel<PREC>, dim3(per * (unsigned)a.batch), dim3(GD_NT), 0, ctx->stream, a, per,
+                               (unsigned)gx, (unsigned)gy, th, tw);
             CDS_LAUNCHED(ctx);
             return CDS_OK;
         }
