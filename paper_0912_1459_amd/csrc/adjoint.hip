@@ -10,7 +10,14 @@
 //   Bsel_bar[s] = W[s] Bvo            (W = omega_bar P dSigma/dG)
 //   Bvo_bar     = sum_s W[s]^T Bsel[s]
 // and the energies enter through the denominators and e_q itself.
-// Transform adjoint: B^K = C^T L^K C gives C_bar = sum_K L^K C (Bbar^K + Bbar^K^T).
+// Transform adjoint: B^K = C^T L^K C gives C_bar = sum_K L^K C (Bbar^K + Bbar^K^T).  Bbar has only the
+// rows of the targets and the virtual-occupied block, so with the rows x = occupied orbitals and
+// targets, Z^K[x][r] their cotangents (occupied i: Bvo_bar[a][i] at r = a; target s: Bsel_bar[s][r]),
+// T^K_x = L^K C_x and Y^K_x = sum_r C_r Z^K[x][r]:
+//   C_bar_r += sum_K sum_x T^K_x Z^K[x][r]   and   C_bar_x += sum_K L^K Y^K_x,
+// 4 n nx (n + nvirt) operations per vector against 4 n^3 for the full symmetric Bbar (n = 480, 120
+// occupied: 0.45 of it; 960: 0.26), every product K-contiguous.  Both sums run over the vectors
+// inside the products, a run of vectors per workgroup, and the runs are added in order.
 #include "cds_internal.h"
 
 #include <cmath>
@@ -89,37 +96,75 @@ __global__ __launch_bounds__(256) void eps_bar_kernel(const double *__restrict__
     if (threadIdx.x == 0) out[r] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
-// S[kb][p][q] = Bbar^K[p][q] + Bbar^K[q][p] (FP64), Bbar scattered from the sel and vo blocks
-template <typename BT>
-__global__ void sym_bar_kernel(const BT *__restrict__ bsel, const BT *__restrict__ bvo, int64_t ldk, int64_t k0,
-                               int nkb, int nmo, int nocc, int nsel, const int32_t *__restrict__ sel,
-                               double *__restrict__ S)
+// CX[x][nu] = C[nu][sel or occupied orbital of row x] (x < nocc: occupied x; xo <= x < xo + nsel:
+// target x - xo; other rows and nu >= nbf: 0), and Ccat[nu][c] = C[nu][nocc + c] for c < nvirt,
+// C[nu][c - ap] for ap <= c < ap + nocc, else 0
+__global__ void coef_adj_kernel(const double *__restrict__ C, int nbf, int nmo, int nocc, int nsel,
+                                const int32_t *__restrict__ sel, int np_, int xo, int xp, int ap, int cp,
+                                double *__restrict__ CX, double *__restrict__ Ccat)
 {
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t per = (int64_t)nmo * nmo;
-    if (t >= per * nkb) return;
-    int kb = (int)(t / per);
-    int64_t rem = t - kb * per;
-    int p = (int)(rem / nmo), q = (int)(rem - (int64_t)p * nmo);
-    int64_t K = k0 + kb;
-    double v = 0.0;
-    for (int s = 0; s < nsel; ++s) {
-        if (sel[s] == p) v += (double)bsel[((int64_t)s * nmo + q) * ldk + K];
-        if (sel[s] == q) v += (double)bsel[((int64_t)s * nmo + p) * ldk + K];
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n1 = (int64_t)xp * np_;
+    if (t < n1) {
+        const int x = (int)(t / np_), nu = (int)(t - (int64_t)x * np_);
+        const int q = x < nocc ? x : (x >= xo && x < xo + nsel ? sel[x - xo] : -1);
+        CX[t] = q >= 0 && nu < nbf ? C[(int64_t)nu * nmo + q] : 0.0;
+    } else if (t - n1 < (int64_t)nbf * cp) {
+        const int64_t u = t - n1;
+        const int nu = (int)(u / cp), c = (int)(u - (int64_t)nu * cp);
+        const int q = c < nmo - nocc ? nocc + c : (c >= ap && c < ap + nocc ? c - ap : -1);
+        Ccat[u] = q >= 0 ? C[(int64_t)nu * nmo + q] : 0.0;
     }
-    if (p >= nocc && q < nocc) v += (double)bvo[((int64_t)(p - nocc) * nocc + q) * ldk + K];
-    if (q >= nocc && p < nocc) v += (double)bvo[((int64_t)(q - nocc) * nocc + p) * ldk + K];
-    S[t] = v;
 }
 
-// Lu[kb][mu][nu] (nu padded to np_) in FP64
+// out[z oz + kb ok + x] = in[z iz + x ix + kb] (FP64) for kb < nkb, x < nx, and 0 for nx <= x < nxp:
+// 32 x 32 tiles through LDS, every load of a thread in flight before its stores
+template <typename BT>
+__global__ __launch_bounds__(256) void bar_transpose_kernel(const BT *__restrict__ in, int64_t iz, int64_t ix, int nkb,
+                                                            int nx, int nxp, int64_t oz, int64_t ok,
+                                                            double *__restrict__ out)
+{
+    __shared__ double t[32][33];
+    const int x0 = blockIdx.y * 32, k0 = blockIdx.x * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const BT *src = in + blockIdx.z * iz;
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int x = x0 + ty + 8 * u, k = k0 + tx;
+        v[u] = x < nx && k < nkb ? (double)src[x * ix + k] : 0.0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[ty + 8 * u][tx] = v[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int k = k0 + ty + 8 * u, x = x0 + tx;
+        if (k < nkb && x < nxp) out[blockIdx.z * oz + k * ok + x] = t[tx][ty + 8 * u];
+    }
+}
+
+// C_bar[mu][r] from the summed products: virtual columns Pv, occupied columns Po, and the columns
+// of P2 (occupied x at x, target s at xo + s)
+__global__ void cbar_kernel(const double *__restrict__ Pv, const double *__restrict__ Po, const double *__restrict__ P2,
+                            int nbf, int nmo, int nocc, int nsel, const int32_t *__restrict__ sel, int xo, int xp,
+                            double *__restrict__ out)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (int64_t)nbf * nmo) return;
+    const int64_t mu = t / nmo;
+    const int r = (int)(t - mu * nmo);
+    double v = r < nocc ? Po[mu * nocc + r] + P2[mu * xp + r] : Pv[mu * (nmo - nocc) + r - nocc];
+    for (int s = 0; s < nsel; ++s)
+        if (sel[s] == r) v += P2[mu * xp + xo + s];
+    out[t] = v;
+}
+
 // out[e] (+)= sum_{b < nb} part[b][e], b in increasing order
 __global__ void sum_parts_kernel(const double *__restrict__ part, int nb, int64_t ne, int accumulate,
                                  double *__restrict__ out)
 {
     int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= ne) return;
-    // in vector order, eight loads in flight at a time
+    // in order, eight loads in flight at a time
     constexpr int U = 8;
     double acc = accumulate ? out[e] : 0.0;
     for (int b0 = 0; b0 < nb; b0 += U) {
@@ -133,6 +178,7 @@ __global__ void sum_parts_kernel(const double *__restrict__ part, int nb, int64_
     out[e] = acc;
 }
 
+// Lu[kb][mu][nu] (nu padded to np_) in FP64
 __global__ void unpack64_kernel(const double *__restrict__ L, int64_t ldl, int64_t k0, int nkb, int nbf,
                                 int np_, double *__restrict__ out)
 {
@@ -296,60 +342,116 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
         CDS_REQUIRE(ctx, h_sel[s] >= 0 && h_sel[s] < nmo, "h_sel[%d] out of range", s);
     CdsTimer tall;
     CDS_CALL(cds_timer_start(ctx, &tall));
-    const int np_ = (int)(cds_ceil_div(nbf, 64) * 64);
-    // vectors per batch: enough that the first product launches about 2048 tiles of 128 x 128,
-    // with the unpacked batch below 1 GiB (C_bar sums the vectors in order whatever the batch)
-    const int64_t tiles = cds_ceil_div(nmo, 128) * cds_ceil_div(nbf, 128);
-    int64_t kbw = std::max<int64_t>(64, cds_ceil_div(2048, tiles));
-    kbw = std::min<int64_t>(kbw, std::max<int64_t>(1, (int64_t)((1ull << 30) / ((size_t)nbf * np_ * 8))));
-    const int kb = (int)std::min<int64_t>(kbw, nvec);
-    void *wl, *ws, *wk, *wsel, *wp;
+    const int nvirt = nmo - nocc;
+    auto up16 = [](int64_t n) { return (int)(cds_ceil_div(n, 16) * 16); };
+    const int np_ = up16(nbf);
+    const int xo = up16(nocc), selp = up16(nsel), xp = xo + selp;    // rows x: occupied, then targets
+    const int ap = up16(nvirt), cp = ap + up16(nocc);                // columns: virtual, then occupied
+    // vectors per batch: the largest of the batch's arrays stays below 1 GiB
+    const int64_t per = 8 * std::max<int64_t>((int64_t)nbf * np_, std::max<int64_t>((int64_t)xp * np_, (int64_t)nmo * xp));
+    const int kb = (int)std::min<int64_t>(std::min<int64_t>(nvec, 8192), std::max<int64_t>(1, (int64_t)(1ull << 30) / per));
+    // runs of vectors per product, so that each product launches about 1024 tiles
+    auto run_of = [&](int64_t n) {
+        const int64_t tiles = cds_ceil_div(nbf, 128) * cds_ceil_div(n, 128);
+        return std::max<int64_t>(1, kb * tiles / 1024);
+    };
+    const int64_t rv = run_of(nvirt), ro = run_of(nocc), r2 = run_of(xp);
+    auto runs = [](int64_t nkb, int64_t run) { return cds_ceil_div(nkb, run); };
+    const int64_t npart = std::max({runs(kb, rv) * nbf * nvirt, runs(kb, ro) * nbf * nocc, runs(kb, r2) * nbf * xp});
+    void *wl, *wt, *wz, *wy, *wc, *wp;
     CDS_CALL(cds_ws(ctx, WS_TR_UNPACK, (size_t)kb * nbf * np_ * 8, &wl));
-    CDS_CALL(cds_ws(ctx, WS_AD_TMP2, (size_t)kb * nmo * nmo * 8, &ws));
-    CDS_CALL(cds_ws(ctx, WS_TR_T, (size_t)kb * nmo * np_ * 8, &wk));
-    CDS_CALL(cds_ws(ctx, WS_TR_CX, (size_t)nsel * 4 + 64, &wsel));
-    CDS_CALL(cds_ws(ctx, WS_AD_TMP, (size_t)kb * nbf * nmo * 8, &wp));
-    CDS_HIP(ctx, hipMemcpyAsync(wsel, h_sel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
-    // Wt columns nbf..np_-1 are never written: zero once so the padded K range adds nothing
-    CDS_HIP(ctx, hipMemsetAsync(wk, 0, (size_t)kb * nmo * np_ * 8, ctx->stream));
+    CDS_CALL(cds_ws(ctx, WS_TR_T, (size_t)kb * nbf * xp * 8, &wt));                       // T[mu][kb][x]
+    const size_t nzv = (size_t)nvirt * kb * xp, nzo = (size_t)nocc * kb * selp;           // Zv[a][kb][x], Zo[r][kb][s]
+    const size_t nzr = (size_t)nocc * kb * ap, nzs = (size_t)nsel * kb * cp;              // Zr[i][kb][a], Zs[s][kb][c]
+    CDS_CALL(cds_ws(ctx, WS_AD_TMP2, (nzv + nzo + nzr + nzs) * 8, &wz));
+    CDS_CALL(cds_ws(ctx, WS_AD_T1, (size_t)xp * kb * np_ * 8, &wy));                      // Y[x][kb][nu]
+    const size_t ncx = (size_t)xp * np_, nccat = (size_t)nbf * cp, nsum = (size_t)nbf * (nmo + xp);
+    CDS_CALL(cds_ws(ctx, WS_TR_CX, (ncx + nccat + nsum) * 8 + (size_t)nsel * 4 + 64, &wc));
+    CDS_CALL(cds_ws(ctx, WS_AD_TMP, (size_t)npart * 8, &wp));
+    double *Lu = (double *)wl, *T = (double *)wt, *Y = (double *)wy, *part = (double *)wp;
+    double *Zv = (double *)wz, *Zo = Zv + nzv, *Zr = Zo + nzo, *Zs = Zr + nzr;
+    double *CX = (double *)wc, *Ccat = CX + ncx, *Pv = Ccat + nccat, *Po = Pv + (size_t)nbf * nvirt, *P2 = Po + (size_t)nbf * nocc;
+    int32_t *dsel = (int32_t *)(P2 + (size_t)nbf * xp);
+    CDS_HIP(ctx, hipMemcpyAsync(dsel, h_sel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
+    const int64_t ncoef = (int64_t)(ncx + nccat);
+    hipLaunchKernelGGL(coef_adj_kernel, dim3((unsigned)cds_ceil_div(ncoef, 256)), dim3(256), 0, ctx->stream, C, nbf, nmo,
+                       nocc, nsel, (const int32_t *)dsel, np_, xo, xp, ap, cp, CX, Ccat);
+    CDS_LAUNCHED(ctx);
+    const size_t bes = prec == CDS_PREC_FP64 ? 8 : 4;
+    // out[z][kb][x] from the rows z * iz + x * ix of a cotangent block, columns k0 ..
+    auto bars = [&](const void *blk, int64_t row0, int64_t iz, int64_t ix, int nz, int nx, int nxp, double *out, int64_t oz,
+                    int64_t ok, int64_t k0, int nkb) -> int {
+        const dim3 g((unsigned)cds_ceil_div(nkb, 32), (unsigned)cds_ceil_div(nxp, 32), (unsigned)nz);
+        const void *src = (const unsigned char *)blk + (size_t)(row0 * ldk + k0) * bes;
+        if (prec == CDS_PREC_FP64)
+            hipLaunchKernelGGL(bar_transpose_kernel<double>, g, dim3(256), 0, ctx->stream, (const double *)src, iz * ldk,
+                               ix * ldk, nkb, nx, nxp, oz, ok, out);
+        else
+            hipLaunchKernelGGL(bar_transpose_kernel<float>, g, dim3(256), 0, ctx->stream, (const float *)src, iz * ldk,
+                               ix * ldk, nkb, nx, nxp, oz, ok, out);
+        CDS_LAUNCHED(ctx);
+        return CDS_OK;
+    };
+    // sum over the vectors of a batch: out[m][n] (+)= sum_kb sum_k A[m][kb][k] B[n][kb][k]
+    auto summed = [&](int64_t N, int64_t K, int nkb, int64_t run, const double *A, int64_t sAm, int64_t sAb,
+                      const double *B, int64_t sBn, int64_t sBb, bool more, double *out) -> int {
+        GemmDesc g = {};
+        g.M = nbf; g.N = N; g.K = K; g.batch = nkb; g.bacc = run;
+        g.A = A; g.sAm = sAm; g.sAk = 1; g.sAb = sAb;
+        g.B = B; g.sBn = sBn; g.sBk = 1; g.sBb = sBb;
+        g.C = part; g.sCm = N; g.sCn = 1; g.sCb = nbf * N;
+        g.alpha = 1.0; g.beta = 0.0;
+        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, g, nullptr, nullptr));
+        const int64_t ne = nbf * N;
+        hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)cds_ceil_div(ne, 256)), dim3(256), 0, ctx->stream,
+                           (const double *)part, (int)runs(nkb, run), ne, more ? 1 : 0, out);
+        CDS_LAUNCHED(ctx);
+        return CDS_OK;
+    };
     for (int64_t k0 = 0; k0 < nvec; k0 += kb) {
         const int nkb = (int)std::min<int64_t>(kb, nvec - k0);
-        int64_t n1 = (int64_t)nkb * nbf * np_;
+        const int64_t n1 = (int64_t)nkb * nbf * np_;
         hipLaunchKernelGGL(unpack64_kernel, dim3((unsigned)cds_ceil_div(n1, 256)), dim3(256), 0, ctx->stream, L,
-                           ldl, k0, nkb, nbf, np_, (double *)wl);
-        int64_t n2 = (int64_t)nkb * nmo * nmo;
-        if (prec == CDS_PREC_FP64)
-            hipLaunchKernelGGL(sym_bar_kernel<double>, dim3((unsigned)cds_ceil_div(n2, 256)), dim3(256), 0,
-                               ctx->stream, (const double *)Bsel_bar, (const double *)Bvo_bar, ldk, k0, nkb,
-                               nmo, nocc, nsel, (const int32_t *)wsel, (double *)ws);
-        else
-            hipLaunchKernelGGL(sym_bar_kernel<float>, dim3((unsigned)cds_ceil_div(n2, 256)), dim3(256), 0,
-                               ctx->stream, (const float *)Bsel_bar, (const float *)Bvo_bar, ldk, k0, nkb,
-                               nmo, nocc, nsel, (const int32_t *)wsel, (double *)ws);
+                           ldl, k0, nkb, nbf, np_, Lu);
         CDS_LAUNCHED(ctx);
-        // Wt[kb][p][nu] = sum_r S[kb][p][r] C[nu][r]   (S symmetric; both operands K-contiguous)
-        GemmDesc g1 = {};
-        g1.M = nmo; g1.N = nbf; g1.K = nmo; g1.batch = nkb;
-        g1.A = ws; g1.sAm = nmo; g1.sAk = 1; g1.sAb = (int64_t)nmo * nmo;
-        g1.B = C; g1.sBn = nmo; g1.sBk = 1; g1.sBb = 0;
-        g1.C = wk; g1.sCm = np_; g1.sCn = 1; g1.sCb = (int64_t)nmo * np_;
-        g1.alpha = 1.0; g1.beta = 0.0;
-        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, g1, nullptr, nullptr));
-        // part[kb][mu][p] = sum_nu Lu[kb][mu][nu] Wt[kb][p][nu]: one product per vector (the batch
-        // index splits the long reduction over (kb, nu) so the tiny output still fills the chip)
-        GemmDesc g2 = {};
-        g2.M = nbf; g2.N = nmo; g2.K = np_; g2.batch = nkb;
-        g2.A = wl; g2.sAm = np_; g2.sAk = 1; g2.sAb = (int64_t)nbf * np_;
-        g2.B = wk; g2.sBn = np_; g2.sBk = 1; g2.sBb = (int64_t)nmo * np_;
-        g2.C = wp; g2.sCm = nmo; g2.sCn = 1; g2.sCb = (int64_t)nbf * nmo;
-        g2.alpha = 1.0; g2.beta = 0.0;
-        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, g2, nullptr, nullptr));
-        // C_bar (+)= sum_kb part[kb] in fixed order
-        const int64_t ne = (int64_t)nbf * nmo;
-        hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)cds_ceil_div(ne, 256)), dim3(256), 0, ctx->stream,
-                           (const double *)wp, nkb, ne, k0 > 0 ? 1 : 0, C_bar);
-        CDS_LAUNCHED(ctx);
+        // T[mu][kb][x] = sum_nu L^K[mu][nu] CX[x][nu]
+        GemmDesc gt = {};
+        gt.M = nbf; gt.N = xp; gt.K = np_; gt.batch = nkb;
+        gt.A = Lu; gt.sAm = np_; gt.sAk = 1; gt.sAb = (int64_t)nbf * np_;
+        gt.B = CX; gt.sBn = np_; gt.sBk = 1; gt.sBb = 0;
+        gt.C = T; gt.sCm = (int64_t)nkb * xp; gt.sCn = 1; gt.sCb = xp;
+        gt.alpha = 1.0; gt.beta = 0.0;
+        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, gt, nullptr, nullptr));
+        // the cotangents with x along the rows (Zv: virtual columns a, occupied rows then targets; Zo:
+        // the targets' occupied columns), then C_bar_r += sum T Z
+        const int64_t zs = (int64_t)nkb * xp;
+        CDS_CALL(bars(Bvo_bar, 0, nocc, 1, nvirt, nocc, xo, Zv, zs, xp, k0, nkb));
+        CDS_CALL(bars(Bsel_bar, nocc, 1, nmo, nvirt, nsel, selp, Zv + xo, zs, xp, k0, nkb));
+        CDS_CALL(bars(Bsel_bar, 0, 1, nmo, nocc, nsel, selp, Zo, (int64_t)nkb * selp, selp, k0, nkb));
+        CDS_CALL(summed(nvirt, xp, nkb, rv, T, zs, xp, Zv, zs, xp, k0 > 0, Pv));
+        CDS_CALL(summed(nocc, selp, nkb, ro, T + xo, zs, xp, Zo, (int64_t)nkb * selp, selp, k0 > 0, Po));
+        // the cotangents with r along the rows, Y[x][kb][nu] = sum_r Z[x][kb][r] C[nu][r], then
+        // C_bar_x += sum L Y
+        CDS_CALL(bars(Bvo_bar, 0, 1, nocc, nocc, nvirt, ap, Zr, (int64_t)nkb * ap, ap, k0, nkb));
+        CDS_CALL(bars(Bsel_bar, nocc, nmo, 1, nsel, nvirt, ap, Zs, (int64_t)nkb * cp, cp, k0, nkb));
+        CDS_CALL(bars(Bsel_bar, 0, nmo, 1, nsel, nocc, cp - ap, Zs + ap, (int64_t)nkb * cp, cp, k0, nkb));
+        GemmDesc gy = {};
+        gy.M = (int64_t)nocc * nkb; gy.N = np_; gy.K = ap; gy.batch = 1;
+        gy.A = Zr; gy.sAm = ap; gy.sAk = 1;
+        gy.B = Ccat; gy.sBn = cp; gy.sBk = 1;
+        gy.C = Y; gy.sCm = np_; gy.sCn = 1;
+        gy.alpha = 1.0; gy.beta = 0.0;
+        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, gy, nullptr, nullptr));
+        gy.M = (int64_t)nsel * nkb; gy.K = cp;
+        gy.A = Zs; gy.sAm = cp;
+        gy.C = Y + (int64_t)xo * nkb * np_;
+        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, gy, nullptr, nullptr));
+        CDS_CALL(summed(xp, np_, nkb, r2, Lu, np_, (int64_t)nbf * np_, Y, (int64_t)nkb * np_, np_, k0 > 0, P2));
     }
+    const int64_t ne = (int64_t)nbf * nmo;
+    hipLaunchKernelGGL(cbar_kernel, dim3((unsigned)cds_ceil_div(ne, 256)), dim3(256), 0, ctx->stream, (const double *)Pv,
+                       (const double *)Po, (const double *)P2, nbf, nmo, nocc, nsel, (const int32_t *)dsel, xo, xp, C_bar);
+    CDS_LAUNCHED(ctx);
     CDS_CALL(cds_timer_stop(ctx, &tall, &ctx->stats.t_adjoint_ms));
     return CDS_OK;
 }

@@ -197,6 +197,8 @@ struct GemmDesc {
     int64_t nblk, sCblk;     // nblk > 0: column n of C lies at (n / nblk) sCblk + (n % nblk) sCn
     int64_t tri;             // tri > 0: tiles whose every column block n / tri is below its every
                              // row block m / tri are not formed (the lower block triangle)
+    int64_t bacc;            // bacc > 1: each run of bacc batch entries is summed, in order, into one
+                             // C (C + run * sCb); K-contiguous, 16-byte aligned FP64 / FP32 operands
 };
 // prec of A/B/C: FP64 -> double, FP32/BF16X3 -> float storage
 int cds_gemm(cds_ctx *ctx, int prec, const GemmDesc &d);

@@ -46,6 +46,7 @@ struct Args {
     int big;                       // GemmDesc::big
     int64_t nblk, sCblk;           // GemmDesc::nblk, sCblk
     int64_t tri;                   // GemmDesc::tri
+    int64_t bacc;                  // GemmDesc::bacc (at least 1)
 };
 
 // element offset of C column n within a row
@@ -508,12 +509,13 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
     const unsigned t = xcd_order<64>(blockIdx.x, gridDim.x), bt = t / per;   // two workgroups on each of 32 CUs
     unsigned tm, tn;
     tile_at(t - bt * per, a.tri, gx, gy, th, tw, tm, tn);
-    const int64_t n0 = (int64_t)tn * tw, m0 = (int64_t)tm * th, batch = bt;
+    const int64_t n0 = (int64_t)tn * tw, m0 = (int64_t)tm * th, batch = bt * a.bacc;
     if (below(a, m0, n0 + tw - 1)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
-    const int64_t ns = a.K / Tr<PREC>::KB;
+    const int64_t nb = a.K / Tr<PREC>::KB;                      // stages per batch entry, and in all
+    const int64_t ns = nb * min(a.bacc, a.batch - batch);
     // this wave's four loads per stage: slice sl (0 A, 1 B), rows 8 q + lane / 8 for q in
     // [4 (wave & 3), 4 (wave & 3) + 4), position lane % 8 holding the swizzled logical chunk
     const int sl = wave >> 2;
@@ -529,11 +531,17 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
         const int64_t row = min(r0g + rr, nrows - 1);
         src[q] = mat + ((batch * sb + row * srow) * ES) + ((pc ^ (rr & 7)) * 16);
     }
-    auto stage_load = [&](int buf, int64_t st) __attribute__((always_inline)) {
+    int64_t koff = 0, left = nb;                                // next stage: byte offset, stages left in its entry
+    auto stage_load = [&](int buf) __attribute__((always_inline)) {
         unsigned char *dst = lds + buf * GD_STAGE + sl * GD_SLICE + (4 * (wave & 3)) * 1024;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (q < nld) cds_lds_dma16(src[q] + st * 128, dst + q * 1024);
+            if (q < nld) cds_lds_dma16(src[q] + koff, dst + q * 1024);
+        koff += 128;
+        if (--left == 0) {
+            left = nb;
+            koff += sb * ES - nb * 128;
+        }
     };
 
     // blocks of 16 x 16 inside C and this wave's share: block rows rb0 .. rb0 + nbr, columns cb0 ..
@@ -556,12 +564,12 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
     auto run = [&](auto NAc, auto FULLc) __attribute__((always_inline)) {
         constexpr int NA = decltype(NAc)::value, NJ = 8 / NA, NV = 16 / ES;
         constexpr bool full = decltype(FULLc)::value;
-        stage_load(0, 0);
+        stage_load(0);
         for (int64_t st = 0; st < ns; ++st) {
             __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's loads of stage st
             __builtin_amdgcn_s_barrier();                      // every wave's; and stage st - 1 is read
             asm volatile("" ::: "memory");
-            if (st + 1 < ns) stage_load((int)((st + 1) & 1), st + 1);
+            if (st + 1 < ns) stage_load((int)((st + 1) & 1));
             const unsigned char *cur = lds + (st & 1) * GD_STAGE;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -597,7 +605,7 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
     else if (nbr == 4 && nbc == 2) run(std::integral_constant<int, 4>(), T_());
     else run(std::integral_constant<int, 4>(), F_());
 
-    E *C = reinterpret_cast<E *>(a.C) + batch * a.sCb;
+    E *C = reinterpret_cast<E *>(a.C) + (int64_t)bt * a.sCb;
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
         const int i = deal == 0 ? b >> 1 : (deal == 1 ? 0 : b), j = deal == 0 ? b & 1 : (deal == 1 ? b : 0);
@@ -629,6 +637,8 @@ int launch(cds_ctx *ctx, Args &a)
     if (PREC == CDS_PREC_BF16X3 && (!a.fastA || !a.fastB))
         return cds_fail(ctx, CDS_EINVAL, "bf16x3 GEMM needs K-contiguous 16-byte aligned operands");
     if (a.M <= 0 || a.N <= 0 || a.batch <= 0) return CDS_OK;
+    if (a.bacc > 1 && (PREC == CDS_PREC_BF16X3 || !a.fastA || !a.fastB))
+        return cds_fail(ctx, CDS_EINVAL, "GEMM over several batch entries needs K-contiguous FP64 or FP32 operands");
     int64_t gx = cds_ceil_div(a.N, BN), gy = cds_ceil_div(a.M, BM);
     if (gy > 65535 || a.batch > 65535)
         return cds_fail(ctx, CDS_EINVAL, "GEMM grid too large (%lld x %lld x %lld)", (long long)gx,
@@ -646,7 +656,7 @@ int launch(cds_ctx *ctx, Args &a)
         }
     }
     if constexpr (PREC != CDS_PREC_BF16X3) {
-        // fast operands have K a multiple of the stage and 16-byte aligned rows; so must the batches
+        // direct-to-LDS stages: fast operands have K a multiple of the stage and 16-byte aligned rows; so must the batches
         if (a.fastA && a.fastB && (a.sAb * (int64_t)sizeof(E)) % 16 == 0 && (a.sBb * (int64_t)sizeof(E)) % 16 == 0 &&
             gx * gy <= 0x7fffffff / a.batch && (!a.tri || a.batch == 1)) {
             // a last tile of one or two blocks of 16 costs a whole tile's loads: there the blocks are
@@ -657,11 +667,12 @@ int launch(cds_ctx *ctx, Args &a)
             };
             const int th = edge(a.M, gy), tw = edge(a.N, gx);
             const unsigned per = (unsigned)count_tiles(a.tri, (unsigned)gx, (unsigned)gy, th, tw);
-            hipLaunchKernelGGL(gemm_dma_kernel<PREC>, dim3(per * (unsigned)a.batch), dim3(GD_NT), 0, ctx->stream, a, per,
+            hipLaunchKernelGGL(gemm_dma_kernel<PREC>, dim3(per * (unsigned)cds_ceil_div(a.batch, a.bacc)), dim3(GD_NT), 0, ctx->stream, a, per,
                                (unsigned)gx, (unsigned)gy, th, tw);
             CDS_LAUNCHED(ctx);
             return CDS_OK;
         }
+        if (a.bacc > 1) return cds_fail(ctx, CDS_EINVAL, "GEMM over several batch entries: unaligned or too many");
     }
     size_t lds = (size_t)2 * Tr<PREC>::PLANES * BM * PITCH;
     hipLaunchKernelGGL(gemm_kernel<PREC>, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.batch), dim3(NT),
@@ -746,6 +757,7 @@ int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, cons
     a.nblk = d.nblk;
     a.sCblk = d.sCblk;
     a.tri = d.tri;
+    a.bacc = d.bacc > 1 ? d.bacc : 1;
     if (a.nblk && a.N > 0x7fffffff) return cds_fail(ctx, CDS_EINVAL, "GEMM columns in blocks: N too large");
     if (prec == CDS_PREC_FP64) return launch<CDS_PREC_FP64>(ctx, a);
     if (prec == CDS_PREC_FP32) return launch<CDS_PREC_FP32>(ctx, a);
