@@ -6,10 +6,11 @@
 // With g = (q r|a j) = G[s][r][a*nocc+j] (Eq. (aomo)) the self-energy Eq. (SE)
 // depends on each integral through its own term and its exchange partner:
 //   dSigma/dx_{a;ij} = (4 x_{a;ij} - 2 x_{a;ji}) / d_{a;ij},  same for y.
-// Since G = Bsel Bvo^T:
-//   Bsel_bar[s] = W[s] Bvo            (W = omega_bar P dSigma/dG)
-//   Bvo_bar     = sum_s W[s]^T Bsel[s]
-// and the energies enter through the denominators and e_q itself.
+// Since G = Bsel Bvo^T, with W = dSigma/dG and the scale omega_bar_s P_s of each target:
+//   Bsel_bar[s] = scale_s W[s] Bvo
+//   Bvo_bar     = sum_s W[s]^T (scale_s Bsel[s])
+// and the energies enter through the denominators and e_q itself.  Only W^T is written, [v][(s, r)]:
+// the first product reads it m-contiguous, the second K-contiguous.
 // Transform adjoint: B^K = C^T L^K C gives C_bar = sum_K L^K C (Bbar^K + Bbar^K^T).  Bbar has only the
 // rows of the targets and the virtual-occupied block, so with the rows x = occupied orbitals and
 // targets, Z^K[x][r] their cotangents (occupied i: Bvo_bar[a][i] at r = a; target s: Bsel_bar[s][r]),
@@ -24,16 +25,8 @@
 #include <vector>
 
 int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, const void *Blo);
-int cds_sigma_eval_internal(cds_ctx *ctx, int prec, int64_t nvec, int64_t ldk, int nmo, int nocc,
-                            int nsel, const void *Bsel, const void *Bvo, const double *eps,
-                            const double *h_omega, int T, double *h_out);
 int cds_contract_internal(cds_ctx *ctx, int prec, int64_t nvec, int64_t ldk, int nmo, int nocc,
                           int nsel, const void *Bsel, const void *Bvo, int s0, int nsc, void *G);
-int cds_grad_epilogue_internal(cds_ctx *ctx, int prec, int nmo, int nocc, int nsc, const void *G,
-                               const double *eps, const double *d_omega, const double *d_gscale,
-                               void *W, double *epsA, double *epsB);
-int cds_sigma_from_g_internal(cds_ctx *ctx, int prec, int nmo, int nocc, int nsc, const void *G,
-                              const double *eps, const double *d_omega, double *d_out);
 
 namespace {
 
@@ -44,56 +37,307 @@ __global__ void planes_to_float_kernel(const __bf16 *__restrict__ b, int64_t n, 
     if (t < n) out[t] = (float)b[t] + (float)b[n + t];
 }
 
+// B[r][c] = 0 for r < nrows, c0 <= c < ld
 template <typename T>
-__global__ void zero_cols_kernel(T *__restrict__ B, int64_t nrows, int64_t ldk, int64_t c0)
+__global__ void zero_cols_kernel(T *__restrict__ B, int64_t nrows, int64_t ld, int64_t c0)
 {
-    int64_t npad = ldk - c0;
+    int64_t npad = ld - c0;
     int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= nrows * npad) return;
     int64_t r = t / npad;
-    B[r * ldk + c0 + (t - r * npad)] = (T)0;
+    B[r * ld + c0 + (t - r * npad)] = (T)0;
 }
 
-// eps_bar[r] = sum over targets and blocks of the energy partials, + P*omega_bar on e_q
-// eps_bar[r]: one workgroup per orbital r; the threads take the (target, virtual) partials in a
-// fixed stride, four loads in flight at a time, and the workgroup sums them in a fixed order
-__global__ __launch_bounds__(256) void eps_bar_kernel(const double *__restrict__ epsA, const double *__restrict__ epsB,
-                                                      int nsel, int nocc, int nvirt, const int32_t *__restrict__ sel,
-                                                      const double *__restrict__ gscale, double *__restrict__ out)
+template <typename T>
+int zero_cols(cds_ctx *ctx, T *B, int64_t nrows, int64_t ld, int64_t c0)
+{
+    if (nrows <= 0 || ld <= c0) return CDS_OK;
+    hipLaunchKernelGGL(zero_cols_kernel<T>, dim3((unsigned)cds_ceil_div(nrows * (ld - c0), 256)), dim3(256), 0, ctx->stream,
+                       B, nrows, ld, c0);
+    CDS_LAUNCHED(ctx);
+    return CDS_OK;
+}
+
+template <int NTH>
+__device__ __forceinline__ double block_sum(double v, double *sh)
+{
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double s = 0.0;
+    for (int k = 0; k < NTH / 64; ++k) s += sh[k];   // fixed order
+    return s;
+}
+
+// Weights and energy partials of a chunk of targets.  Both kernels read every integral once, both
+// exchange partners together, and write W^T in runs of consecutive r: HBM traffic is one read of G
+// and one write of W^T.  (Separate kernels for Sigma', W with a thread per row, and a transposed
+// copy of W took 3.2 ms for 480 orbitals, 12 targets FP64; these take 1.1 ms.)
+struct WArgs {
+    const void *G;          // integrals of the chunk [sc][nmo][nvo]
+    void *WT;               // weights [nvo][kc_pad], column s * nmo + r
+    int nmo, nocc, nvirt;
+    int64_t nvo, ldw;
+    const double *eps, *omega;      // omega: [sc]
+    double *epsA;           // [sc][nvirt][nocc + 1]: part A by virtual a: each e_i, then e_a
+    double *epsBi;          // [sc][pairs of virtual tiles][nocc]: part B, each e_i
+    double *epsBv;          // [sc][pairs][2 * WB]: part B, e_a of the pair's two tiles
+    int npairs;
+};
+
+// part A (fixed virtual a = blockIdx.x, target blockIdx.y), X[i][j] = (qi|aj), d = w + e_a - e_i - e_j:
+// 32 x 32 tile pairs (IB <= JB) of X and its transpose through LDS.  W_ij = (4 x - 2 x') / d; with
+// u = (2 x - x') x and t_ij = (u_ij + u_ji) / d^2 (symmetric), e_i gets sum_j t_ij and e_a
+// -sum_ij u_ij / d^2.
+template <typename GT>
+__global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
 {
     __shared__ double sh[4];
-    const int r = blockIdx.x;
-    const int64_t per = (int64_t)nvirt * (nocc + 1);
-    double acc = 0.0;
-    if (r < nocc) {
-        const int64_t n = (int64_t)nsel * nvirt;                 // (target, virtual) pairs
-        constexpr int U = 4;
-        for (int64_t q0 = threadIdx.x; q0 < n; q0 += (int64_t)U * 256) {
-            double va[U], vb[U];
+    __shared__ double eo[1024], ei[1024];
+    __shared__ double t1[32][33], t2[32][33];
+    const int a = blockIdx.x, s = blockIdx.y, nocc = e.nocc;
+    for (int i = threadIdx.x; i < nocc; i += 256) {
+        eo[i] = e.eps[i];
+        ei[i] = 0.0;
+    }
+    const double d0 = e.omega[s] + e.eps[nocc + a];
+    const GT *G = (const GT *)e.G + (int64_t)s * e.nmo * e.nvo + (int64_t)a * nocc;     // + i*nvo + j
+    GT *WT = (GT *)e.WT + (int64_t)a * nocc * e.ldw + (int64_t)s * e.nmo;               // + j*ldw + i
+    double ea = 0.0;
+    const int nb = (nocc + 31) / 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    for (int IB = 0; IB < nb; ++IB)
+        for (int JB = IB; JB < nb; ++JB) {
+            double v1[4], v2[4];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int64_t q = q0 + (int64_t)u * 256 < n ? q0 + (int64_t)u * 256 : n - 1;
-                const int64_t s = q / nvirt, a = q - s * nvirt;
-                const int64_t off = s * per + a * (nocc + 1) + r;
-                va[u] = epsA[off];
-                vb[u] = epsB[off];
+            for (int u = 0; u < 4; ++u) {
+                const int r = ty + 8 * u;
+                const int i1 = IB * 32 + r, j1 = JB * 32 + tx, i2 = JB * 32 + r, j2 = IB * 32 + tx;
+                v1[u] = i1 < nocc && j1 < nocc ? (double)G[(int64_t)i1 * e.nvo + j1] : 0.0;   // X[i1][j1]
+                v2[u] = i2 < nocc && j2 < nocc ? (double)G[(int64_t)i2 * e.nvo + j2] : 0.0;   // X[i2][j2]
             }
+            __syncthreads();
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (q0 + (int64_t)u * 256 < n) acc += va[u] + vb[u];
+            for (int u = 0; u < 4; ++u) {
+                t1[ty + 8 * u][tx] = v1[u];
+                t2[ty + 8 * u][tx] = v2[u];
+            }
+            __syncthreads();
+            // element (i, j) = (IB*32 + tx, JB*32 + cj): the weights of both partners, W_ij along i
+            // straight out, W_ji (along j) and t_ij back into the tiles
+            double tv[4], wv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int cj = ty + 8 * u, i = IB * 32 + tx, j = JB * 32 + cj;
+                const bool in = i < nocc && j < nocc;
+                const double x = t1[tx][cj], xt = t2[cj][tx];
+                const double id = in ? 1.0 / (d0 - eo[i] - eo[j]) : 0.0;
+                const double uu = (2.0 * x - xt) * x, ut = (2.0 * xt - x) * xt;
+                tv[u] = in ? (uu + ut) * id * id : 0.0;
+                wv[u] = (4.0 * xt - 2.0 * x) * id;
+                // off the diagonal tile both partners are counted here
+                ea -= in ? (IB == JB ? uu : uu + ut) * id * id : 0.0;
+                if (in) WT[(int64_t)j * e.ldw + i] = (GT)((4.0 * x - 2.0 * xt) * id);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                t1[tx][ty + 8 * u] = tv[u];
+                t2[tx][ty + 8 * u] = wv[u];                              // W_ji at [i][j]
+            }
+            __syncthreads();
+            if (IB != JB)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = IB * 32 + ty + 8 * u, j = JB * 32 + tx;
+                    if (i < nocc && j < nocc) WT[(int64_t)i * e.ldw + j] = (GT)t2[ty + 8 * u][tx];
+                }
+            // row sums of t to e_i, and off the diagonal tile its column sums to e_j
+            if (threadIdx.x < 32) {
+                double v = 0.0;
+                for (int c = 0; c < 32; ++c) v += t1[threadIdx.x][c];
+                if (IB * 32 + (int)threadIdx.x < nocc) ei[IB * 32 + threadIdx.x] += v;
+            } else if (threadIdx.x >= 64 && threadIdx.x < 96 && IB != JB) {
+                double v = 0.0;
+                for (int r = 0; r < 32; ++r) v += t1[r][threadIdx.x - 64];
+                if (JB * 32 + (int)threadIdx.x - 64 < nocc) ei[JB * 32 + threadIdx.x - 64] += v;
+            }
         }
-    } else {
-        for (int s = threadIdx.x; s < nsel; s += 256) {
-            const int64_t off = (int64_t)s * per + (int64_t)(r - nocc) * (nocc + 1) + nocc;
-            acc += epsA[off] + epsB[off];
+    __syncthreads();
+    double *dst = e.epsA + ((int64_t)s * e.nvirt + a) * (nocc + 1);
+    for (int i = threadIdx.x; i < nocc; i += 256) dst[i] = ei[i];
+    ea = block_sum<256>(ea, sh);
+    if (threadIdx.x == 0) dst[nocc] = ea;
+}
+
+// part B, Y_i[a][b] = (qa|ib) = G[nocc + a][b nocc + i], d = w + e_i - e_a - e_b: a pair of tiles of WB
+// virtuals (TA <= TB) and all i, WB at a time.  e_i gets -sum_ab u_ab / d^2 and e_a sum_b (u_ab +
+// u_ba) / d^2.
+constexpr int WB = 16, WB_A = WB * WB + 1;      // LDS: [a][b][i], rows of a padded to an odd stride
+
+template <typename GT>
+__global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
+{
+    __shared__ double y1[WB * WB_A], y2[WB * WB_A];
+    __shared__ double sb[WB][WB + 1];
+    const int s = blockIdx.y, nocc = e.nocc, nvirt = e.nvirt;
+    int TA = 0, p = blockIdx.x;
+    const int nt = (nvirt + WB - 1) / WB;
+    while (p >= nt - TA) p -= nt - TA++;
+    const int TB = TA + p;
+    const bool diag = TA == TB;
+    const int a0 = TA * WB, b0 = TB * WB;
+    const int lo = threadIdx.x & 15, hi = threadIdx.x >> 4;
+    const GT *G = (const GT *)e.G + (int64_t)s * e.nmo * e.nvo;
+    GT *WT = (GT *)e.WT + (int64_t)s * e.nmo + nocc;                 // + (b nocc + i) ldw + a
+    const double *ev = e.eps + nocc;
+    double ea[WB];                                                   // e_a of the pair's first tile
+    for (int a = 0; a < WB; ++a) ea[a] = 0.0;
+    double eb = 0.0;                                                 // e_b, b = b0 + hi
+    const double w0 = e.omega[s], vb = ev[min(b0 + hi, nvirt - 1)];
+    for (int i0 = 0; i0 < nocc; i0 += WB) {
+        // thread (b, i) = (hi, lo): every a of the first tile and both partners
+        const int i = i0 + lo, b = b0 + hi;
+        const bool inb = i < nocc && b < nvirt;
+        const double wi = w0 + e.eps[min(i, nocc - 1)] - vb;
+        double y[WB], yt[WB];
+#pragma unroll
+        for (int a = 0; a < WB; ++a) {
+            const bool in = inb && a0 + a < nvirt;
+            y[a] = in ? (double)G[(int64_t)(nocc + a0 + a) * e.nvo + (int64_t)b * nocc + i] : 0.0;
+            yt[a] = in ? (double)G[(int64_t)(nocc + b) * e.nvo + (int64_t)(a0 + a) * nocc + i] : 0.0;
+        }
+        double si = 0.0;
+        __syncthreads();                                             // the tiles of the last round are written out
+#pragma unroll
+        for (int a = 0; a < WB; ++a) {
+            const bool in = inb && a0 + a < nvirt;
+            const double id = in ? 1.0 / (wi - ev[min(a0 + a, nvirt - 1)]) : 0.0;
+            const double u = (2.0 * y[a] - yt[a]) * y[a] * id * id, ut = (2.0 * yt[a] - y[a]) * yt[a] * id * id;
+            si -= diag ? u : u + ut;
+            ea[a] += u + ut;
+            eb += u + ut;
+            y1[a * WB_A + hi * WB + lo] = (4.0 * y[a] - 2.0 * yt[a]) * id;
+            y2[a * WB_A + hi * WB + lo] = (4.0 * yt[a] - 2.0 * y[a]) * id;
+        }
+        sb[lo][hi] = si;
+        __syncthreads();
+        // W^T rows (b, i), 16 consecutive a; rows (a, i), 16 consecutive b (thread (i, r) = (hi, lo))
+        const int io = i0 + hi;
+        if (io < nocc) {
+#pragma unroll 4
+            for (int c = 0; c < WB; ++c)
+                if (a0 + lo < nvirt && b0 + c < nvirt)
+                    WT[((int64_t)(b0 + c) * nocc + io) * e.ldw + a0 + lo] = (GT)y1[lo * WB_A + c * WB + hi];
+            if (!diag)
+#pragma unroll 4
+                for (int c = 0; c < WB; ++c)
+                    if (b0 + lo < nvirt && a0 + c < nvirt)
+                        WT[((int64_t)(a0 + c) * nocc + io) * e.ldw + b0 + lo] = (GT)y2[c * WB_A + lo * WB + hi];
+        }
+        if (threadIdx.x < WB && i0 + (int)threadIdx.x < nocc) {
+            double v = 0.0;
+            for (int c = 0; c < WB; ++c) v += sb[threadIdx.x][c];
+            e.epsBi[((int64_t)s * e.npairs + blockIdx.x) * nocc + i0 + threadIdx.x] = v;
         }
     }
-    for (int s = threadIdx.x; s < nsel; s += 256)
-        if (sel[s] == r) acc += gscale[s];
-    for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = acc;
+    // e_a: over the 256 threads; e_b: over the 16 threads of b (off the diagonal: the second tile)
     __syncthreads();
-    if (threadIdx.x == 0) out[r] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+#pragma unroll
+    for (int a = 0; a < WB; ++a) y1[a * WB_A + threadIdx.x] = ea[a];
+    y2[threadIdx.x] = eb;
+    __syncthreads();
+    if (threadIdx.x < WB) {
+        double v = 0.0, x = 0.0;
+        for (int c = 0; c < 256; ++c) v += y1[threadIdx.x * WB_A + c];
+        for (int c = 0; c < WB; ++c) x += y2[threadIdx.x * WB + c];
+        double *dst = e.epsBv + ((int64_t)s * e.npairs + blockIdx.x) * 2 * WB;
+        dst[threadIdx.x] = v;
+        dst[WB + threadIdx.x] = diag ? 0.0 : x;
+    }
+}
+
+// scale[s] = omega_bar_s / (1 - Sigma'_s): Sigma' is the sum of part A's e_a and part B's e_i partials
+// (each is -sum u / d^2)
+__global__ __launch_bounds__(256) void scale_kernel(const double *__restrict__ epsA, const double *__restrict__ epsBi,
+                                                    int nocc, int nvirt, int npairs, const double *__restrict__ omega_bar,
+                                                    double *__restrict__ scale)
+{
+    __shared__ double sh[4];
+    const int s = blockIdx.x;
+    double v = 0.0;
+    for (int a = threadIdx.x; a < nvirt; a += 256) v += epsA[((int64_t)s * nvirt + a) * (nocc + 1) + nocc];
+    const int64_t n = (int64_t)npairs * nocc;
+    constexpr int U = 4;
+    for (int64_t q0 = threadIdx.x; q0 < n; q0 += U * 256) {
+        double x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) x[u] = q0 + u * 256 < n ? epsBi[s * n + q0 + u * 256] : 0.0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) v += x[u];
+    }
+    v = block_sum<256>(v, sh);
+    if (threadIdx.x == 0) scale[s] = omega_bar[s] / (1.0 - v);
+}
+
+// eps_bar[r] = sum_s scale_s (the energy partials of r) + scale_s on e_q: one workgroup per orbital,
+// partials in a fixed stride, four loads in flight at a time, summed in a fixed order
+__global__ __launch_bounds__(256) void eps_bar_kernel(const double *__restrict__ epsA, const double *__restrict__ epsBi,
+                                                      const double *__restrict__ epsBv, int nsel, int nocc, int nvirt,
+                                                      int npairs, const int32_t *__restrict__ sel,
+                                                      const double *__restrict__ scale, double *__restrict__ out)
+{
+    __shared__ double sh[4];
+    const int r = blockIdx.x, nt = (nvirt + WB - 1) / WB;
+    const int ta = (r - nocc) / WB, la = (r - nocc) % WB;            // r >= nocc: its tile and place
+    const int per = r < nocc ? nvirt + npairs : nt + 1;              // partials of r per target
+    const int64_t n = (int64_t)nsel * per;
+    constexpr int U = 4;
+    double acc = 0.0;
+    for (int64_t q0 = threadIdx.x; q0 < n; q0 += (int64_t)U * 256) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = q0 + (int64_t)u * 256 < n ? q0 + (int64_t)u * 256 : n - 1;
+            const int64_t s = q / per;
+            const int k = (int)(q - s * per);
+            if (r < nocc) {
+                v[u] = k < nvirt ? epsA[(s * nvirt + k) * (nocc + 1) + r] : epsBi[(s * npairs + k - nvirt) * nocc + r];
+            } else if (k == nt) {
+                v[u] = epsA[(s * nvirt + r - nocc) * (nocc + 1) + nocc];
+            } else {
+                // tile pair (min(ta, k), max(ta, k)): first place where ta is the smaller
+                const int lo = ta < k ? ta : k, hi = ta < k ? k : ta;
+                const int64_t pr = (int64_t)lo * nt - (int64_t)lo * (lo - 1) / 2 + (hi - lo);
+                v[u] = epsBv[(s * npairs + pr) * 2 * WB + (ta <= k ? 0 : WB) + la];
+            }
+            v[u] *= scale[s];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (q0 + (int64_t)u * 256 < n) acc += v[u];
+    }
+    for (int s = threadIdx.x; s < nsel; s += 256)
+        if (sel[s] == r) acc += scale[s];
+    acc = block_sum<256>(acc, sh);
+    if (threadIdx.x == 0) out[r] = acc;
+}
+
+// B[row][n] = scale[row / per] sum_b part[b][row][n] in order, n < nvec; 0 for nvec <= n < ldk
+template <typename T>
+__global__ __launch_bounds__(256) void sum_scaled_kernel(const T *__restrict__ part, int nb, int64_t rows, int64_t nvec,
+                                                         int64_t per, const double *__restrict__ scale,
+                                                         T *__restrict__ B, int64_t ldk)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= rows * ldk) return;
+    const int64_t row = t / ldk, n = t - row * ldk;
+    double v = 0.0;
+    if (n < nvec) {
+        for (int b = 0; b < nb; ++b) v += (double)part[(int64_t)b * rows * nvec + row * nvec + n];
+        v *= scale[row / per];
+    }
+    B[t] = (T)v;
 }
 
 // CX[x][nu] = C[nu][sel or occupied orbital of row x] (x < nocc: occupied x; xo <= x < xo + nsel:
@@ -218,17 +462,15 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
     const int nvirt = nmo - nocc;
     const int64_t nvo = (int64_t)nvirt * nocc, nselr = (int64_t)nsel * nmo;
 
-    // the pole strengths at the converged energies come from each chunk's integrals (below)
-    std::vector<double> out((size_t)nsel * 2), hscale(nsel);
-
     // working copies: float operands for BF16X3 (planes -> float)
     const int gprec = prec == CDS_PREC_FP64 ? CDS_PREC_FP64 : CDS_PREC_FP32;
     const size_t es = prec == CDS_PREC_FP64 ? 8 : 4;
     const void *Bs = Bsel, *Bv = Bvo;
     void *tmp;
     size_t nB = (size_t)(nselr + nvo) * ldk;
-    size_t small = (size_t)nsel * 8 * 5 + (size_t)nsel * 4 + 256;
-    size_t epsbytes = (size_t)2 * nsel * nvirt * (nocc + 1) * 8;
+    const int nt = (nvirt + WB - 1) / WB, npairs = nt * (nt + 1) / 2;
+    size_t small = (size_t)nsel * 8 * 3 + (size_t)nsel * 4 + 256;
+    size_t epsbytes = (size_t)nsel * 8 * ((size_t)nvirt * (nocc + 1) + (size_t)npairs * (nocc + 2 * WB));
     CDS_CALL(cds_ws(ctx, WS_AD_TMP, (prec == CDS_PREC_BF16X3 ? nB * 4 : 0) + small + epsbytes, &tmp));
     unsigned char *tp = (unsigned char *)tmp;
     if (prec == CDS_PREC_BF16X3) {
@@ -243,82 +485,114 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
         tp += nB * 4;
     }
     double *d_omega = (double *)tp;
-    double *d_scale = d_omega + nsel;
-    double *d_sig = d_scale + nsel;                    // [nsel][2]: Sigma, Sigma'
-    int32_t *d_sel = (int32_t *)(d_sig + 2 * nsel);
-    double *epsA = (double *)(tp + small);
-    double *epsB = epsA + (size_t)nsel * nvirt * (nocc + 1);
+    double *d_obar = d_omega + nsel;
+    double *d_scale = d_obar + nsel;
+    int32_t *d_sel = (int32_t *)(d_scale + nsel);
+    double *epsA = (double *)(tp + (small + 7) / 8 * 8);
+    double *epsBi = epsA + (size_t)nsel * nvirt * (nocc + 1);
+    double *epsBv = epsBi + (size_t)nsel * npairs * nocc;
     CDS_HIP(ctx, hipMemcpyAsync(d_omega, h_omega, (size_t)nsel * 8, hipMemcpyHostToDevice, ctx->stream));
+    CDS_HIP(ctx, hipMemcpyAsync(d_obar, h_omega_bar, (size_t)nsel * 8, hipMemcpyHostToDevice, ctx->stream));
     CDS_HIP(ctx, hipMemcpyAsync(d_sel, h_sel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
 
-    // chunks of targets: G, W and W^T each nsc * nmo * nvo, at most 12 GiB each (few, large
-    // chunks: the product over nvo below has only nsc * nmo / 128 tile rows)
-    size_t per = (size_t)nmo * nvo * es;
+    // chunks of targets: G and W^T each nsc * nmo * nvo, at most 12 GiB each (few, large chunks: the
+    // product over nvo below has only nsc * nmo / 128 tile rows)
+    const size_t per = (size_t)nmo * nvo * es;
     int csz = (int)std::max<size_t>(1, ((size_t)12 << 30) / std::max<size_t>(per, 1));
     if (ctx->target_chunk > 0) csz = std::min(csz, ctx->target_chunk);
     csz = std::min(csz, (int)nsel);
-    void *G, *W;
+    // K padding of the products (their stage holds 16 FP64 or 32 FP32 k): the sum over v in S parts of
+    // vp (the tiles of Bsel_bar alone do not fill the chip: 360 of 512 workgroups for 480 orbitals,
+    // 12 targets, 930 vectors), the sum over (s, r) to kcp.  S: the fewest rounds of 512 workgroups
+    // per part, each part adding a pass over its result
+    const int64_t ks = es == 8 ? 16 : 32;
+    auto up = [&](int64_t n) { return cds_ceil_div(n, ks) * ks; };
+    int S = 1;
+    {
+        const int64_t tiles = cds_ceil_div((int64_t)csz * nmo, 128) * cds_ceil_div(nvec, 128);
+        double best = 0.0;
+        for (int c = 1; c <= 16 && (c == 1 || nvo / c >= 512); ++c) {
+            const double cost = (double)cds_ceil_div(tiles * c, 512) / c * (1.0 + 0.01 * c);
+            if (c == 1 || cost < best) {
+                best = cost;
+                S = c;
+            }
+        }
+    }
+    const int64_t vp = up(cds_ceil_div(nvo, S)), nvp = S * vp;
+    const int64_t kcp = up((int64_t)csz * nmo);
+    void *G, *WT, *BvT, *BsT, *part;
     CDS_CALL(cds_ws(ctx, WS_SG_G, (size_t)csz * per, &G));
-    CDS_CALL(cds_ws(ctx, WS_AD_G, (size_t)csz * per, &W));
-    // K-contiguous copies of the operands the two products read across K (the GEMM's fast path
-    // loads rows along K): Bvo^T [nvec][nvo], then per chunk W^T [nvo][nsc*nmo] and the chunk's
-    // Bsel^T [nvec][nsc*nmo]
-    void *BvT, *WT, *BsT;
-    CDS_CALL(cds_ws(ctx, WS_AD_T1, (size_t)nvec * nvo * es, &BvT));
-    CDS_CALL(cds_ws(ctx, WS_AD_T2, (size_t)csz * per, &WT));
-    CDS_CALL(cds_ws(ctx, WS_AD_T3, (size_t)nvec * csz * nmo * es, &BsT));
-    CDS_CALL(cds_transpose(ctx, (int)es, nvo, nvec, Bv, ldk, BvT, nvo));
+    CDS_CALL(cds_ws(ctx, WS_AD_G, (size_t)nvp * kcp * es, &WT));
+    CDS_CALL(cds_ws(ctx, WS_AD_T1, (size_t)nvec * nvp * es, &BvT));                 // Bvo^T
+    CDS_CALL(cds_ws(ctx, WS_AD_T2, (size_t)S * csz * nmo * nvec * es, &part));      // Bsel_bar's parts
+    CDS_CALL(cds_ws(ctx, WS_AD_T3, (size_t)nvec * kcp * es, &BsT));                 // the chunk's scaled Bsel^T
+    CDS_CALL(cds_transpose(ctx, (int)es, nvo, nvec, Bv, ldk, BvT, nvp));
     for (int s0 = 0; s0 < nsel; s0 += csz) {
         const int nsc = std::min(csz, nsel - s0);
+        const int64_t kc = (int64_t)nsc * nmo, kp = up(kc);
         CDS_CALL(cds_contract_internal(ctx, prec, nvec, ldk, nmo, nocc, nsel, Bsel, Bvo, s0, nsc, G));
-        // P_s = 1 / (1 - Sigma'(w*_s)) from the same integrals, then the weights' scale
-        CDS_CALL(cds_sigma_from_g_internal(ctx, prec, nmo, nocc, nsc, G, eps, d_omega + s0, d_sig + 2 * s0));
-        CDS_HIP(ctx, hipMemcpyAsync(out.data() + 2 * s0, d_sig + 2 * s0, (size_t)nsc * 2 * 8, hipMemcpyDeviceToHost,
-                                    ctx->stream));
-        CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        for (int s = s0; s < s0 + nsc; ++s) hscale[s] = h_omega_bar[s] / (1.0 - out[2 * s + 1]);
-        CDS_HIP(ctx, hipMemcpyAsync(d_scale + s0, hscale.data() + s0, (size_t)nsc * 8, hipMemcpyHostToDevice,
-                                    ctx->stream));
-        CDS_CALL(cds_grad_epilogue_internal(ctx, prec, nmo, nocc, nsc, G, eps, d_omega + s0, d_scale + s0, W,
-                                            epsA + (size_t)s0 * nvirt * (nocc + 1),
-                                            epsB + (size_t)s0 * nvirt * (nocc + 1)));
-        // Bsel_bar[s0..] = W Bvo :  (nsc*nmo) x nvec, reduction over nvo
+        WArgs w = {};
+        w.G = G;
+        w.WT = WT;
+        w.nmo = nmo;
+        w.nocc = nocc;
+        w.nvirt = nvirt;
+        w.nvo = nvo;
+        w.ldw = kp;
+        w.eps = eps;
+        w.omega = d_omega + s0;
+        w.epsA = epsA + (size_t)s0 * nvirt * (nocc + 1);
+        w.epsBi = epsBi + (size_t)s0 * npairs * nocc;
+        w.epsBv = epsBv + (size_t)s0 * npairs * 2 * WB;
+        w.npairs = npairs;
+        const dim3 ga((unsigned)nvirt, (unsigned)nsc), gb((unsigned)npairs, (unsigned)nsc);
+        if (es == 8) {
+            hipLaunchKernelGGL(weights_a_kernel<double>, ga, dim3(256), 0, ctx->stream, w);
+            hipLaunchKernelGGL(weights_b_kernel<double>, gb, dim3(256), 0, ctx->stream, w);
+            CDS_CALL(zero_cols(ctx, (double *)WT, nvo, kp, kc));
+            CDS_CALL(zero_cols(ctx, (double *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
+        } else {
+            hipLaunchKernelGGL(weights_a_kernel<float>, ga, dim3(256), 0, ctx->stream, w);
+            hipLaunchKernelGGL(weights_b_kernel<float>, gb, dim3(256), 0, ctx->stream, w);
+            CDS_CALL(zero_cols(ctx, (float *)WT, nvo, kp, kc));
+            CDS_CALL(zero_cols(ctx, (float *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
+        }
+        hipLaunchKernelGGL(scale_kernel, dim3((unsigned)nsc), dim3(256), 0, ctx->stream, (const double *)w.epsA,
+                           (const double *)w.epsBi, nocc, nvirt, npairs, (const double *)d_obar + s0, d_scale + s0);
+        CDS_LAUNCHED(ctx);
+        // Bsel_bar[s0..] = scale W Bvo :  (nsc*nmo) x nvec, reduction over nvo in S parts
         GemmDesc d1 = {};
-        d1.M = (int64_t)nsc * nmo; d1.N = nvec; d1.K = nvo; d1.batch = 1;
-        d1.A = W; d1.sAm = nvo; d1.sAk = 1;
-        d1.B = BvT; d1.sBk = 1; d1.sBn = nvo;
-        d1.C = (unsigned char *)Bsel_bar + (size_t)s0 * nmo * ldk * es; d1.sCm = ldk; d1.sCn = 1;
+        d1.M = kc; d1.N = nvec; d1.K = vp; d1.batch = S; d1.ka = 1;
+        d1.A = WT; d1.sAm = 1; d1.sAk = kp; d1.sAb = vp * kp;
+        d1.B = BvT; d1.sBk = 1; d1.sBn = nvp; d1.sBb = vp;
+        d1.C = part; d1.sCm = nvec; d1.sCn = 1; d1.sCb = kc * nvec;
         d1.alpha = 1.0; d1.beta = 0.0;
         CDS_CALL(cds_gemm_ex(ctx, gprec, d1, nullptr, nullptr));
-        // Bvo_bar += W^T Bsel[s0..] : nvo x nvec, reduction over nsc*nmo
-        const int64_t kc = (int64_t)nsc * nmo;
-        CDS_CALL(cds_transpose(ctx, (int)es, kc, nvo, W, nvo, WT, kc));
+        const dim3 gs((unsigned)cds_ceil_div(kc * ldk, 256));
+        void *out = (unsigned char *)Bsel_bar + (size_t)s0 * nmo * ldk * es;
+        if (es == 8)
+            hipLaunchKernelGGL(sum_scaled_kernel<double>, gs, dim3(256), 0, ctx->stream, (const double *)part, S, kc, nvec,
+                               (int64_t)nmo, (const double *)d_scale + s0, (double *)out, ldk);
+        else
+            hipLaunchKernelGGL(sum_scaled_kernel<float>, gs, dim3(256), 0, ctx->stream, (const float *)part, S, kc, nvec,
+                               (int64_t)nmo, (const double *)d_scale + s0, (float *)out, ldk);
+        CDS_LAUNCHED(ctx);
+        // Bvo_bar += W^T (scale Bsel[s0..]) : nvo x nvec, reduction over nsc*nmo
         CDS_CALL(cds_transpose(ctx, (int)es, kc, nvec, (const unsigned char *)Bs + (size_t)s0 * nmo * ldk * es, ldk,
-                               BsT, kc));
+                               BsT, kp, d_scale + s0, nmo));
         GemmDesc d2 = {};
-        d2.M = nvo; d2.N = nvec; d2.K = kc; d2.batch = 1;
-        d2.A = WT; d2.sAm = kc; d2.sAk = 1;
-        d2.B = BsT; d2.sBk = 1; d2.sBn = kc;
+        d2.M = nvo; d2.N = nvec; d2.K = kp; d2.batch = 1;
+        d2.A = WT; d2.sAm = kp; d2.sAk = 1;
+        d2.B = BsT; d2.sBk = 1; d2.sBn = kp;
         d2.C = Bvo_bar; d2.sCm = ldk; d2.sCn = 1;
         d2.alpha = 1.0; d2.beta = s0 == 0 ? 0.0 : 1.0;
         CDS_CALL(cds_gemm_ex(ctx, gprec, d2, nullptr, nullptr));
     }
-    if (ldk > nvec) {
-        if (gprec == CDS_PREC_FP64) {
-            hipLaunchKernelGGL(zero_cols_kernel<double>, dim3((unsigned)cds_ceil_div(nselr * (ldk - nvec), 256)),
-                               dim3(256), 0, ctx->stream, (double *)Bsel_bar, nselr, ldk, nvec);
-            hipLaunchKernelGGL(zero_cols_kernel<double>, dim3((unsigned)cds_ceil_div(nvo * (ldk - nvec), 256)),
-                               dim3(256), 0, ctx->stream, (double *)Bvo_bar, nvo, ldk, nvec);
-        } else {
-            hipLaunchKernelGGL(zero_cols_kernel<float>, dim3((unsigned)cds_ceil_div(nselr * (ldk - nvec), 256)),
-                               dim3(256), 0, ctx->stream, (float *)Bsel_bar, nselr, ldk, nvec);
-            hipLaunchKernelGGL(zero_cols_kernel<float>, dim3((unsigned)cds_ceil_div(nvo * (ldk - nvec), 256)),
-                               dim3(256), 0, ctx->stream, (float *)Bvo_bar, nvo, ldk, nvec);
-        }
-        CDS_LAUNCHED(ctx);
-    }
-    hipLaunchKernelGGL(eps_bar_kernel, dim3((unsigned)nmo), dim3(256), 0, ctx->stream,
-                       (const double *)epsA, (const double *)epsB, nsel, nocc, nvirt, (const int32_t *)d_sel,
+    if (es == 8) CDS_CALL(zero_cols(ctx, (double *)Bvo_bar, nvo, ldk, nvec));
+    else CDS_CALL(zero_cols(ctx, (float *)Bvo_bar, nvo, ldk, nvec));
+    hipLaunchKernelGGL(eps_bar_kernel, dim3((unsigned)nmo), dim3(256), 0, ctx->stream, (const double *)epsA,
+                       (const double *)epsBi, (const double *)epsBv, nsel, nocc, nvirt, npairs, (const int32_t *)d_sel,
                        (const double *)d_scale, eps_bar);
     CDS_LAUNCHED(ctx);
     CDS_CALL(cds_timer_stop(ctx, &tall, &ctx->stats.t_adjoint_ms));

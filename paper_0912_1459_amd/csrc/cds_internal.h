@@ -199,14 +199,17 @@ struct GemmDesc {
                              // row block m / tri are not formed (the lower block triangle)
     int64_t bacc;            // bacc > 1: each run of bacc batch entries is summed, in order, into one
                              // C (C + run * sCb); K-contiguous, 16-byte aligned FP64 / FP32 operands
+    int ka;                  // 1: A has sAm 1 and rows of k (sAk, a multiple of 16 bytes, M rounded up
+                             // to 16 bytes readable); K a multiple of 16 (FP64) or 32 (FP32)
 };
 // prec of A/B/C: FP64 -> double, FP32/BF16X3 -> float storage
 int cds_gemm(cds_ctx *ctx, int prec, const GemmDesc &d);
 // Alo/Blo: lo planes of BF16X3 operands (hi planes at d.A / d.B); NULL otherwise
 int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, const void *Blo);
-// out[c*ldo + r] = in[r*ldi + c] for r < rows, c < cols; elements of es bytes (4 or 8)
+// out[c*ldo + r] = in[r*ldi + c] (times scale[r / per], if given) for r < rows, 0 for rows <= r < ldo,
+// c < cols; elements of es bytes (4 or 8)
 int cds_transpose(cds_ctx *ctx, int es, int64_t rows, int64_t cols, const void *in, int64_t ldi, void *out,
-                  int64_t ldo);
+                  int64_t ldo, const double *scale = nullptr, int64_t per = 1);
 
 // Fused self-energy contraction (sigma_fused.hip): the integrals of Eq. (SE) are formed by MFMA
 // products and reduced over the energy denominators in one kernel, task by task (a task = one

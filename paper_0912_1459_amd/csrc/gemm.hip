@@ -47,6 +47,7 @@ struct Args {
     int64_t nblk, sCblk;           // GemmDesc::nblk, sCblk
     int64_t tri;                   // GemmDesc::tri
     int64_t bacc;                  // GemmDesc::bacc (at least 1)
+    int ka;                        // GemmDesc::ka
 };
 
 // element offset of C column n within a row
@@ -497,7 +498,12 @@ bool fast_ok(const void *p, int64_t srow, int64_t sk, int64_t K, int kb, size_t 
 // FP32 went through gemm_kernel's registers before: 240 orbitals, 1662 vectors, the transform's
 // products 833 us, here 630 us (short K: the first loads of a tile are not hidden).
 constexpr int GD_NT = 512, GD_SLICE = 16384, GD_STAGE = 2 * GD_SLICE;
-template <int PREC>
+
+// KA: A is stored with m contiguous (GemmDesc::ka).  Its stage is the 16 (FP64) or 32 (FP32) k rows
+// of 128 m; the fragments are read element by element, 16 lanes along m, with the 16-m blocks of a
+// row permuted by k / 2 (k / 4) & 7 so that the lane groups' rows fall into distinct banks.  The
+// lanes hold the same k as with a K-contiguous A.
+template <int PREC, bool KA>
 __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per, unsigned gx, unsigned gy, int th, int tw)
 {
     typedef typename Tr<PREC>::E E;
@@ -523,10 +529,20 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
     const unsigned char *mat = sl ? a.B : a.A;
     const int64_t srow = sl ? a.sBn : a.sAm, sb = sl ? a.sBb : a.sAb;
     const int64_t nrows = sl ? a.N : a.M, r0g = sl ? n0 : m0;
-    const int nld = max(0, min(4, ((sl ? tw : th) - 32 * (wave & 3)) / 8));   // loads that reach into the tile
+    // loads that reach into the tile
+    const int nld = KA && !sl ? 4 : max(0, min(4, ((sl ? tw : th) - 32 * (wave & 3)) / 8));
+    const int64_t kstep = KA && !sl ? Tr<PREC>::KB * a.sAk * ES : 128;     // bytes from a stage to the next
     const unsigned char *src[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+        if (KA && !sl) {
+            constexpr int CPR = 8 * ES;                     // 16-byte chunks of a k row
+            const int k = (4 * (wave & 3) + q) * (64 / CPR) + lane / CPR, c = lane % CPR;
+            const int lc = c ^ (((F64 ? k >> 1 : k >> 2) & 7) * (CPR / 8));
+            const int64_t m = min(m0 + lc * (16 / ES), (a.M - 1) / (16 / ES) * (16 / ES));
+            src[q] = mat + (batch * sb + k * a.sAk + m) * ES;
+            continue;
+        }
         const int rr = 8 * (4 * (wave & 3) + q) + lrow;
         const int64_t row = min(r0g + rr, nrows - 1);
         src[q] = mat + ((batch * sb + row * srow) * ES) + ((pc ^ (rr & 7)) * 16);
@@ -537,10 +553,10 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             if (q < nld) cds_lds_dma16(src[q] + koff, dst + q * 1024);
-        koff += 128;
+        koff += kstep;
         if (--left == 0) {
             left = nb;
-            koff += sb * ES - nb * 128;
+            koff += sb * ES - nb * kstep;
         }
     };
 
@@ -576,7 +592,20 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
                 const int co = fo + (((g + 4 * h) ^ sw) * 16);
                 V fa[NA], fb[NJ];
 #pragma unroll
-                for (int i = 0; i < NA; ++i) fa[i] = *reinterpret_cast<const V *>(cur + (rb0 + i) * 2048 + co);
+                for (int i = 0; i < NA; ++i) {
+                    if constexpr (KA) {
+                        const int lc = g + 4 * h;
+                        const unsigned char *p = cur + lc * 2048 + ((rb0 + i) ^ lc) * (16 * ES) + r16 * ES;
+                        fa[i].x = *reinterpret_cast<const E *>(p);
+                        fa[i].y = *reinterpret_cast<const E *>(p + 128 * ES);
+                        if constexpr (!F64) {
+                            fa[i].z = *reinterpret_cast<const E *>(p + 256 * ES);
+                            fa[i].w = *reinterpret_cast<const E *>(p + 384 * ES);
+                        }
+                    } else {
+                        fa[i] = *reinterpret_cast<const V *>(cur + (rb0 + i) * 2048 + co);
+                    }
+                }
 #pragma unroll
                 for (int j = 0; j < NJ; ++j)
                     fb[j] = *reinterpret_cast<const V *>(cur + GD_SLICE + (cb0 + j) * 2048 + co);
@@ -637,8 +666,11 @@ int launch(cds_ctx *ctx, Args &a)
     if (PREC == CDS_PREC_BF16X3 && (!a.fastA || !a.fastB))
         return cds_fail(ctx, CDS_EINVAL, "bf16x3 GEMM needs K-contiguous 16-byte aligned operands");
     if (a.M <= 0 || a.N <= 0 || a.batch <= 0) return CDS_OK;
-    if (a.bacc > 1 && (PREC == CDS_PREC_BF16X3 || !a.fastA || !a.fastB))
-        return cds_fail(ctx, CDS_EINVAL, "GEMM over several batch entries needs K-contiguous FP64 or FP32 operands");
+    if (a.ka)
+        a.fastA = PREC != CDS_PREC_BF16X3 && a.sAm == 1 && a.K % KB == 0 && cds_aligned(a.A, 16) &&
+                  (a.sAk * (int64_t)sizeof(E)) % 16 == 0;
+    if ((a.bacc > 1 || a.ka) && (PREC == CDS_PREC_BF16X3 || !a.fastA || !a.fastB))
+        return cds_fail(ctx, CDS_EINVAL, "GEMM over several batch entries or an m-contiguous A needs aligned FP64 or FP32 operands");
     int64_t gx = cds_ceil_div(a.N, BN), gy = cds_ceil_div(a.M, BM);
     if (gy > 65535 || a.batch > 65535)
         return cds_fail(ctx, CDS_EINVAL, "GEMM grid too large (%lld x %lld x %lld)", (long long)gx,
@@ -667,12 +699,13 @@ int launch(cds_ctx *ctx, Args &a)
             };
             const int th = edge(a.M, gy), tw = edge(a.N, gx);
             const unsigned per = (unsigned)count_tiles(a.tri, (unsigned)gx, (unsigned)gy, th, tw);
-            hipLaunchKernelGGL(gemm_dma_kernel<PREC>, dim3(per * (unsigned)cds_ceil_div(a.batch, a.bacc)), dim3(GD_NT), 0, ctx->stream, a, per,
+            const auto kern = a.ka ? gemm_dma_kernel<PREC, true> : gemm_dma_kernel<PREC, false>;
+            hipLaunchKernelGGL(kern, dim3(per * (unsigned)cds_ceil_div(a.batch, a.bacc)), dim3(GD_NT), 0, ctx->stream, a, per,
                                (unsigned)gx, (unsigned)gy, th, tw);
             CDS_LAUNCHED(ctx);
             return CDS_OK;
         }
-        if (a.bacc > 1) return cds_fail(ctx, CDS_EINVAL, "GEMM over several batch entries: unaligned or too many");
+        if (a.bacc > 1 || a.ka) return cds_fail(ctx, CDS_EINVAL, "GEMM over several batch entries: unaligned or too many");
     }
     size_t lds = (size_t)2 * Tr<PREC>::PLANES * BM * PITCH;
     hipLaunchKernelGGL(gemm_kernel<PREC>, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.batch), dim3(NT),
@@ -684,10 +717,12 @@ int launch(cds_ctx *ctx, Args &a)
 }  // namespace
 
 namespace {
-// 32 x 32 tiles through LDS (33-word pitch), every load of a thread in flight before its stores
+// 32 x 32 tiles through LDS (33-word pitch), every load of a thread in flight before its stores;
+// rows past `rows` up to ldo read as 0
 template <typename T>
 __global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ in, int64_t ldi, T *__restrict__ out,
-                                                        int64_t ldo, int64_t rows, int64_t cols)
+                                                        int64_t ldo, int64_t rows, int64_t cols,
+                                                        const double *__restrict__ scale, int64_t per)
 {
     __shared__ T t[32][33];
     const int64_t r0 = (int64_t)blockIdx.y * 32, c0 = (int64_t)blockIdx.x * 32;
@@ -697,6 +732,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ in
     for (int u = 0; u < 4; ++u) {
         const int64_t r = r0 + ty + 8 * u, c = c0 + tx;
         v[u] = (r < rows && c < cols) ? in[r * ldi + c] : T(0);
+        if (scale && r < rows) v[u] = (T)(scale[r / per] * (double)v[u]);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) t[ty + 8 * u][tx] = v[u];
@@ -704,25 +740,25 @@ __global__ __launch_bounds__(256) void transpose_kernel(const T *__restrict__ in
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         const int64_t c = c0 + ty + 8 * u, r = r0 + tx;
-        if (r < rows && c < cols) out[c * ldo + r] = t[tx][ty + 8 * u];
+        if (r < ldo && c < cols) out[c * ldo + r] = t[tx][ty + 8 * u];
     }
 }
 }  // namespace
 
 int cds_transpose(cds_ctx *ctx, int es, int64_t rows, int64_t cols, const void *in, int64_t ldi, void *out,
-                  int64_t ldo)
+                  int64_t ldo, const double *scale, int64_t per)
 {
     CDS_REQUIRE(ctx, es == 4 || es == 8, "transpose: element size %d", es);
     CDS_REQUIRE(ctx, rows >= 0 && cols >= 0 && ldi >= cols && ldo >= rows, "transpose: bad shape");
     if (rows == 0 || cols == 0) return CDS_OK;
-    CDS_REQUIRE(ctx, cds_ceil_div(rows, 32) <= 65535, "transpose: too many rows");
-    const dim3 g((unsigned)cds_ceil_div(cols, 32), (unsigned)cds_ceil_div(rows, 32));
+    CDS_REQUIRE(ctx, cds_ceil_div(ldo, 32) <= 65535, "transpose: too many rows");
+    const dim3 g((unsigned)cds_ceil_div(cols, 32), (unsigned)cds_ceil_div(ldo, 32));
     if (es == 8)
         hipLaunchKernelGGL(transpose_kernel<double>, g, dim3(256), 0, ctx->stream, (const double *)in, ldi,
-                           (double *)out, ldo, rows, cols);
+                           (double *)out, ldo, rows, cols, scale, per);
     else
         hipLaunchKernelGGL(transpose_kernel<float>, g, dim3(256), 0, ctx->stream, (const float *)in, ldi,
-                           (float *)out, ldo, rows, cols);
+                           (float *)out, ldo, rows, cols, scale, per);
     CDS_LAUNCHED(ctx);
     return CDS_OK;
 }
@@ -758,6 +794,7 @@ int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, cons
     a.sCblk = d.sCblk;
     a.tri = d.tri;
     a.bacc = d.bacc > 1 ? d.bacc : 1;
+    a.ka = d.ka;
     if (a.nblk && a.N > 0x7fffffff) return cds_fail(ctx, CDS_EINVAL, "GEMM columns in blocks: N too large");
     if (prec == CDS_PREC_FP64) return launch<CDS_PREC_FP64>(ctx, a);
     if (prec == CDS_PREC_FP32) return launch<CDS_PREC_FP32>(ctx, a);

@@ -27,7 +27,7 @@ namespace {
 constexpr int EP_NT = 256;
 constexpr int TMAX = 16;
 
-enum EpMode { EP_SIGMA = 0, EP_RESIDUE = 1, EP_GRAD = 2 };
+enum EpMode { EP_SIGMA = 0, EP_RESIDUE = 1 };
 
 struct EpArgs {
     const void *G;          // integrals of this chunk: [sc][nmo][nvo] (double or float)
@@ -40,11 +40,6 @@ struct EpArgs {
     int nblkA, nblkB;       // blocks per target in part A / part B
     void *R;                // residues [sc][nres] (RESIDUE mode)
     int64_t nres, offB;     // residues per target; start of part B within a target
-    // gradient mode
-    const double *gscale;   // [sc] omega_bar * P per target
-    void *W;                // weights dSigma/dG scaled, same layout as G
-    double *epsA;           // [sc][nvirt][nocc + 1] part A energy partials
-    double *epsB;           // [sc][nvirt][nocc + 1] part B energy partials
 };
 
 template <typename GT>
@@ -240,105 +235,6 @@ __global__ __launch_bounds__(EP_NT) void pair_b_kernel(EpArgs e)
                 if (threadIdx.x == 0 && t < e.T) dst[t * 2 + c] = v;
             }
     }
-}
-
-// Gradient weights, part A (block per (a, s)): W = gscale (4 x_ij - 2 x_ji) / d for every
-// ordered element; thread i owns e-bar_i (row sums), the block sums e-bar_a.
-template <typename GT>
-__global__ __launch_bounds__(EP_NT) void grad_a_kernel(EpArgs e)
-{
-    __shared__ double sh[EP_NT / 64];
-    __shared__ double eo[1024];
-    const int a = blockIdx.x, s = blockIdx.y, nocc = e.nocc;
-    for (int i = threadIdx.x; i < nocc; i += EP_NT) eo[i] = e.eps[i];
-    __syncthreads();
-    const double ea = e.eps[nocc + a];
-    const int64_t gbase = (int64_t)s * e.nmo * e.nvo + (int64_t)a * nocc;
-    const double w0 = e.omega[s];
-    const double gs = e.gscale[s];
-    double sa = 0.0;
-    for (int i = threadIdx.x; i < nocc; i += EP_NT) {
-        double si = 0.0;
-        // JU columns at a time, their loads in flight before the first use (same order of terms)
-        constexpr int JU = 4;
-        for (int j0 = 0; j0 < nocc; j0 += JU) {
-            double xv[JU], xtv[JU];
-#pragma unroll
-            for (int u = 0; u < JU; ++u) {
-                const int j = j0 + u < nocc ? j0 + u : nocc - 1;
-                xv[u] = ld<GT>(e.G, gbase + (int64_t)i * e.nvo + j);
-                xtv[u] = ld<GT>(e.G, gbase + (int64_t)j * e.nvo + i);
-            }
-#pragma unroll
-            for (int u = 0; u < JU; ++u) {
-                const int j = j0 + u;
-                if (j >= nocc) break;
-                const double x = xv[u], xt = xtv[u];
-                double d = w0 + ea - eo[i] - eo[j];
-                double uu = (2.0 * x - xt) * x, ut = (2.0 * xt - x) * xt;
-                double id = 1.0 / d;
-                ((GT *)e.W)[gbase + (int64_t)i * e.nvo + j] = (GT)(gs * (4.0 * x - 2.0 * xt) * id);
-                si += (uu + ut) * id * id;     // d symmetric in (i, j)
-                sa -= uu * id * id;
-            }
-        }
-        e.epsA[((int64_t)s * e.nvirt + a) * (nocc + 1) + i] = gs * si;
-    }
-    sa = block_sum<EP_NT>(sa, sh);
-    if (threadIdx.x == 0) e.epsA[((int64_t)s * e.nvirt + a) * (nocc + 1) + nocc] = gs * sa;
-}
-
-// Gradient weights, part B (block per (a, s)) over all (b, i); per-i sums are owned by
-// fixed threads (i = tid % nocc) and combined in a fixed order.
-template <typename GT>
-__global__ __launch_bounds__(EP_NT) void grad_b_kernel(EpArgs e)
-{
-    __shared__ double sh[EP_NT / 64];
-    __shared__ double eo[1024];
-    __shared__ double acc_i[1024];
-    const int s = blockIdx.y, nocc = e.nocc, nvirt = e.nvirt, a = blockIdx.x;
-    for (int i = threadIdx.x; i < nocc; i += EP_NT) {
-        eo[i] = e.eps[i];
-        acc_i[i] = 0.0;
-    }
-    __syncthreads();
-    const double *ev = e.eps + nocc;
-    const int64_t gs0 = (int64_t)s * e.nmo * e.nvo;
-    const double ea = ev[a];
-    const int64_t base_a = gs0 + (int64_t)(nocc + a) * e.nvo;
-    const double gsc = e.gscale[s];
-    const double w0 = e.omega[s];
-    const int per = EP_NT / nocc > 0 ? EP_NT / nocc : 1;
-    const int i0 = threadIdx.x % nocc, bsub = threadIdx.x / nocc;
-    double sa = 0.0, si = 0.0;
-    if (bsub < per) {
-        for (int i = i0; i < nocc; i += (nocc > EP_NT ? EP_NT : nocc)) {
-            double sii = 0.0;
-            for (int b = bsub; b < nvirt; b += per) {
-                double y = ld<GT>(e.G, base_a + (int64_t)b * nocc + i);
-                double yt = ld<GT>(e.G, gs0 + (int64_t)(nocc + b) * e.nvo + (int64_t)a * nocc + i);
-                double d = w0 + eo[i] - ea - ev[b];
-                double id = 1.0 / d;
-                double u = (2.0 * y - yt) * y, ut = (2.0 * yt - y) * yt;
-                ((GT *)e.W)[base_a + (int64_t)b * nocc + i] = (GT)(gsc * (4.0 * y - 2.0 * yt) * id);
-                sii -= u * id * id;           // role i of element (a, b, i)
-                sa += (u + ut) * id * id;     // roles a of (a,b,i) and b of (b,a,i)
-            }
-            si = sii;
-            if (nocc > EP_NT) e.epsB[((int64_t)s * nvirt + a) * (nocc + 1) + i] = gsc * si;
-        }
-    }
-    if (nocc <= EP_NT) {
-        for (int k = 0; k < per; ++k) {
-            __syncthreads();
-            if (bsub == k && bsub < per) acc_i[i0] += si;
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < nocc; i += EP_NT)
-            e.epsB[((int64_t)s * nvirt + a) * (nocc + 1) + i] = gsc * acc_i[i];
-    }
-    sa = block_sum<EP_NT>(sa, sh);
-    if (threadIdx.x == 0) e.epsB[((int64_t)s * nvirt + a) * (nocc + 1) + nocc] = gsc * sa;
 }
 
 // Newton sweep over stored residues: Sigma(w) = sum R / (w - pole), one energy per target.
@@ -668,18 +564,6 @@ int launch_epilogue_t(cds_ctx *ctx, const SigmaShape &sh, EpArgs &e)
 template <int MODE>
 int launch_epilogue(cds_ctx *ctx, const SigmaShape &sh, EpArgs &e, bool fp64)
 {
-    if (MODE == EP_GRAD) {
-        dim3 g((unsigned)sh.nvirt, (unsigned)e.nsc);
-        if (fp64) {
-            hipLaunchKernelGGL(grad_a_kernel<double>, g, dim3(EP_NT), 0, ctx->stream, e);
-            hipLaunchKernelGGL(grad_b_kernel<double>, g, dim3(EP_NT), 0, ctx->stream, e);
-        } else {
-            hipLaunchKernelGGL(grad_a_kernel<float>, g, dim3(EP_NT), 0, ctx->stream, e);
-            hipLaunchKernelGGL(grad_b_kernel<float>, g, dim3(EP_NT), 0, ctx->stream, e);
-        }
-        CDS_LAUNCHED(ctx);
-        return CDS_OK;
-    }
     return fp64 ? launch_epilogue_t<double, MODE>(ctx, sh, e) : launch_epilogue_t<float, MODE>(ctx, sh, e);
 }
 
@@ -781,60 +665,6 @@ int cds_contract_internal(cds_ctx *ctx, int prec, int64_t nvec, int64_t ldk, int
     SigmaShape sh = {prec, nvec, ldk, nmo, nocc, nmo - nocc, nsel,
                      (int64_t)(nmo - nocc) * nocc, (int64_t)nsel * nmo};
     return contract_chunk(ctx, sh, Bsel, Bvo, s0, nsc, G);
-}
-
-// Sigma and Sigma' of a chunk's targets at one energy each (device d_omega[nsc]) from its formed
-// integrals G -> device d_out[nsc][2] (adjoint: the pole strengths at the converged energies)
-int cds_sigma_from_g_internal(cds_ctx *ctx, int prec, int nmo, int nocc, int nsc, const void *G,
-                              const double *eps, const double *d_omega, double *d_out)
-{
-    SigmaShape sh = {prec, 0, 0, nmo, nocc, nmo - nocc, nsc,
-                     (int64_t)(nmo - nocc) * nocc, (int64_t)nsc * nmo};
-    const int nblk = sh.nvirt + (sh.nvirt + 1) / 2;
-    void *part;
-    CDS_CALL(cds_ws(ctx, WS_SG_PART, (size_t)nsc * nblk * 2 * 8, &part));
-    EpArgs e = {};
-    e.G = G;
-    e.nmo = nmo;
-    e.nocc = nocc;
-    e.nvirt = sh.nvirt;
-    e.nsc = nsc;
-    e.nvo = sh.nvo;
-    e.eps = eps;
-    e.omega = d_omega;
-    e.T = 1;
-    e.part = (double *)part;
-    e.nblkA = sh.nvirt;
-    e.nblkB = (sh.nvirt + 1) / 2;
-    CDS_CALL(launch_epilogue<EP_SIGMA>(ctx, sh, e, prec == CDS_PREC_FP64));
-    hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)(nsc * 2)), dim3(256), 0, ctx->stream,
-                       (const double *)part, nsc, nblk, 1, d_out);
-    CDS_LAUNCHED(ctx);
-    return CDS_OK;
-}
-
-// gradient-weight epilogue for a chunk (adjoint)
-int cds_grad_epilogue_internal(cds_ctx *ctx, int prec, int nmo, int nocc, int nsc, const void *G,
-                               const double *eps, const double *d_omega, const double *d_gscale,
-                               void *W, double *epsA, double *epsB)
-{
-    SigmaShape sh = {prec, 0, 0, nmo, nocc, nmo - nocc, nsc,
-                     (int64_t)(nmo - nocc) * nocc, (int64_t)nsc * nmo};
-    EpArgs e = {};
-    e.G = G;
-    e.nmo = nmo;
-    e.nocc = nocc;
-    e.nvirt = nmo - nocc;
-    e.nsc = nsc;
-    e.nvo = sh.nvo;
-    e.eps = eps;
-    e.omega = d_omega;
-    e.T = 1;
-    e.gscale = d_gscale;
-    e.W = W;
-    e.epsA = epsA;
-    e.epsB = epsB;
-    return launch_epilogue<EP_GRAD>(ctx, sh, e, prec == CDS_PREC_FP64);
 }
 
 extern "C" int cds_set_target_chunk(cds_ctx *ctx, int32_t n)
