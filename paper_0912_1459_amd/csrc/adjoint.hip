@@ -422,24 +422,6 @@ __global__ void sum_parts_kernel(const double *__restrict__ part, int nb, int64_
     out[e] = acc;
 }
 
-// Lu[kb][mu][nu] (nu padded to np_) in FP64
-__global__ void unpack64_kernel(const double *__restrict__ L, int64_t ldl, int64_t k0, int nkb, int nbf,
-                                int np_, double *__restrict__ out)
-{
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t per = (int64_t)nbf * np_;
-    if (t >= per * nkb) return;
-    int kb = (int)(t / per);
-    int64_t rem = t - (int64_t)kb * per;
-    int mu = (int)(rem / np_), nu = (int)(rem - (int64_t)mu * np_);
-    double v = 0.0;
-    if (nu < nbf) {
-        int a = mu < nu ? mu : nu, b = mu < nu ? nu : mu;
-        v = L[(k0 + kb) * ldl + (int64_t)b * (b + 1) / 2 + a];
-    }
-    out[t] = v;
-}
-
 }  // namespace
 
 extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, int32_t nmo,
@@ -618,7 +600,7 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
     CDS_CALL(cds_timer_start(ctx, &tall));
     const int nvirt = nmo - nocc;
     auto up16 = [](int64_t n) { return (int)(cds_ceil_div(n, 16) * 16); };
-    const int np_ = up16(nbf);
+    const int np_ = (int)(cds_ceil_div(nbf, 32) * 32);
     const int xo = up16(nocc), selp = up16(nsel), xp = xo + selp;    // rows x: occupied, then targets
     const int ap = up16(nvirt), cp = ap + up16(nocc);                // columns: virtual, then occupied
     // vectors per batch: the largest of the batch's arrays stays below 1 GiB
@@ -684,10 +666,7 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
     };
     for (int64_t k0 = 0; k0 < nvec; k0 += kb) {
         const int nkb = (int)std::min<int64_t>(kb, nvec - k0);
-        const int64_t n1 = (int64_t)nkb * nbf * np_;
-        hipLaunchKernelGGL(unpack64_kernel, dim3((unsigned)cds_ceil_div(n1, 256)), dim3(256), 0, ctx->stream, L,
-                           ldl, k0, nkb, nbf, np_, Lu);
-        CDS_LAUNCHED(ctx);
+        CDS_CALL(cds_unpack64(ctx, L, ldl, k0, nkb, nbf, np_, Lu));
         // T[mu][kb][x] = sum_nu L^K[mu][nu] CX[x][nu]
         GemmDesc gt = {};
         gt.M = nbf; gt.N = xp; gt.K = np_; gt.batch = nkb;

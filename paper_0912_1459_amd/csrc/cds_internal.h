@@ -211,6 +211,9 @@ int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, cons
 int cds_transpose(cds_ctx *ctx, int es, int64_t rows, int64_t cols, const void *in, int64_t ldi, void *out,
                   int64_t ldo, const double *scale = nullptr, int64_t per = 1);
 
+// out[kb][mu][nu] = L^{k0+kb}_{mu nu}, 0 for nbf <= nu < np_ (np_ a multiple of 32), kb < nkb <= 65535
+int cds_unpack64(cds_ctx *ctx, const double *L, int64_t ldl, int64_t k0, int nkb, int nbf, int np_, double *out);
+
 // Fused self-energy contraction (sigma_fused.hip): the integrals of Eq. (SE) are formed by MFMA
 // products and reduced over the energy denominators in one kernel, task by task (a task = one
 // tile pair of the (qi|aj) matrix of a virtual a or the (qa|ib) matrix of an occupied i).

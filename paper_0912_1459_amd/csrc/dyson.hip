@@ -8,10 +8,9 @@
 // (d is symmetric in i, j and in a, b): element e = (a; i <= j) or (i; a <= b) carries
 //   u_s = (si|aj), v_s = (sj|ai)   resp.   u_s = (sa|ib), v_s = (sb|ia),
 // and contributes c_e (2 u_s u_t + 2 v_s v_t - u_s v_t - v_s u_t) / (w + d_e) to Sigma_st,
-// with c_e = 1/2 on the diagonal (i = j, a = b) and 1 otherwise.  sigma_pairs_kernel
-// stages chunks of elements (u, v of every selected orbital, weights for every trial
-// energy) in LDS; each thread owns two (s <= t) pairs; per-block partial sums are reduced
-// in a fixed order.
+// with c_e = 1/2 on the diagonal (i = j, a = b) and 1 otherwise: over the pairs (s <= t) and the trial
+// energies that is a product num[pair][e] weight[e][energy] summed over the elements, which
+// sigma_pairs_kernel gives to FP64 MFMA; per-block partial sums are reduced in a fixed order.
 //
 // The Dyson search (host loop of the library, like the quasi-particle Newton solve): one
 // root per selected orbital, started at e_q with u = unit vector q; at each step the
@@ -29,11 +28,14 @@ int cds_contract_internal(cds_ctx *ctx, int prec, int64_t nvec, int64_t ldk, int
 
 namespace {
 
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
 constexpr int DY_NT = 256;
 constexpr int DY_CH = 64;            // elements per chunk
-constexpr int DY_MAXSEL = 31;        // selected orbitals (<= 2 pairs per thread)
-constexpr int DY_TT = 8;             // trial energies per launch
-constexpr int DY_BLOCKS = 2048;
+constexpr int DY_P = DY_CH + 2;      // LDS row pitch: 16-byte reads of 8 rows fall into distinct banks
+constexpr int DY_MAXSEL = 31;        // selected orbitals
+constexpr int DY_TT = 16;            // trial energies per launch
+constexpr int DY_BLOCKS = 512;       // workgroups (two per CU)
 constexpr size_t DY_G_MAX = (size_t)16 << 30;
 
 __device__ __forceinline__ int64_t tri_hi(int64_t x)
@@ -45,124 +47,156 @@ __device__ __forceinline__ int64_t tri_hi(int64_t x)
     return b;
 }
 
-template <typename GT>
-__global__ __launch_bounds__(DY_NT) void sigma_pairs_kernel(const GT *__restrict__ G, int nsel, int nmo, int nocc,
-                                                           int nvirt, int64_t nvo, const double *__restrict__ eps,
-                                                           const double *__restrict__ omega, int T, int64_t nA,
-                                                           int64_t nE, int64_t cpb, double *__restrict__ part)
+// Chunks of 64 elements, taken in turn by the workgroups: part A, virtual a, an 8 x 8 tile of (i, j)
+// (IB <= JB); then part B, virtual a, 64 consecutive (b, i) of row a (chunks wholly below b = a are
+// passed over).  Both families' integrals are read in runs: u of part B 512 bytes, of part A 64
+// bytes, v at least 64 bytes (elements in the order (i <= j; a), (a <= b; i) read 8 bytes per line:
+// 894 us per launch for 16 of 240 orbitals, 120 occupied; this order and the MFMA form 490 us for twice the energies).
+// A chunk's u and v of every orbital and its weights are staged in LDS; a wave owns blocks of 16
+// pairs: lane (r, g) forms num of pair r for elements 8h + 2g and 8h + 2g + 1 (MFMA operand A) and
+// reads the same elements' weights of energy column r (operand B).  Columns: 2t Sigma, 2t + 1 Sigma'.
+// NB: pair blocks per wave (4 waves); NC: column blocks of 8 energies.
+template <typename GT, int NB, int NC>
+__global__ __launch_bounds__(DY_NT, 2) void sigma_pairs_kernel(const GT *__restrict__ G, int nsel, int nmo, int nocc,
+                                                              int nvirt, int64_t nvo, const double *__restrict__ eps,
+                                                              const double *__restrict__ omega, int T, int64_t nchA,
+                                                              int64_t nch, int nchB, double *__restrict__ part)
 {
-    // rows padded by one element: lanes of a wave read one element l of different orbitals s,
-    // which a pitch of DY_CH doubles would put in one bank
-    __shared__ double su[DY_MAXSEL][DY_CH + 1], sv[DY_MAXSEL][DY_CH + 1];
-    __shared__ double sw[DY_TT][DY_CH], swi[DY_TT][DY_CH];
-    __shared__ int64_t ou[DY_CH], ov[DY_CH];
+    extern __shared__ __align__(16) double lds[];
+    double *su = lds, *sv = su + nsel * DY_P, *sw = sv + nsel * DY_P;      // [nsel][DY_P] x 2, [16 NC][DY_P]
+    int64_t *ou = (int64_t *)(sw + 16 * NC * DY_P), *ov = ou + DY_CH;
+    double *sd = (double *)(ov + DY_CH), *sc = sd + DY_CH;
     const int npair = nsel * (nsel + 1) / 2;
     const int64_t gstride = (int64_t)nmo * nvo;
-    int ps[2], pt[2];
-    bool pok[2];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane >> 4, r16 = lane & 15;
+    // pair of this lane in each block of its wave (blocks wave, wave + 4, ...): LDS rows of s and t
+    int as[NB], at[NB];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int P = threadIdx.x + h * DY_NT;
-        pok[h] = P < npair;
-        const int t = pok[h] ? (int)tri_hi(P) : 0;
-        pt[h] = t;
-        ps[h] = pok[h] ? P - t * (t + 1) / 2 : 0;
+    for (int b = 0; b < NB; ++b) {
+        const int P = min((wave + 4 * b) * 16 + r16, npair - 1);
+        const int t = (int)tri_hi(P);
+        as[b] = (P - t * (t + 1) / 2) * DY_P + 2 * g;
+        at[b] = t * DY_P + 2 * g;
     }
-    double acc[2][DY_TT][2];
+    doublex4 acc[NB][NC];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int t = 0; t < DY_TT; ++t) acc[h][t][0] = acc[h][t][1] = 0.0;
-    const int64_t np2 = (int64_t)nocc * (nocc + 1) / 2, nv2 = (int64_t)nvirt * (nvirt + 1) / 2;
-    const int64_t c0 = (int64_t)blockIdx.x * cpb;
-    for (int64_t c = c0; c < c0 + cpb; ++c) {
-        const int64_t e0 = c * DY_CH;
-        if (e0 >= nE) break;
-        __syncthreads();
+        for (int c = 0; c < NC; ++c) acc[b][c] = doublex4{0.0, 0.0, 0.0, 0.0};
+    const int nt8 = (nocc + 7) / 8, ntri = nt8 * (nt8 + 1) / 2;
+    for (int64_t c = blockIdx.x; c < nch; c += gridDim.x) {
+        const bool partA = c < nchA;
+        int a, JB = 0, IB = 0;
+        int64_t q0 = 0;
+        if (partA) {
+            a = (int)(c / ntri);
+            const int p = (int)(c - (int64_t)a * ntri);
+            JB = (int)tri_hi(p);
+            IB = p - JB * (JB + 1) / 2;
+        } else {
+            const int64_t f = c - nchA;
+            a = (int)(f / nchB);
+            q0 = (f - (int64_t)a * nchB) * DY_CH;
+            if (q0 + DY_CH <= (int64_t)a * nocc) continue;         // wholly below b = a
+        }
+        __syncthreads();                                           // the last chunk is read
         if (threadIdx.x < DY_CH) {
             const int l = threadIdx.x;
-            const int64_t e = e0 + l;
             int64_t offu = 0, offv = 0;
             double d = 0.0, ce = 0.0;
-            if (e < nA) {
-                const int64_t a = e / np2, ij = e - a * np2;
-                const int64_t j = tri_hi(ij), i = ij - j * (j + 1) / 2;
-                offu = i * nvo + a * nocc + j;
-                offv = j * nvo + a * nocc + i;
-                d = eps[nocc + a] - eps[i] - eps[j];
-                ce = i == j ? 0.5 : 1.0;
-            } else if (e < nE) {
-                const int64_t f = e - nA;
-                const int64_t i = f / nv2, ab = f - i * nv2;
-                const int64_t b = tri_hi(ab), a = ab - b * (b + 1) / 2;
-                offu = (nocc + a) * nvo + b * nocc + i;
-                offv = (nocc + b) * nvo + a * nocc + i;
-                d = eps[i] - eps[nocc + a] - eps[nocc + b];
-                ce = a == b ? 0.5 : 1.0;
+            if (partA) {
+                const int i = IB * 8 + (l >> 3), j = JB * 8 + (l & 7);
+                if (j < nocc && i <= j) {
+                    offu = i * nvo + (int64_t)a * nocc + j;
+                    offv = j * nvo + (int64_t)a * nocc + i;
+                    d = eps[nocc + a] - eps[i] - eps[j];
+                    ce = i == j ? 0.5 : 1.0;
+                }
+            } else {
+                const int64_t q = q0 + l;
+                const int b = (int)(q / nocc), i = (int)(q - (int64_t)b * nocc);
+                if (b < nvirt && b >= a) {
+                    offu = (nocc + a) * nvo + q;
+                    offv = (int64_t)(nocc + b) * nvo + (int64_t)a * nocc + i;
+                    d = eps[i] - eps[nocc + a] - eps[nocc + b];
+                    ce = a == b ? 0.5 : 1.0;
+                }
             }
             ou[l] = offu;
             ov[l] = offv;
-#pragma unroll
-            for (int t = 0; t < DY_TT; ++t) {
-                const double inv = t < T ? 1.0 / (omega[t] + d) : 0.0;
-                sw[t][l] = ce * inv;
-                swi[t][l] = inv;
-            }
+            sd[l] = d;
+            sc[l] = ce;
         }
         __syncthreads();
         {
-            // every gathered load of a thread in flight before its LDS stores
+            // every gathered load of a thread in flight before its LDS stores; elements that do not
+            // count (weight 0) read as 0
             constexpr int QN = (DY_MAXSEL * DY_CH + DY_NT - 1) / DY_NT;
+            const int l = threadIdx.x & (DY_CH - 1), s0 = threadIdx.x / DY_CH;
+            const bool on = sc[l] != 0.0;
+            const GT *pu = G + ou[l], *pv = G + ov[l];
             double gu[QN], gv[QN];
 #pragma unroll
             for (int u = 0; u < QN; ++u) {
-                const int q = threadIdx.x + u * DY_NT;
-                const int s = q / DY_CH, l = q - s * DY_CH;
-                const bool ok = q < nsel * DY_CH && e0 + l < nE;
-                gu[u] = ok ? (double)G[s * gstride + ou[l]] : 0.0;
-                gv[u] = ok ? (double)G[s * gstride + ov[l]] : 0.0;
+                const int s = s0 + 4 * u;
+                const bool ok = on && s < nsel;
+                gu[u] = ok ? (double)pu[s * gstride] : 0.0;
+                gv[u] = ok ? (double)pv[s * gstride] : 0.0;
+            }
+            // weights: thread (l, t) of energies t = s0, s0 + 4, ...
+#pragma unroll
+            for (int t = s0; t < 8 * NC; t += 4) {
+                const double inv = on && t < T ? 1.0 / (omega[t] + sd[l]) : 0.0;
+                const double w = sc[l] * inv;
+                sw[2 * t * DY_P + l] = w;
+                sw[(2 * t + 1) * DY_P + l] = -w * inv;
             }
 #pragma unroll
             for (int u = 0; u < QN; ++u) {
-                const int q = threadIdx.x + u * DY_NT;
-                const int s = q / DY_CH, l = q - s * DY_CH;
-                if (q < nsel * DY_CH) {
-                    su[s][l] = gu[u];
-                    sv[s][l] = gv[u];
+                const int s = s0 + 4 * u;
+                if (s < nsel) {
+                    su[s * DY_P + l] = gu[u];
+                    sv[s * DY_P + l] = gv[u];
                 }
             }
         }
         __syncthreads();
+        for (int h = 0; h < DY_CH / 8; ++h) {
+            double2 w[NC];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (!pok[h]) continue;
-            const int s = ps[h], t2 = pt[h];
-            for (int l = 0; l < DY_CH; ++l) {
-                const double us = su[s][l], vs = sv[s][l], ut = su[t2][l], vt = sv[t2][l];
-                const double num = 2.0 * (us * ut + vs * vt) - us * vt - vs * ut;
+            for (int cb = 0; cb < NC; ++cb)
+                w[cb] = *reinterpret_cast<const double2 *>(sw + (16 * cb + r16) * DY_P + 2 * g + 8 * h);
 #pragma unroll
-                for (int t = 0; t < DY_TT; ++t) {
-                    const double x = num * sw[t][l];
-                    acc[h][t][0] += x;
-                    acc[h][t][1] -= x * swi[t][l];
+            for (int b = 0; b < NB; ++b) {
+                if (NB > 1 && (wave + 4 * b) * 16 >= npair) continue;
+                const double2 us = *reinterpret_cast<const double2 *>(su + as[b] + 8 * h);
+                const double2 vs = *reinterpret_cast<const double2 *>(sv + as[b] + 8 * h);
+                const double2 ut = *reinterpret_cast<const double2 *>(su + at[b] + 8 * h);
+                const double2 vt = *reinterpret_cast<const double2 *>(sv + at[b] + 8 * h);
+                const double nx = 2.0 * (us.x * ut.x + vs.x * vt.x) - us.x * vt.x - vs.x * ut.x;
+                const double ny = 2.0 * (us.y * ut.y + vs.y * vt.y) - us.y * vt.y - vs.y * ut.y;
+#pragma unroll
+                for (int cb = 0; cb < NC; ++cb) {
+                    acc[b][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(nx, w[cb].x, acc[b][cb], 0, 0, 0);
+                    acc[b][cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(ny, w[cb].y, acc[b][cb], 0, 0, 0);
                 }
             }
         }
     }
+    // lane (r16, g): column r16 of pairs 16 block + g + 4e
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (!pok[h]) continue;
-        const int P = threadIdx.x + h * DY_NT;
-        double *dst = part + ((int64_t)blockIdx.x * npair + P) * DY_TT * 2;
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int t = 0; t < DY_TT; ++t) {
-            dst[2 * t] = acc[h][t][0];
-            dst[2 * t + 1] = acc[h][t][1];
-        }
-    }
+        for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int P = (wave + 4 * b) * 16 + g + 4 * e;
+                if (P < npair) part[((int64_t)blockIdx.x * npair + P) * (16 * NC) + 16 * cb + r16] = acc[b][cb][e];
+            }
 }
 
-// out[q] = sum_b part[b][q], q over pairs x DY_TT x 2: one wave per output, lane l sums
+// out[q] = sum_b part[b][q], q over pairs x columns: one wave per output, lane l sums
 // blocks l, l+64, ... in order, then a fixed shuffle tree (deterministic)
 __global__ void pairs_reduce_kernel(const double *__restrict__ part, int nblk, int64_t nq, double *__restrict__ out)
 {
@@ -225,8 +259,8 @@ struct DyState {
     void *G;
     const double *eps;
     double *d_omega, *part, *out;
-    int nblk;
-    int64_t cpb, nA, nE;
+    int nblk, nchB;
+    int64_t nchA, nch;
 };
 
 int dy_setup(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, int32_t nmo, int32_t nocc, int32_t nsel,
@@ -251,11 +285,11 @@ int dy_setup(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, int32_t nmo,
     const size_t gbytes = (size_t)nsel * nmo * S.nvo * gs;
     CDS_REQUIRE(ctx, gbytes <= DY_G_MAX, "integrals of the selected orbitals exceed %zu bytes", DY_G_MAX);
     CDS_CALL(cds_ws(ctx, WS_DY_G, gbytes, &S.G));
-    S.nA = (int64_t)S.nvirt * ((int64_t)nocc * (nocc + 1) / 2);
-    S.nE = S.nA + (int64_t)nocc * ((int64_t)S.nvirt * (S.nvirt + 1) / 2);
-    const int64_t nch = cds_ceil_div(S.nE, DY_CH);
-    S.nblk = (int)std::min<int64_t>(DY_BLOCKS, nch);
-    S.cpb = cds_ceil_div(nch, S.nblk);
+    const int64_t nt8 = cds_ceil_div(nocc, 8);
+    S.nchA = S.nvirt * (nt8 * (nt8 + 1) / 2);
+    S.nchB = (int)cds_ceil_div(S.nvo, DY_CH);
+    S.nch = S.nchA + (int64_t)S.nvirt * S.nchB;
+    S.nblk = (int)std::min<int64_t>(DY_BLOCKS, S.nch);
     const int npair = nsel * (nsel + 1) / 2;
     void *w;
     const size_t nq = (size_t)npair * DY_TT * 2;
@@ -268,24 +302,36 @@ int dy_setup(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, int32_t nmo,
     return CDS_OK;
 }
 
+template <typename GT, int NC>
+void dy_launch(cds_ctx *ctx, const DyState &S, int T)
+{
+    const size_t lds = ((size_t)(2 * S.nsel + 16 * NC) * DY_P + 4 * DY_CH) * 8;
+    const int nb = (int)cds_ceil_div(cds_ceil_div(S.nsel * (S.nsel + 1) / 2, 16), 4);   // pair blocks per wave
+    const auto k = nb <= 1 ? sigma_pairs_kernel<GT, 1, NC> : nb <= 2 ? sigma_pairs_kernel<GT, 2, NC>
+                 : nb <= 3 ? sigma_pairs_kernel<GT, 3, NC> : nb <= 5 ? sigma_pairs_kernel<GT, 5, NC>
+                           : sigma_pairs_kernel<GT, 8, NC>;
+    hipLaunchKernelGGL(k, dim3((unsigned)S.nblk), dim3(DY_NT), lds, ctx->stream, (const GT *)S.G, S.nsel, S.nmo, S.nocc,
+                       S.nvirt, S.nvo, S.eps, (const double *)S.d_omega, T, S.nchA, S.nch, S.nchB, S.part);
+}
+
 // Sigma_SS and Sigma'_SS at up to DY_TT trial energies -> host (T x nsel x nsel each)
 int dy_eval(cds_ctx *ctx, const DyState &S, int T, const double *h_w, double *h_sig, double *h_dsig)
 {
     const int npair = S.nsel * (S.nsel + 1) / 2;
-    const int64_t nq = (int64_t)npair * DY_TT * 2;
+    const int ncol = T <= 8 ? 16 : 32;
+    const int64_t nq = (int64_t)npair * ncol;
     void *hp;
-    CDS_CALL(cds_pinned(ctx, (size_t)nq * 8 + 256, &hp));
+    CDS_CALL(cds_pinned(ctx, (size_t)npair * 2 * DY_TT * 8 + 256, &hp));
     double *hb = (double *)hp;
     for (int t = 0; t < DY_TT; ++t) hb[t] = h_w[t < T ? t : T - 1];
     CDS_HIP(ctx, hipMemcpyAsync(S.d_omega, hb, DY_TT * 8, hipMemcpyHostToDevice, ctx->stream));
-    if (S.prec == CDS_PREC_FP64)
-        hipLaunchKernelGGL(sigma_pairs_kernel<double>, dim3((unsigned)S.nblk), dim3(DY_NT), 0, ctx->stream,
-                           (const double *)S.G, S.nsel, S.nmo, S.nocc, S.nvirt, S.nvo, S.eps,
-                           (const double *)S.d_omega, T, S.nA, S.nE, S.cpb, S.part);
-    else
-        hipLaunchKernelGGL(sigma_pairs_kernel<float>, dim3((unsigned)S.nblk), dim3(DY_NT), 0, ctx->stream,
-                           (const float *)S.G, S.nsel, S.nmo, S.nocc, S.nvirt, S.nvo, S.eps,
-                           (const double *)S.d_omega, T, S.nA, S.nE, S.cpb, S.part);
+    if (S.prec == CDS_PREC_FP64) {
+        if (T <= 8) dy_launch<double, 1>(ctx, S, T);
+        else dy_launch<double, 2>(ctx, S, T);
+    } else {
+        if (T <= 8) dy_launch<float, 1>(ctx, S, T);
+        else dy_launch<float, 2>(ctx, S, T);
+    }
     CDS_LAUNCHED(ctx);
     hipLaunchKernelGGL(pairs_reduce_kernel, dim3((unsigned)cds_ceil_div(nq, 4)), dim3(256), 0, ctx->stream,
                        (const double *)S.part, S.nblk, nq, S.out);
@@ -298,7 +344,7 @@ int dy_eval(cds_ctx *ctx, const DyState &S, int T, const double *h_w, double *h_
         while ((t2 + 1) * (t2 + 2) / 2 <= P) ++t2;
         const int s = P - t2 * (t2 + 1) / 2;
         for (int t = 0; t < T; ++t) {
-            const double v = hb[((size_t)P * DY_TT + t) * 2], dv = hb[((size_t)P * DY_TT + t) * 2 + 1];
+            const double v = hb[(size_t)P * ncol + 2 * t], dv = hb[(size_t)P * ncol + 2 * t + 1];
             h_sig[(size_t)t * n * n + (size_t)s * n + t2] = h_sig[(size_t)t * n * n + (size_t)t2 * n + s] = v;
             h_dsig[(size_t)t * n * n + (size_t)s * n + t2] = h_dsig[(size_t)t * n * n + (size_t)t2 * n + s] = dv;
         }

@@ -107,6 +107,19 @@ __global__ __launch_bounds__(256) void unpack_blocks_kernel(const double *__rest
     put4(out, prec, base + (int64_t)nu_row * np_ + bm * 32 + c0, plane, v);
 }
 
+}  // namespace
+
+int cds_unpack64(cds_ctx *ctx, const double *L, int64_t ldl, int64_t k0, int nkb, int nbf, int np_, double *out)
+{
+    const int nb = np_ / 32;
+    hipLaunchKernelGGL(unpack_blocks_kernel, dim3((unsigned)(nb * (nb + 1) / 2), (unsigned)nkb), dim3(256), 0, ctx->stream, L,
+                       ldl, k0, nbf, np_, (void *)out, CDS_PREC_FP64, (int64_t)0);
+    CDS_LAUNCHED(ctx);
+    return CDS_OK;
+}
+
+namespace {
+
 // Ct[p][mu] = C[mu][p]; CX rows: occupied 0..nocc-1 then the MOs ext[0..nx-nocc); k padded to np_
 __global__ void coef_kernel(const double *__restrict__ C, int nbf, int nmo, int nocc, int nx,
                             const int32_t *__restrict__ ext, int np_, void *Ct, void *CX, int prec,
