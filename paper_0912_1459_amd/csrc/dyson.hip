@@ -12,9 +12,9 @@
 // energies that is a product num[pair][e] weight[e][energy] summed over the elements, which
 // sigma_pairs_kernel gives to FP64 MFMA; per-block partial sums are reduced in a fixed order.
 //
-// The Dyson search (host loop of the library, like the quasi-particle Newton solve): one
+// The Dyson search (steps on the device, dyson_step_kernel; the host follows the statuses): one
 // root per selected orbital, started at e_q with u = unit vector q; at each step the
-// symmetric matrix diag(e_S) + Sigma_SS(w) is diagonalised (cyclic Jacobi), the
+// symmetric matrix diag(e_S) + Sigma_SS(w) is diagonalised (Jacobi), the
 // eigenvector of largest overlap with the previous one is followed, and
 //   w <- w + (lambda - w) P,   P = 1 / (1 - u^T Sigma'(w) u)
 // until |dw| <= conv (Eq. (NR)); P is the pole strength.  With one orbital this is Eq. (iter).
@@ -59,7 +59,8 @@ __device__ __forceinline__ int64_t tri_hi(int64_t x)
 template <typename GT, int NB, int NC>
 __global__ __launch_bounds__(DY_NT, 2) void sigma_pairs_kernel(const GT *__restrict__ G, int nsel, int nmo, int nocc,
                                                               int nvirt, int64_t nvo, const double *__restrict__ eps,
-                                                              const double *__restrict__ omega, int T, int64_t nchA,
+                                                              const double *__restrict__ omega,
+                                                              const int *__restrict__ list, int T, int64_t nchA,
                                                               int64_t nch, int nchB, double *__restrict__ part)
 {
     extern __shared__ __align__(16) double lds[];
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(DY_NT, 2) void sigma_pairs_kernel(const GT *__restr
             // weights: thread (l, t) of energies t = s0, s0 + 4, ...
 #pragma unroll
             for (int t = s0; t < 8 * NC; t += 4) {
-                const double inv = on && t < T ? 1.0 / (omega[t] + sd[l]) : 0.0;
+                const double inv = on && t < T ? 1.0 / (omega[list ? list[t] : t] + sd[l]) : 0.0;
                 const double w = sc[l] * inv;
                 sw[2 * t * DY_P + l] = w;
                 sw[(2 * t + 1) * DY_P + l] = -w * inv;
@@ -209,48 +210,153 @@ __global__ void pairs_reduce_kernel(const double *__restrict__ part, int nblk, i
     if (l == 0) out[q] = a;
 }
 
-// cyclic Jacobi for a symmetric n x n matrix (row-major, destroyed): eigenvalues w,
-// eigenvectors in the columns of V
-void jacobi_eigh(int n, std::vector<double> &A, std::vector<double> &w, std::vector<double> &V)
+// One Newton step of the Dyson search for the roots act[blockIdx.x]: the matrix diag(e_S) + Sigma_SS(w)
+// of the root's energy (columns 2t, 2t + 1 of the reduced sums) is diagonalised by parallel-ordered
+// Jacobi sweeps in LDS (round-robin rounds of disjoint rotations), the eigenvector of largest
+// overlap with the previous one is followed, and w <- w + (lambda - w) P.  A workgroup per root:
+// the host did them one after the other (16 roots of 16 orbitals: about 450 us per solve).
+struct DyRoots {
+    double *w, *pole, *U;        // [n], [n], [n][n]: row k = tracked vector of root k
+    int *status, *iters;         // [n]
+    const double *eS;            // [n]
+};
+
+__global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__restrict__ sums, int ncol,
+                                                         const int *__restrict__ act, double conv, int it, DyRoots d)
 {
-    V.assign((size_t)n * n, 0.0);
-    for (int i = 0; i < n; ++i) V[(size_t)i * n + i] = 1.0;
-    for (int sweep = 0; sweep < 100; ++sweep) {
-        double off = 0.0, tot = 0.0;
-        for (int i = 0; i < n; ++i)
-            for (int j = 0; j < n; ++j) {
-                const double x = A[(size_t)i * n + j] * A[(size_t)i * n + j];
-                tot += x;
-                if (i != j) off += x;
-            }
-        if (off <= 1e-30 * tot || off == 0.0) break;
-        for (int p = 0; p < n - 1; ++p)
-            for (int q = p + 1; q < n; ++q) {
-                const double apq = A[(size_t)p * n + q];
-                if (apq == 0.0) continue;
-                const double app = A[(size_t)p * n + p], aqq = A[(size_t)q * n + q];
-                const double theta = (aqq - app) / (2.0 * apq);
-                const double t = (theta >= 0.0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
-                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-                for (int k = 0; k < n; ++k) {              // columns p, q
-                    const double akp = A[(size_t)k * n + p], akq = A[(size_t)k * n + q];
-                    A[(size_t)k * n + p] = c * akp - s * akq;
-                    A[(size_t)k * n + q] = s * akp + c * akq;
-                }
-                for (int k = 0; k < n; ++k) {              // rows p, q
-                    const double apk = A[(size_t)p * n + k], aqk = A[(size_t)q * n + k];
-                    A[(size_t)p * n + k] = c * apk - s * aqk;
-                    A[(size_t)q * n + k] = s * apk + c * aqk;
-                }
-                for (int k = 0; k < n; ++k) {
-                    const double vkp = V[(size_t)k * n + p], vkq = V[(size_t)k * n + q];
-                    V[(size_t)k * n + p] = c * vkp - s * vkq;
-                    V[(size_t)k * n + q] = s * vkp + c * vkq;
-                }
-            }
+    __shared__ double A[DY_MAXSEL + 1][DY_MAXSEL + 2], V[DY_MAXSEL + 1][DY_MAXSEL + 2];
+    __shared__ double rc[(DY_MAXSEL + 1) / 2], rs[(DY_MAXSEL + 1) / 2], red[2][256], ov[DY_MAXSEL + 1], un[DY_MAXSEL + 1];
+    __shared__ int jbest;
+    const int t = blockIdx.x, k = act[t], tid = threadIdx.x;
+    for (int e = tid; e < n * n; e += 256) {
+        const int i = e / n, j = e - i * n, hi = max(i, j), lo = min(i, j);
+        A[i][j] = sums[(int64_t)(hi * (hi + 1) / 2 + lo) * ncol + 2 * t] + (i == j ? d.eS[i] : 0.0);
+        V[i][j] = i == j ? 1.0 : 0.0;
     }
-    w.resize(n);
-    for (int i = 0; i < n; ++i) w[i] = A[(size_t)i * n + i];
+    const int m = n + (n & 1), half = m / 2;      // players of the round robin (an odd n sits one out)
+    for (int sweep = 0; sweep < 100; ++sweep) {
+        __syncthreads();
+        double off = 0.0, tot = 0.0;
+        for (int e = tid; e < n * n; e += 256) {
+            const int i = e / n, j = e - i * n;
+            const double x = A[i][j] * A[i][j];
+            tot += x;
+            if (i != j) off += x;
+        }
+        red[0][tid] = off;
+        red[1][tid] = tot;
+        for (int o = 128; o > 0; o >>= 1) {
+            __syncthreads();
+            if (tid < o) {
+                red[0][tid] += red[0][tid + o];
+                red[1][tid] += red[1][tid + o];
+            }
+        }
+        __syncthreads();
+        // (a matrix that is not finite leaves here too: its comparison is false both ways)
+        if (!(red[0][0] > 1e-30 * red[1][0])) break;
+        for (int r = 0; r < m - 1; ++r) {
+            // round r: (m-1, r) and ((r + i) mod (m-1), (r - i) mod (m-1)), i = 1 .. half - 1
+            auto pair = [&](int i, int &p, int &q) {
+                const int x = i == 0 ? m - 1 : (r + i) % (m - 1), y = i == 0 ? r : (r + m - 1 - i) % (m - 1);
+                p = min(x, y);
+                q = max(x, y);
+            };
+            if (tid < half) {
+                int p, q;
+                pair(tid, p, q);
+                double c = 1.0, s = 0.0;
+                if (q < n && A[p][q] != 0.0) {
+                    const double theta = (A[q][q] - A[p][p]) / (2.0 * A[p][q]);
+                    const double tn = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
+                    c = 1.0 / sqrt(tn * tn + 1.0);
+                    s = tn * c;
+                }
+                rc[tid] = c;
+                rs[tid] = s;
+            }
+            __syncthreads();
+            for (int e = tid; e < half * n * 2; e += 256) {      // columns p, q of A and V
+                const int i = e / (2 * n), rem = e - i * 2 * n, x = rem >> 1;
+                int p, q;
+                pair(i, p, q);
+                if (q >= n || rs[i] == 0.0) continue;
+                double(*M)[DY_MAXSEL + 2] = rem & 1 ? V : A;
+                const double a = M[x][p], b = M[x][q];
+                M[x][p] = rc[i] * a - rs[i] * b;
+                M[x][q] = rs[i] * a + rc[i] * b;
+            }
+            __syncthreads();
+            for (int e = tid; e < half * n; e += 256) {          // rows p, q of A
+                const int i = e / n, x = e - i * n;
+                int p, q;
+                pair(i, p, q);
+                if (q >= n || rs[i] == 0.0) continue;
+                const double a = A[p][x], b = A[q][x];
+                A[p][x] = rc[i] * a - rs[i] * b;
+                A[q][x] = rs[i] * a + rc[i] * b;
+            }
+            __syncthreads();
+        }
+    }
+    if (tid < n) {
+        double v = 0.0;
+        for (int i = 0; i < n; ++i) v += V[i][tid] * d.U[(int64_t)k * n + i];
+        ov[tid] = v;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        int jb = 0;
+        double best = -1.0;
+        for (int j = 0; j < n; ++j)
+            if (fabs(ov[j]) > best) {
+                best = fabs(ov[j]);
+                jb = j;
+            }
+        jbest = jb;
+    }
+    __syncthreads();
+    const int jb = jbest;
+    if (tid < n) un[tid] = (ov[jb] >= 0.0 ? 1.0 : -1.0) * V[tid][jb];
+    __syncthreads();
+    if (tid < n) {
+        d.U[(int64_t)k * n + tid] = un[tid];
+        double v = 0.0;
+        for (int j = 0; j < n; ++j) {
+            const int hi = max(tid, j), lo = min(tid, j);
+            v += sums[(int64_t)(hi * (hi + 1) / 2 + lo) * ncol + 2 * t + 1] * un[j];
+        }
+        red[0][tid] = un[tid] * v;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        double sp = 0.0;
+        for (int i = 0; i < n; ++i) sp += red[0][i];
+        const double P = 1.0 / (1.0 - sp), w = d.w[k], wn = w + (A[jb][jb] - w) * P;
+        d.pole[k] = P;
+        d.iters[k] = it;
+        d.w[k] = wn;
+        if (!isfinite(wn) || !isfinite(P)) d.status[k] = CDS_QP_NONFINITE;
+        else if (fabs(wn - w) <= conv) d.status[k] = CDS_QP_CONVERGED;
+    }
+}
+
+// the roots still iterating, in order; first: the state is set up (w = e_q, unit vectors)
+__global__ __launch_bounds__(64) void dyson_list_kernel(int n, int first, const double *__restrict__ eps,
+                                                        const int *__restrict__ sel, double *__restrict__ eS, DyRoots d,
+                                                        int *__restrict__ act)
+{
+    const int k = threadIdx.x;                    // n <= DY_MAXSEL
+    if (first && k < n) {
+        d.w[k] = eS[k] = eps[sel[k]];
+        d.pole[k] = __builtin_nan("");
+        d.status[k] = -1;
+        d.iters[k] = 0;
+        for (int i = 0; i < n; ++i) d.U[k * n + i] = i == k ? 1.0 : 0.0;
+    }
+    const bool on = k < n && (first || d.status[k] < 0);
+    const unsigned long long m = __ballot(on);
+    if (on) act[__popcll(m & ((1ull << k) - 1))] = k;
 }
 
 struct DyState {
@@ -303,7 +409,7 @@ int dy_setup(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, int32_t nmo,
 }
 
 template <typename GT, int NC>
-void dy_launch(cds_ctx *ctx, const DyState &S, int T)
+void dy_launch(cds_ctx *ctx, const DyState &S, int T, const double *omega, const int *list)
 {
     const size_t lds = ((size_t)(2 * S.nsel + 16 * NC) * DY_P + 4 * DY_CH) * 8;
     const int nb = (int)cds_ceil_div(cds_ceil_div(S.nsel * (S.nsel + 1) / 2, 16), 4);   // pair blocks per wave
@@ -311,31 +417,40 @@ void dy_launch(cds_ctx *ctx, const DyState &S, int T)
                  : nb <= 3 ? sigma_pairs_kernel<GT, 3, NC> : nb <= 5 ? sigma_pairs_kernel<GT, 5, NC>
                            : sigma_pairs_kernel<GT, 8, NC>;
     hipLaunchKernelGGL(k, dim3((unsigned)S.nblk), dim3(DY_NT), lds, ctx->stream, (const GT *)S.G, S.nsel, S.nmo, S.nocc,
-                       S.nvirt, S.nvo, S.eps, (const double *)S.d_omega, T, S.nchA, S.nch, S.nchB, S.part);
+                       S.nvirt, S.nvo, S.eps, omega, list, T, S.nchA, S.nch, S.nchB, S.part);
+}
+
+int dy_cols(int T) { return T <= 8 ? 16 : 32; }
+
+// the pairs' sums S.out [pair][dy_cols(T)] at T <= DY_TT device energies: omega[t], or omega[list[t]]
+int dy_sums(cds_ctx *ctx, const DyState &S, int T, const double *omega, const int *list)
+{
+    const int64_t nq = (int64_t)(S.nsel * (S.nsel + 1) / 2) * dy_cols(T);
+    if (S.prec == CDS_PREC_FP64) {
+        if (T <= 8) dy_launch<double, 1>(ctx, S, T, omega, list);
+        else dy_launch<double, 2>(ctx, S, T, omega, list);
+    } else {
+        if (T <= 8) dy_launch<float, 1>(ctx, S, T, omega, list);
+        else dy_launch<float, 2>(ctx, S, T, omega, list);
+    }
+    CDS_LAUNCHED(ctx);
+    hipLaunchKernelGGL(pairs_reduce_kernel, dim3((unsigned)cds_ceil_div(nq, 4)), dim3(256), 0, ctx->stream,
+                       (const double *)S.part, S.nblk, nq, S.out);
+    CDS_LAUNCHED(ctx);
+    return CDS_OK;
 }
 
 // Sigma_SS and Sigma'_SS at up to DY_TT trial energies -> host (T x nsel x nsel each)
 int dy_eval(cds_ctx *ctx, const DyState &S, int T, const double *h_w, double *h_sig, double *h_dsig)
 {
-    const int npair = S.nsel * (S.nsel + 1) / 2;
-    const int ncol = T <= 8 ? 16 : 32;
+    const int npair = S.nsel * (S.nsel + 1) / 2, ncol = dy_cols(T);
     const int64_t nq = (int64_t)npair * ncol;
     void *hp;
     CDS_CALL(cds_pinned(ctx, (size_t)npair * 2 * DY_TT * 8 + 256, &hp));
     double *hb = (double *)hp;
     for (int t = 0; t < DY_TT; ++t) hb[t] = h_w[t < T ? t : T - 1];
     CDS_HIP(ctx, hipMemcpyAsync(S.d_omega, hb, DY_TT * 8, hipMemcpyHostToDevice, ctx->stream));
-    if (S.prec == CDS_PREC_FP64) {
-        if (T <= 8) dy_launch<double, 1>(ctx, S, T);
-        else dy_launch<double, 2>(ctx, S, T);
-    } else {
-        if (T <= 8) dy_launch<float, 1>(ctx, S, T);
-        else dy_launch<float, 2>(ctx, S, T);
-    }
-    CDS_LAUNCHED(ctx);
-    hipLaunchKernelGGL(pairs_reduce_kernel, dim3((unsigned)cds_ceil_div(nq, 4)), dim3(256), 0, ctx->stream,
-                       (const double *)S.part, S.nblk, nq, S.out);
-    CDS_LAUNCHED(ctx);
+    CDS_CALL(dy_sums(ctx, S, T, S.d_omega, nullptr));
     CDS_HIP(ctx, hipMemcpyAsync(hb, S.out, (size_t)nq * 8, hipMemcpyDeviceToHost, ctx->stream));
     CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
     const int n = S.nsel;
@@ -388,77 +503,48 @@ extern "C" int cds_dyson_solve(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t
     CDS_CALL(cds_timer_start(ctx, &tm));
     CDS_CALL(dy_setup(ctx, prec, nvec, ldk, nmo, nocc, nsel, h_sel, Bsel, Bvo, eps, S));
     const int n = nsel;
-    std::vector<double> eS(n), w(n), pole(n, NAN), U((size_t)n * n, 0.0);
-    {
-        std::vector<double> eh(nmo);
-        void *hp;
-        CDS_CALL(cds_pinned(ctx, (size_t)nmo * 8, &hp));
-        CDS_HIP(ctx, hipMemcpyAsync(hp, eps, (size_t)nmo * 8, hipMemcpyDeviceToHost, ctx->stream));
+    // the roots' state, read back whole after every step: w, P, the vectors, status, steps; then the
+    // orbitals' own energies, their numbers and the list of roots still iterating
+    const size_t state = (size_t)n * (2 + n) * 8 + (size_t)2 * n * 4;
+    void *wr, *hp;
+    CDS_CALL(cds_ws(ctx, WS_AD_TMP2, state + (size_t)n * 16 + 64, &wr));
+    CDS_CALL(cds_pinned(ctx, state + (size_t)n * 4, &hp));
+    DyRoots R;
+    R.w = (double *)wr;
+    R.pole = R.w + n;
+    R.U = R.pole + n;
+    R.status = (int *)(R.U + (size_t)n * n);
+    R.iters = R.status + n;
+    double *d_eS = (double *)(R.iters + n);
+    R.eS = d_eS;
+    int *d_sel = (int *)(d_eS + n), *d_act = d_sel + n;
+    std::copy(h_sel, h_sel + n, (int32_t *)hp);
+    CDS_HIP(ctx, hipMemcpyAsync(d_sel, hp, (size_t)n * 4, hipMemcpyHostToDevice, ctx->stream));
+    const double *hw = (const double *)hp, *hP = hw + n, *hU = hP + n;
+    const int *hs = (const int *)(hU + (size_t)n * n), *hi = hs + n;
+    int nact = n;
+    for (int it = 1; it <= max_iter && nact > 0; ++it) {
+        hipLaunchKernelGGL(dyson_list_kernel, dim3(1), dim3(64), 0, ctx->stream, n, it == 1 ? 1 : 0, eps,
+                           (const int *)d_sel, d_eS, R, d_act);
+        CDS_LAUNCHED(ctx);
+        for (int b0 = 0; b0 < nact; b0 += DY_TT) {
+            const int nt = std::min(DY_TT, nact - b0);
+            CDS_CALL(dy_sums(ctx, S, nt, R.w, d_act + b0));
+            hipLaunchKernelGGL(dyson_step_kernel, dim3((unsigned)nt), dim3(256), 0, ctx->stream, n, (const double *)S.out,
+                               dy_cols(nt), (const int *)d_act + b0, conv, it, R);
+            CDS_LAUNCHED(ctx);
+        }
+        CDS_HIP(ctx, hipMemcpyAsync(hp, wr, state, hipMemcpyDeviceToHost, ctx->stream));
         CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        std::copy((const double *)hp, (const double *)hp + nmo, eh.begin());
-        for (int k = 0; k < n; ++k) {
-            eS[k] = eh[h_sel[k]];
-            w[k] = eS[k];
-            U[(size_t)k * n + k] = 1.0;                    // row k: tracked vector of root k
-        }
-    }
-    std::vector<int> status(n, -1), iters(n, 0);
-    std::vector<double> sig((size_t)DY_TT * n * n), dsig((size_t)DY_TT * n * n), A, lam, V;
-    for (int it = 1; it <= max_iter; ++it) {
-        std::vector<int> act;
-        for (int k = 0; k < n; ++k)
-            if (status[k] < 0) act.push_back(k);
-        if (act.empty()) break;
-        for (size_t b0 = 0; b0 < act.size(); b0 += DY_TT) {
-            const int nt = (int)std::min<size_t>(DY_TT, act.size() - b0);
-            double wt[DY_TT];
-            for (int t = 0; t < nt; ++t) wt[t] = w[act[b0 + t]];
-            CDS_CALL(dy_eval(ctx, S, nt, wt, sig.data(), dsig.data()));
-            for (int t = 0; t < nt; ++t) {
-                const int k = act[b0 + t];
-                A.assign(sig.begin() + (size_t)t * n * n, sig.begin() + (size_t)(t + 1) * n * n);
-                for (int i = 0; i < n; ++i) A[(size_t)i * n + i] += eS[i];
-                jacobi_eigh(n, A, lam, V);
-                int jb = 0;
-                double best = -1.0, sgn = 1.0;
-                for (int j = 0; j < n; ++j) {
-                    double ov = 0.0;
-                    for (int i = 0; i < n; ++i) ov += V[(size_t)i * n + j] * U[(size_t)k * n + i];
-                    if (std::fabs(ov) > best) {
-                        best = std::fabs(ov);
-                        jb = j;
-                        sgn = ov >= 0.0 ? 1.0 : -1.0;
-                    }
-                }
-                double sp = 0.0;
-                const double *dS = dsig.data() + (size_t)t * n * n;
-                for (int i = 0; i < n; ++i) {
-                    U[(size_t)k * n + i] = sgn * V[(size_t)i * n + jb];
-                }
-                for (int i = 0; i < n; ++i)
-                    for (int j = 0; j < n; ++j) sp += U[(size_t)k * n + i] * dS[(size_t)i * n + j] * U[(size_t)k * n + j];
-                const double P = 1.0 / (1.0 - sp);
-                const double wn = w[k] + (lam[jb] - w[k]) * P;
-                pole[k] = P;
-                iters[k] = it;
-                if (!std::isfinite(wn) || !std::isfinite(P)) {
-                    w[k] = wn;
-                    status[k] = CDS_QP_NONFINITE;
-                } else if (std::fabs(wn - w[k]) <= conv) {
-                    w[k] = wn;
-                    status[k] = CDS_QP_CONVERGED;
-                } else {
-                    w[k] = wn;
-                }
-            }
-        }
+        nact = 0;
+        for (int k = 0; k < n; ++k) nact += hs[k] < 0;
     }
     for (int k = 0; k < n; ++k) {
-        h_omega[k] = w[k];
-        h_pole[k] = pole[k];
-        h_iters[k] = iters[k];
-        h_status[k] = status[k] < 0 ? CDS_QP_MAX_ITER : status[k];
-        for (int i = 0; i < n; ++i) h_vec[(size_t)k * n + i] = U[(size_t)k * n + i];
+        h_omega[k] = hw[k];
+        h_pole[k] = hP[k];
+        h_iters[k] = hi[k];
+        h_status[k] = hs[k] < 0 ? CDS_QP_MAX_ITER : hs[k];
+        for (int i = 0; i < n; ++i) h_vec[(size_t)k * n + i] = hU[(size_t)k * n + i];
     }
     CDS_CALL(cds_timer_stop(ctx, &tm, &ctx->stats.t_dyson_ms));
     CDS_CALL(cds_timers_flush(ctx));

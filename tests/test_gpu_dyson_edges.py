@@ -57,3 +57,32 @@ def test_sigma_matrix_edges(prec, nocc, nvirt, nvec, nsel, T):
             m = (m + m.T).cpu().numpy()
             assert (np.abs(got - r.cpu().numpy()) <= u * m).all(), (prec, t)
             assert (got == got.T).all()
+
+
+@pytest.mark.parametrize("nsel", [1, 2, 3, 16, 17, 31])
+def test_dyson_step_equals_host_diagonalisation(nsel):
+    # one step of every root from e_q with the unit vector: the matrix at e_q diagonalised by LAPACK.
+    # Both are backward stable; eigenvectors move by (rounding)/(gap), so the bar is 1e-13 / gap.
+    import paper_0912_1459_amd.core as C
+    g = np.random.default_rng(nsel)
+    nocc, nvirt, nvec = 20, 24, 30
+    nmo = nocc + nvirt
+    B = blocks_from_numpy(g.standard_normal((nvec, nsel, nmo)) * 0.02, g.standard_normal((nvec, nvirt, nocc)) * 0.02, nocc,
+                          np.arange(4, 4 + nsel), "fp64")
+    e = np.concatenate([np.sort(g.uniform(-1.5, -0.3, nocc)), np.sort(g.uniform(0.1, 3.0, nvirt))])
+    eps = torch.tensor(e, device="cuda")
+    print("dyson step", nsel, flush=True)
+    r = C.dyson_solve(B, eps, conv=1e-300, max_iter=1)
+    sel = np.arange(4, 4 + nsel)
+    s, ds = C.sigma2_matrix(B, eps, e[sel])
+    for k in range(nsel):
+        lam, V = np.linalg.eigh(np.diag(e[sel]) + s[k])
+        j = int(np.argmax(np.abs(V[k])))
+        u = V[:, j] * np.sign(V[k, j])
+        gap = np.abs(np.delete(lam, j) - lam[j]).min() if nsel > 1 else 1.0
+        tol = 1e-13 / gap
+        assert np.abs(r.vec[k] - u).max() <= tol
+        P = 1.0 / (1.0 - u @ ds[k] @ u)
+        assert abs(r.pole[k] - P) <= 10 * tol * max(1.0, np.abs(ds[k]).max())
+        assert abs(r.omega[k] - (e[sel[k]] + (lam[j] - e[sel[k]]) * P)) <= 10 * tol * max(1.0, np.abs(ds[k]).max())
+    assert (r.iters == 1).all()
