@@ -67,6 +67,7 @@ constexpr int CD_CG = 8;                 // candidate columns per thread in the 
 constexpr int CD_NCG = CD_NCAND / CD_CG; // column groups (rows of the column grid)
 constexpr int CD_PASS_D = 2;            // k-steps (4 vectors each) in flight per wave in the pass
 constexpr int CD_PASS_ZROWS = 8;        // zero rows of P after row k0
+constexpr int CD_PASS_SPLIT = 128;      // tiles up to which the pass takes 16 candidates per workgroup
 constexpr int CD_TPT = 4;               // tile records per thread in the flat pivot search
 constexpr int CD_ONE_TILE_MAX = 1280;   // tiles up to which a step block holds one tile
 constexpr int CD_SPEC_MAX = 48;         // steps of one speculative look-ahead block (multiple of 8, <= 64)
@@ -1532,8 +1533,8 @@ __global__ __launch_bounds__(256) void cd_commit_kernel(CdBufs b, CdParams cp, c
     }
     const int64_t tile = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (tile < b.ntile) tile_record(b, w, sw, cp, tile, ok && m == 0, ok && m != 1, d);
+    if (blockIdx.x == 0 && (int)threadIdx.x < nc) piv[k0 + threadIdx.x] = sp[threadIdx.x];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        for (int j = 0; j < nc; ++j) piv[k0 + j] = so->p[j];
         st->k = k0 + nc;
         st->dmax = so->cmax[nc - 1];
         st->nspec += nc;
@@ -1601,15 +1602,88 @@ __device__ unsigned long long radix_boundary(const unsigned long long (&u)[KPT],
     return *s_prefix;
 }
 
+// The same boundary from one histogram where it lies within a factor of 256 of the largest key
+// (top 32 bits `top`): bins of 2^15 key steps (3 %) below the largest, and the few keys of the
+// boundary's bin ranked among themselves by one wave.  Keys further down are not counted (they
+// would all meet in one bin).  Otherwise, or with more than SEL_LIST keys in that bin, the radix
+// passes.  The selection with four passes
+// of 256 bins each, its rows' marks and residuals loaded one after the other, took 17.1 us at 820
+// pairs (now 10.1), 21.7 at 28,920 (17.8) and 67 with 128 candidates of 461,280 (44 us).
+constexpr int SEL_LIST = 256;
+template <int NT, int KPT>
+__device__ unsigned long long top_boundary(const unsigned long long (&u)[KPT], unsigned top, int want, unsigned int *hist,
+                                           unsigned *list, unsigned long long *s_prefix, int *s_need)
+{
+    for (int q = threadIdx.x; q < 256; q += NT) hist[q] = 0;
+    __syncthreads();
+    auto bin = [&](unsigned long long k) {
+        const unsigned h = (unsigned)(k >> 32);
+        return k == 0ull || h > top ? 255u : min(255u, (top - h) >> 15);
+    };
+#pragma unroll
+    for (int e = 0; e < KPT; ++e) {
+        const unsigned q = bin(u[e]);
+        if (q < 255u) atomicAdd(&hist[q], 1u);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        // the first bin at which the running count reaches `want`; lane l holds bins 4l..4l+3
+        const int l = threadIdx.x;
+        int h[4], own = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) own += h[i] = hist[4 * l + i];
+        int S = own;                                       // sum over lanes <= l
+        for (int o = 1; o < 64; o <<= 1) {
+            const int v = __shfl_up(S, o, 64);
+            if (l >= o) S += v;
+        }
+        const unsigned long long ok = __ballot(S >= want);
+        if (ok == 0ull) {
+            if (l == 0) *s_need = -1;
+        } else if (l == __ffsll((long long)ok) - 1) {
+            int rem = want - (S - own), q = 0;
+            while (h[q] < rem) rem -= h[q++];
+            *s_need = (4 * l + q) << 16 | rem;             // bin, rank within it (at most NT KPT keys)
+        }
+        if (l == 0) *s_prefix = 0ull;
+    }
+    __syncthreads();
+    const int found = *s_need;
+    const int q = found >> 16, rem = found & 0xffff;
+    if (found < 0 || (int)hist[q] > SEL_LIST) {
+        __syncthreads();                                   // every thread has read s_need and hist
+        return radix_boundary<NT, KPT>(u, want, hist, s_prefix, s_need);
+    }
+    const int cnt = hist[q];
+    __syncthreads();
+    if (threadIdx.x == 0) hist[0] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < KPT; ++e)
+        if (bin(u[e]) == (unsigned)q) list[atomicAdd(&hist[0], 1u)] = (unsigned)(u[e] >> 32);
+    __syncthreads();
+    if ((int)threadIdx.x < cnt) {
+        const unsigned v = list[threadIdx.x];
+        int gt = 0, ge = 0;
+        for (int i = 0; i < cnt; ++i) {
+            gt += list[i] > v;
+            ge += list[i] >= v;
+        }
+        if (gt < rem && rem <= ge) *s_prefix = v;          // equal keys write the same value
+    }
+    __syncthreads();
+    return *s_prefix;
+}
+
 // Writes the ids of the top `want` keys to out[] in a deterministic order (keys above the
 // boundary first, then boundary keys, each by id); ids are threadIdx.x * KPT + e.  Returns
 // how many were written.
 template <int NT, int KPT, typename F>
-__device__ int select_top(const unsigned long long (&u)[KPT], int want, unsigned int *hist,
+__device__ int select_top(const unsigned long long (&u)[KPT], unsigned top, int want, unsigned int *hist, unsigned *list,
                           unsigned long long *s_prefix, int *s_need, int *shs, F &&emit,
                           unsigned long long *s_rest)
 {
-    const unsigned long long thr = radix_boundary<NT, KPT>(u, want, hist, s_prefix, s_need);
+    const unsigned long long thr = top_boundary<NT, KPT>(u, top, want, hist, list, s_prefix, s_need);
     int na = 0, nbd = 0;
 #pragma unroll
     for (int e = 0; e < KPT; ++e) {
@@ -1664,6 +1738,7 @@ __global__ __launch_bounds__(NT) void cd_cand_kernel(CdBufs b, CdParams cp, int 
                   "candidate selection shape");
     __shared__ PickShared psh;
     __shared__ unsigned int hist[256];
+    __shared__ unsigned list[SEL_LIST];
     __shared__ unsigned long long s_prefix;
     __shared__ int s_need;
     __shared__ int shs[NT / 64 + 1];
@@ -1681,8 +1756,10 @@ __global__ __launch_bounds__(NT) void cd_cand_kernel(CdBufs b, CdParams cp, int 
     }
     // the previous block's rows leave the slot map
     const int nmap = st->nmap;
-    if ((int)threadIdx.x < nmap) b.slot[cand[threadIdx.x]] = -1;
-    __syncthreads();
+    if ((int)threadIdx.x < nmap) b.slot[cand[threadIdx.x]] = -1;    // (barriers below, before the new marks)
+    // up to NT tiles a thread's one tile key is loaded with the pivot search's records
+    const bool one = b.ntile <= NT;
+    const double tmx = one && (int64_t)threadIdx.x < b.ntile ? b.ts[r][threadIdx.x].mx : 0.0;
     const Pick pk = cd_pick<NT>(b, r, sr, cp, k, psh);
     if (pk.status != PICK_GO) {                  // the step kernel records the termination
         if (threadIdx.x == 0) {
@@ -1693,32 +1770,49 @@ __global__ __launch_bounds__(NT) void cd_cand_kernel(CdBufs b, CdParams cp, int 
     }
     const int64_t p = pk.p;
     const TileStat *ts = b.ts[r];
-    unsigned long long u[TK];
+    const unsigned top = (unsigned)((unsigned long long)__double_as_longlong(pk.mx) >> 32);   // no key is larger
+    int ntsel;
+    unsigned long long rest_tile;                // largest maximum of a tile not selected
+    if (b.ntile < NC) {                          // every tile (one without a positive row adds no key)
+        ntsel = (int)b.ntile;
+        rest_tile = 0ull;
+        if ((int)threadIdx.x < ntsel) stile[threadIdx.x] = threadIdx.x;
+    } else if (one) {
+        const unsigned long long u[1] = {tmx > 0.0 ? (unsigned long long)__double_as_longlong(tmx) : 0ull};
+        ntsel = select_top<NT, 1>(u, top, NC, hist, list, &s_prefix, &s_need, shs,
+                                  [&](int pos, int id) { stile[pos] = id; }, &s_rest);
+        rest_tile = s_rest;
+    } else {
+        unsigned long long u[TK];
 #pragma unroll
-    for (int e = 0; e < TK; ++e) {
-        const int64_t t = (int64_t)threadIdx.x * TK + e;
-        const double v = t < b.ntile ? ts[t].mx : 0.0;
-        u[e] = v > 0.0 ? (unsigned long long)__double_as_longlong(v) : 0ull;
+        for (int e = 0; e < TK; ++e) {
+            const int64_t t = (int64_t)threadIdx.x * TK + e;
+            const double v = t < b.ntile ? ts[t].mx : 0.0;
+            u[e] = v > 0.0 ? (unsigned long long)__double_as_longlong(v) : 0ull;
+        }
+        ntsel = select_top<NT, TK>(u, top, NC, hist, list, &s_prefix, &s_need, shs,
+                                   [&](int pos, int id) { stile[pos] = id; }, &s_rest);
+        rest_tile = s_rest;
     }
-    const int ntsel = select_top<NT, TK>(u, NC, hist, &s_prefix, &s_need, shs,
-                                                 [&](int pos, int id) { stile[pos] = id; }, &s_rest);
-    const unsigned long long rest_tile = s_rest;  // largest maximum of a tile not selected
     __syncthreads();
+    // the rows' marks and residuals, every load in flight before the first is looked at
     unsigned long long v[RK];
+    double rd[RK];
+    unsigned char rm[RK];
 #pragma unroll
     for (int e = 0; e < RK; ++e) {
         const int i = threadIdx.x * RK + e;
         const int slot = i / CD_TILE;
-        v[e] = 0ull;
-        if (slot < ntsel) {
-            const int64_t I = stile[slot] * CD_TILE + i % CD_TILE;
-            if (I < cp.npairs && I != p && !b.mask[r][I]) {
-                const double d = b.D[r][I];
-                if (d > 0.0) v[e] = (unsigned long long)__double_as_longlong(d);
-            }
-        }
+        const int64_t I = slot < ntsel ? stile[slot] * CD_TILE + i % CD_TILE : cp.npairs;
+        const int64_t Ic = I < cp.npairs ? I : 0;
+        rm[e] = b.mask[r][Ic];
+        rd[e] = b.D[r][Ic];
+        v[e] = I < cp.npairs && I != p ? 1ull : 0ull;
     }
-    const int nrow = select_top<NT, RK>(v, NC - 1, hist, &s_prefix, &s_need, shs, [&](int pos, int id) {
+#pragma unroll
+    for (int e = 0; e < RK; ++e)
+        v[e] = v[e] && !rm[e] && rd[e] > 0.0 ? (unsigned long long)__double_as_longlong(rd[e]) : 0ull;
+    const int nrow = select_top<NT, RK>(v, top, NC - 1, hist, list, &s_prefix, &s_need, shs, [&](int pos, int id) {
         cand[1 + pos] = stile[id / CD_TILE] * CD_TILE + id % CD_TILE;
     }, &s_rest);
     // every eligible row outside the candidates is at most the larger of the two rests (keys
@@ -1834,10 +1928,13 @@ __global__ void cd_candcol_gather_kernel(PairTable pt, const double *__restrict_
 // candidates of P at once (16 bytes), half the load instructions of one row each; the MFMA
 // row (column) r16 of block 2u + h is then tile row (candidate) 32u + 2 r16 + h.  Each output
 // takes the same products in the same order either way.
+// NN: groups of 16 candidates per workgroup, blockIdx.y takes the next NN (4: all 64; 1 where the
+// rows alone are too few workgroups to hide the epilogue's integrals: 820 pairs, 13 workgroups of
+// 16 integrals per thread, 21.5 us per block; 52 of 4, 8.4 us).  The same values either way.
 // ERI: R holds nothing yet; the epilogue evaluates the candidate columns' integrals V[I][cand_c]
 // itself (the values the column kernel would have stored, bit for bit), which saves writing R and
 // reading it back (2 x 8 x npairs x 64 bytes per block).
-template <bool W16, bool ERI>
+template <bool W16, bool ERI, int NN>
 __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_t ldl, int64_t npairs,
                                                          int64_t k0, const CdState *__restrict__ st,
                                                          const double *P, double *__restrict__ R,
@@ -1846,10 +1943,11 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
                                                          const int64_t *__restrict__ cand)
 {
     constexpr int D = CD_PASS_D;
-    __shared__ double red[2][CD_NCAND][CD_TILE];           // red[slot][cand][row ^ cand]
+    __shared__ double red[2][16 * NN][CD_TILE];            // red[slot][cand][row ^ cand]
     if (spec_idle(st) || st->ncand == 0) return;
     if (k0 < 0) k0 = st->k;                                // speculative block: from the state
     const int nc = st->ncand;
+    const int cb = blockIdx.y * 16 * NN;                   // first candidate of this workgroup
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
     const int64_t tile0 = (int64_t)blockIdx.x * CD_TILE;
@@ -1867,12 +1965,13 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
     const int64_t s0 = ks * w / 4, s1 = ks * (w + 1) / 4;
     const int64_t jz = 4 * ks;                             // a zero row of P (k0 <= jz < k0 + 4)
     const int64_t jl_max = k0 > 0 ? k0 - 1 : 0;
-    doublex4 acc[4][4];
+    doublex4 acc[4][NN];
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int n = 0; n < 4; ++n) acc[m][n] = doublex4{0.0, 0.0, 0.0, 0.0};
-    double a[D][4], b[D][4];
+        for (int n = 0; n < NN; ++n) acc[m][n] = doublex4{0.0, 0.0, 0.0, 0.0};
+    double a[D][4], b[D][NN];
+    constexpr bool P16 = W16 && NN % 2 == 0;               // two candidates at once
     auto load = [&](int64_t s, double *as, double *bs) {
         const int64_t j = 4 * s + g;
         const int64_t jl = min(j, jl_max);                 // L row: finite
@@ -1884,22 +1983,25 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
                 as[2 * u] = x.x;
                 as[2 * u + 1] = x.y;
             }
+        } else {
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const double2 y = *reinterpret_cast<const double2 *>(P + jp * CD_NCAND + 32 * u + 2 * r16);
+            for (int m = 0; m < 4; ++m) as[m] = L[jl * ldl + rowL[m]];
+        }
+        if constexpr (P16) {
+#pragma unroll
+            for (int u = 0; u < NN / 2; ++u) {
+                const double2 y = *reinterpret_cast<const double2 *>(P + jp * CD_NCAND + cb + 32 * u + 2 * r16);
                 bs[2 * u] = y.x;
                 bs[2 * u + 1] = y.y;
             }
         } else {
 #pragma unroll
-            for (int m = 0; m < 4; ++m) as[m] = L[jl * ldl + rowL[m]];
-#pragma unroll
-            for (int n = 0; n < 4; ++n) bs[n] = P[jp * CD_NCAND + 16 * n + r16];
+            for (int n = 0; n < NN; ++n) bs[n] = P[jp * CD_NCAND + cb + 16 * n + r16];
         }
     };
-    // tile row of MFMA block m, lane row q (0..15), and candidate of block n, lane column r
+    // tile row of MFMA block m, lane row q (0..15), and candidate (from cb) of block n, lane column r
     auto trow = [&](int m, int q) { return W16 ? 32 * (m >> 1) + 2 * q + (m & 1) : 16 * m + q; };
-    auto tcol = [&](int n, int r) { return W16 ? 32 * (n >> 1) + 2 * r + (n & 1) : 16 * n + r; };
+    auto tcol = [&](int n, int r) { return P16 ? 32 * (n >> 1) + 2 * r + (n & 1) : 16 * n + r; };
     if (k0 > 0) {
 #pragma unroll
         for (int i = 0; i < D; ++i) {
@@ -1912,7 +2014,7 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
-                    for (int n = 0; n < 4; ++n)
+                    for (int n = 0; n < NN; ++n)
                         acc[m][n] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][m], b[i][n], acc[m][n], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
                 asm volatile("" ::: "memory");       // the refill stays behind the MFMAs of its slot
@@ -1927,7 +2029,7 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int n = 0; n < 4; ++n)
+            for (int n = 0; n < NN; ++n)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int c = tcol(n, r16), row = trow(m, g + 4 * e);
@@ -1938,7 +2040,7 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
 #pragma unroll
         for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int n = 0; n < 4; ++n)
+            for (int n = 0; n < NN; ++n)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int c = tcol(n, r16), row = trow(m, g + 4 * e);
@@ -1966,8 +2068,8 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
     if (w < 2) put(w);
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < CD_TILE * CD_NCAND / 256; ++q) {
-        const int c = (threadIdx.x + 256 * q) / CD_TILE;
+    for (int q = 0; q < CD_TILE * 16 * NN / 256; ++q) {
+        const int cl = (threadIdx.x + 256 * q) / CD_TILE, c = cb + cl;
         if (c < nc && I < npairs) {
             double base;                                           // V[I][cand_c]
             if constexpr (ERI) {
@@ -1976,7 +2078,7 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
             } else {
                 base = R[(int64_t)c * ldr + I];
             }
-            const double v = base - (red[0][c][row ^ c] + red[1][c][row ^ c]);
+            const double v = base - (red[0][cl][row ^ cl] + red[1][cl][row ^ cl]);
             R[(int64_t)c * ldr + I] = v;
             if (sl >= 0) rc[c * CD_NCAND + sl] = v;
         }
@@ -2620,20 +2722,25 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
             if (ctx->kernel_timing) CDS_CALL(cds_timer_stop(ctx, &tsp, &ctx->stats.t_cd_spec_ms));
             CdsTimer tp;
             if (ctx->kernel_timing) CDS_CALL(cds_timer_start(ctx, &tp));
-            if (pass16 && !dense)
-                hipLaunchKernelGGL((cd_pass_kernel<true, true>), grid, dim3(256), 0, ctx->stream, (const double *)L,
+            if (pass16 && !dense && ntile <= CD_PASS_SPLIT)
+                hipLaunchKernelGGL((cd_pass_kernel<true, true, 1>), dim3((unsigned)ntile, CD_NCAND / 16), dim3(256), 0,
+                                   ctx->stream, (const double *)L, ldl, npairs, (int64_t)-1, (const CdState *)st,
+                                   (const double *)Pc, Rc, ldr, (const signed char *)bf.slot, bf.rc, pt,
+                                   (const int64_t *)cand);
+            else if (pass16 && !dense)
+                hipLaunchKernelGGL((cd_pass_kernel<true, true, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
                                    (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
             else if (pass16)
-                hipLaunchKernelGGL((cd_pass_kernel<true, false>), grid, dim3(256), 0, ctx->stream, (const double *)L,
+                hipLaunchKernelGGL((cd_pass_kernel<true, false, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
                                    (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
             else if (!dense)
-                hipLaunchKernelGGL((cd_pass_kernel<false, true>), grid, dim3(256), 0, ctx->stream, (const double *)L,
+                hipLaunchKernelGGL((cd_pass_kernel<false, true, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
                                    (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
             else
-                hipLaunchKernelGGL((cd_pass_kernel<false, false>), grid, dim3(256), 0, ctx->stream, (const double *)L,
+                hipLaunchKernelGGL((cd_pass_kernel<false, false, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
                                    (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
             CDS_LAUNCHED(ctx);
@@ -2749,11 +2856,11 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
                 CdsTimer tp;
                 if (ctx->kernel_timing) CDS_CALL(cds_timer_start(ctx, &tp));
                 if (pass16)
-                    hipLaunchKernelGGL((cd_pass_kernel<true, false>), grid, dim3(256), 0, ctx->stream,
+                    hipLaunchKernelGGL((cd_pass_kernel<true, false, 4>), grid, dim3(256), 0, ctx->stream,
                                        (const double *)L, ldl, npairs, k, (const CdState *)st, (const double *)Pc, Rc,
                                        ldr, (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
                 else
-                    hipLaunchKernelGGL((cd_pass_kernel<false, false>), grid, dim3(256), 0, ctx->stream,
+                    hipLaunchKernelGGL((cd_pass_kernel<false, false, 4>), grid, dim3(256), 0, ctx->stream,
                                        (const double *)L, ldl, npairs, k, (const CdState *)st, (const double *)Pc, Rc,
                                        ldr, (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
                 CDS_LAUNCHED(ctx);
