@@ -41,7 +41,6 @@ enum CdsSlot {
     WS_AD_T1,       // adjoint: K-contiguous copies of transposed GEMM operands
     WS_AD_T2,
     WS_AD_T3,
-    WS_SG_TSEL,     // target slots of the fused self-energy launches
     WS_TR_UNPACK2,  // second set of transform batch buffers (the overlapped call's last
     WS_TR_T2,       // vectors, on the caller's stream beside the side stream's batches)
     WS_TR_B2,
@@ -227,16 +226,16 @@ struct CdsFusedPlan {
 // false when the blocks do not suit the fused kernel (alignment, K padding); p filled otherwise
 bool cds_fused_plan(int prec, int64_t nvec, int64_t ldk, int nmo, int nocc, const void *Bsel, const void *Bvo,
                     const void *Bsel_lo, const void *Bvo_lo, CdsFusedPlan *p);
-// partial sums d_part[nsc][tpt][T][2] of Sigma and Sigma' for the targets d_tsel[0..nsc) at
+// partial sums d_part[nsc][tpt][T][2] of Sigma and Sigma' for the targets s0 .. s0 + nsc - 1 at
 // d_omega[nsc][T]
 int cds_fused_sigma(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc,
-                    const int *d_tsel, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
+                    int s0, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
                     const double *eps, const double *d_omega, int T, double *d_part);
-// pole residues R[nsc][nres] (double for FP64, float otherwise) of the targets d_tsel[0..nsc); with
+// pole residues R[nsc][nres] (double for FP64, float otherwise) of the targets s0 .. s0 + nsc - 1; with
 // d_part, also the sums at d_omega0[nsc] from the stored residues, d_part[nsc][tpt][2] (the
 // layout of a sweep's partials)
 int cds_fused_residues(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc,
-                       const int *d_tsel, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
+                       int s0, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
                        const double *eps, void *R, const double *d_omega0 = nullptr, double *d_part = nullptr);
 // one Newton sweep: d_part[nactive][tpt][2] for the targets d_active at d_omega[target]; with
 // d_cnt, only the first d_cnt[0] <= nactive of them (read on the device)

@@ -486,23 +486,6 @@ int fused_chunk(const cds_ctx *ctx, const SigmaShape &sh)
     return ctx->target_chunk > 0 ? std::min(ctx->target_chunk, sh.nsel) : sh.nsel;
 }
 
-__global__ void iota_kernel(int *__restrict__ p, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = i;
-}
-
-// device list 0 .. nsel-1 of target slots (slot s0 + j of a launch is entry s0 + j)
-int target_slots(cds_ctx *ctx, int nsel, int **d_tsel)
-{
-    void *p;
-    CDS_CALL(cds_ws(ctx, WS_SG_TSEL, (size_t)nsel * 4, &p));
-    hipLaunchKernelGGL(iota_kernel, dim3((unsigned)cds_ceil_div(nsel, 256)), dim3(256), 0, ctx->stream, (int *)p, nsel);
-    CDS_LAUNCHED(ctx);
-    *d_tsel = (int *)p;
-    return CDS_OK;
-}
-
 // G for targets [s0, s0+nsc)
 int contract_chunk(cds_ctx *ctx, const SigmaShape &sh, const void *Bsel, const void *Bvo, int s0,
                    int nsc, void *G)
@@ -567,6 +550,16 @@ int launch_epilogue(cds_ctx *ctx, const SigmaShape &sh, EpArgs &e, bool fp64)
     return fp64 ? launch_epilogue_t<double, MODE>(ctx, sh, e) : launch_epilogue_t<float, MODE>(ctx, sh, e);
 }
 
+// n pairs (Sigma, Sigma') to the host; the pinned buffer holds the n energies sent and these
+int read_out(cds_ctx *ctx, const void *out, size_t n, double *h_out)
+{
+    double *hp = (double *)ctx->pinned + n;
+    CDS_HIP(ctx, hipMemcpyAsync(hp, out, n * 16, hipMemcpyDeviceToHost, ctx->stream));
+    CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    std::memcpy(h_out, hp, n * 16);
+    return CDS_OK;
+}
+
 // Sigma, Sigma' for all targets at T energies each (device omega [nsel][T]) -> host out [nsel][T][2]
 int eval_sigma(cds_ctx *ctx, const SigmaShape &sh, const void *Bsel, const void *Bvo,
                const double *eps, const double *d_omega, int T, double *h_out)
@@ -577,8 +570,6 @@ int eval_sigma(cds_ctx *ctx, const SigmaShape &sh, const void *Bsel, const void 
     if (cds_fused_plan(sh.prec, sh.nvec, sh.ldk, sh.nmo, sh.nocc, Bsel, Bvo, Slo, Vlo, &fp)) {
         // integrals formed and reduced over the denominators in one kernel (never stored)
         const int csz = fused_chunk(ctx, sh);
-        int *tsel;
-        CDS_CALL(target_slots(ctx, sh.nsel, &tsel));
         void *part, *out;
         CDS_CALL(cds_ws(ctx, WS_SG_PART, (size_t)csz * fp.tpt * T * 2 * 8, &part));
         CDS_CALL(cds_ws(ctx, WS_SG_OUT, (size_t)sh.nsel * T * 2 * 8, &out));
@@ -586,7 +577,7 @@ int eval_sigma(cds_ctx *ctx, const SigmaShape &sh, const void *Bsel, const void 
             const int nsc = std::min(csz, sh.nsel - s0);
             CdsTimer t;
             CDS_CALL(cds_timer_start(ctx, &t));
-            CDS_CALL(cds_fused_sigma(ctx, sh.prec, fp, sh.ldk, sh.nmo, sh.nocc, nsc, tsel + s0, Bsel, Bvo, Slo, Vlo,
+            CDS_CALL(cds_fused_sigma(ctx, sh.prec, fp, sh.ldk, sh.nmo, sh.nocc, nsc, s0, Bsel, Bvo, Slo, Vlo,
                                      eps, d_omega + (int64_t)s0 * T, T, (double *)part));
             CDS_CALL(cds_timer_stop(ctx, &t, &ctx->stats.t_contract_ms));
             ctx->stats.flops_contract += 2.0 * (double)sh.nvec * nsc * sh.nmo * (double)sh.nvo;
@@ -600,9 +591,7 @@ int eval_sigma(cds_ctx *ctx, const SigmaShape &sh, const void *Bsel, const void 
             CDS_LAUNCHED(ctx);
             CDS_CALL(cds_timer_stop(ctx, &t2, &ctx->stats.t_epilogue_ms));
         }
-        CDS_HIP(ctx, hipMemcpyAsync(h_out, out, (size_t)sh.nsel * T * 2 * 8, hipMemcpyDeviceToHost, ctx->stream));
-        CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
-        return CDS_OK;
+        return read_out(ctx, out, (size_t)sh.nsel * T, h_out);
     }
     // blocks the fused kernel cannot read (K padding or alignment): integrals through HBM
     const int csz = chunk_targets(ctx, sh);
@@ -638,9 +627,7 @@ int eval_sigma(cds_ctx *ctx, const SigmaShape &sh, const void *Bsel, const void 
         CDS_LAUNCHED(ctx);
         CDS_CALL(cds_timer_stop(ctx, &t, &ctx->stats.t_epilogue_ms));
     }
-    CDS_HIP(ctx, hipMemcpyAsync(h_out, out, (size_t)sh.nsel * T * 2 * 8, hipMemcpyDeviceToHost, ctx->stream));
-    CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    return CDS_OK;
+    return read_out(ctx, out, (size_t)sh.nsel * T, h_out);
 }
 
 }  // namespace
@@ -654,7 +641,11 @@ int cds_sigma_eval_internal(cds_ctx *ctx, int prec, int64_t nvec, int64_t ldk, i
                      (int64_t)(nmo - nocc) * nocc, (int64_t)nsel * nmo};
     void *om;
     CDS_CALL(cds_ws(ctx, WS_SG_OMEGA, (size_t)nsel * T * 8, &om));
-    CDS_HIP(ctx, hipMemcpyAsync(om, h_omega, (size_t)nsel * T * 8, hipMemcpyHostToDevice, ctx->stream));
+    // through pinned memory both ways: a copy from or to pageable memory waits on the host
+    void *hp;
+    CDS_CALL(cds_pinned(ctx, (size_t)nsel * T * 3 * 8, &hp));
+    std::memcpy(hp, h_omega, (size_t)nsel * T * 8);
+    CDS_HIP(ctx, hipMemcpyAsync(om, hp, (size_t)nsel * T * 8, hipMemcpyHostToDevice, ctx->stream));
     return eval_sigma(ctx, sh, Bsel, Bvo, eps, (const double *)om, T, h_out);
 }
 
@@ -769,19 +760,22 @@ extern "C" int cds_qp_solve(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ld
         nd.cnt = nd.sel + nsel;
         nd.act = (int *)act;
         om = nd.om;
-        CDS_HIP(ctx, hipMemcpyAsync(nd.sel, h_sel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
-        if (h_omega0)
-            CDS_HIP(ctx, hipMemcpyAsync(om, h_omega0, (size_t)nsel * 8, hipMemcpyHostToDevice, ctx->stream));
+        // through the pinned buffer (its first reader below is a later copy of the same stream)
+        int32_t *hsel = (int32_t *)((double *)hp + nsel);
+        std::memcpy(hsel, h_sel, (size_t)nsel * 4);
+        CDS_HIP(ctx, hipMemcpyAsync(nd.sel, hsel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
+        if (h_omega0) {
+            std::memcpy(hp, h_omega0, (size_t)nsel * 8);
+            CDS_HIP(ctx, hipMemcpyAsync(om, hp, (size_t)nsel * 8, hipMemcpyHostToDevice, ctx->stream));
+        }
         hipLaunchKernelGGL(newton_init_kernel, dim3(1), dim3(256), 0, ctx->stream, nsel, eps, h_omega0 ? 1 : 0, nd);
         CDS_LAUNCHED(ctx);
         const int csz = fused_chunk(ctx, sh);
-        int *tsel;
-        CDS_CALL(target_slots(ctx, nsel, &tsel));
         for (int s0 = 0; s0 < nsel; s0 += csz) {
             const int nsc = std::min(csz, nsel - s0);
             CdsTimer t;
             CDS_CALL(cds_timer_start(ctx, &t));
-            CDS_CALL(cds_fused_residues(ctx, prec, fp, ldk, nmo, nocc, nsc, tsel + s0, Bsel, Bvo, Slo, Vlo, eps,
+            CDS_CALL(cds_fused_residues(ctx, prec, fp, ldk, nmo, nocc, nsc, s0, Bsel, Bvo, Slo, Vlo, eps,
                                         (unsigned char *)R + (size_t)s0 * fp.nres * res_es, (const double *)om + s0,
                                         (double *)part + (size_t)s0 * nblk_sweep * 2));
             CDS_CALL(cds_timer_stop(ctx, &t, &ctx->stats.t_contract_ms));
@@ -982,11 +976,11 @@ extern "C" int cds_sigma2_noalloc(cds_ctx *ctx, int32_t prec, int64_t nvec, int6
                 "K stage (16 FP64, 32 FP32 / BF16X3) and ldk * element size a multiple of 16");
     if (!ctx->scratch) return cds_fail(ctx, CDS_ESTATE, "no device address for the scratch array");
     // scratch layout: partials [csz][tpt][T][2], sigma [nsel][T], dsigma [nsel][T],
-    // trial energies [nsel][T], target slots [nsel]
+    // trial energies [nsel][T]
     const int csz = fused_chunk(ctx, sh);
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t b_part = up((size_t)csz * fp.tpt * T * 2 * 8), b_nt = up((size_t)nsel * T * 8);
-    const size_t need = b_part + 3 * b_nt + up((size_t)nsel * 4);
+    const size_t need = b_part + 3 * b_nt + up((size_t)nsel * 4);   // (the documented bound)
     CDS_REQUIRE(ctx, need <= (size_t)CDS_NOALLOC_SCRATCH_BYTES,
                 "allocation-free path: %zu bytes of scratch needed, %d available (fewer targets per "
                 "launch, see cds_set_target_chunk, or fewer trial energies)",
@@ -995,13 +989,10 @@ extern "C" int cds_sigma2_noalloc(cds_ctx *ctx, int32_t prec, int64_t nvec, int6
     double *part = (double *)sp;
     double *sig = (double *)(sp + b_part), *dsig = (double *)(sp + b_part + b_nt);
     double *om = (double *)(sp + b_part + 2 * b_nt);
-    int *tsel = (int *)(sp + b_part + 3 * b_nt);
     CDS_HIP(ctx, hipMemcpyAsync(om, h_omega, (size_t)nsel * T * 8, hipMemcpyHostToDevice, ctx->stream));
-    hipLaunchKernelGGL(iota_kernel, dim3((unsigned)cds_ceil_div(nsel, 256)), dim3(256), 0, ctx->stream, tsel, nsel);
-    CDS_LAUNCHED(ctx);
     for (int s0 = 0; s0 < nsel; s0 += csz) {
         const int nsc = std::min(csz, nsel - s0);
-        CDS_CALL(cds_fused_sigma(ctx, prec, fp, ldk, nmo, nocc, nsc, tsel + s0, Bsel, Bvo, Slo, Vlo, eps,
+        CDS_CALL(cds_fused_sigma(ctx, prec, fp, ldk, nmo, nocc, nsc, s0, Bsel, Bvo, Slo, Vlo, eps,
                                  om + (int64_t)s0 * T, T, part));
         const int nout = nsc * T * 2;
         hipLaunchKernelGGL(reduce_split_kernel, dim3((unsigned)nout), dim3(256), 0, ctx->stream,

@@ -77,7 +77,7 @@ struct FArgs {
     int64_t ns;                                 // K stages (the sum runs over ns * KS entries)
     int nmo, nocc, nvirt;
     int nsc;                                    // targets of this launch
-    const int *tsel;                            // [nsc] target slot (row block of Bsel)
+    int s0;                                     // first target (row block of Bsel) of this launch
     int nTA, nTB, nPA, nPB;                     // tiles and tile pairs of parts A and B
     int nLA, nLB;                               // tile pairs per fixed index in this launch
     int64_t tpt;                                // tasks per target
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
     const Task k = task_of_launch<DG>(a, tid);
     constexpr bool diag = DG;
     const int n = k.fam ? a.nvirt : a.nocc;
-    const int s = a.tsel[k.sl];
+    const int s = a.s0 + k.sl;
     const int64_t pb = (int64_t)s * a.nmo + (k.fam ? a.nocc : 0);     // P row r: Bsel row pb + r
     const int64_t qb = k.fam ? (int64_t)k.idx : (int64_t)k.idx * a.nocc;
     const int64_t qs = k.fam ? a.nocc : 1;                            // Q row c: Bvo row qb + c qs
@@ -661,7 +661,7 @@ bool cds_fused_plan(int prec, int64_t nvec, int64_t ldk, int nmo, int nocc, cons
     return true;
 }
 
-static FArgs fused_args(int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc, const int *tsel,
+static FArgs fused_args(int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc, int s0,
                         const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
                         const double *eps)
 {
@@ -676,7 +676,7 @@ static FArgs fused_args(int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, i
     a.nocc = nocc;
     a.nvirt = nmo - nocc;
     a.nsc = nsc;
-    a.tsel = tsel;
+    a.s0 = s0;
     a.nTA = p.nTA;
     a.nTB = p.nTB;
     a.nPA = p.nPA;
@@ -728,10 +728,10 @@ static int launch_fused(cds_ctx *ctx, int prec, const FArgs &a, int T)
 }
 
 int cds_fused_sigma(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc,
-                    const int *d_tsel, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
+                    int s0, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
                     const double *eps, const double *d_omega, int T, double *d_part)
 {
-    FArgs a = fused_args(prec, p, ldk, nmo, nocc, nsc, d_tsel, Bsel, Bvo, Bsel_lo, Bvo_lo, eps);
+    FArgs a = fused_args(prec, p, ldk, nmo, nocc, nsc, s0, Bsel, Bvo, Bsel_lo, Bvo_lo, eps);
     a.omega = d_omega;
     a.T = T;
     a.part = d_part;
@@ -739,10 +739,10 @@ int cds_fused_sigma(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int64_t ldk, 
 }
 
 int cds_fused_residues(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int64_t ldk, int nmo, int nocc, int nsc,
-                       const int *d_tsel, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
+                       int s0, const void *Bsel, const void *Bvo, const void *Bsel_lo, const void *Bvo_lo,
                        const double *eps, void *R, const double *d_omega0, double *d_part)
 {
-    FArgs a = fused_args(prec, p, ldk, nmo, nocc, nsc, d_tsel, Bsel, Bvo, Bsel_lo, Bvo_lo, eps);
+    FArgs a = fused_args(prec, p, ldk, nmo, nocc, nsc, s0, Bsel, Bvo, Bsel_lo, Bvo_lo, eps);
     a.R = R;
     if (!d_part) return launch_fused<1>(ctx, prec, a, 1);
     a.omega = d_omega0;
@@ -755,7 +755,7 @@ int cds_fused_sweep(cds_ctx *ctx, int prec, const CdsFusedPlan &p, int nmo, int 
                     const int *d_active, const double *eps, const double *d_omega, const void *R, double *d_part,
                     const int *d_cnt)
 {
-    FArgs a = fused_args(prec, p, 0, nmo, nocc, 1, nullptr, nullptr, nullptr, nullptr, nullptr, eps);
+    FArgs a = fused_args(prec, p, 0, nmo, nocc, 1, 0, nullptr, nullptr, nullptr, nullptr, eps);
     a.omega = d_omega;
     a.R = const_cast<void *>(R);
     a.part = d_part;
