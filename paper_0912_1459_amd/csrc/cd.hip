@@ -11,7 +11,8 @@
 // blocks that start at step k0:
 //     cd_cand    the pivot of step k0 plus the rows with the largest residual
 //                diagonals (CD_NCAND candidates in all)
-//     cd_candcol R[c][I] = V[I][cand_c]                               (ERI columns)
+//     cd_candcol R[c][I] = V[I][cand_c]                               (ERI columns; small path on
+//                demand: cd_lockstep's, for the columns that become pivots)
 //     cd_gather  P[j][c] = L[j][cand_c]                               j < k0
 //     cd_pass    R[c][I] -= sum_{j<k0} L[j][I] P[j][c]                (one read of L,
 //                FP64 MFMA)
@@ -167,30 +168,43 @@ __device__ __forceinline__ double okey_min(unsigned long long u)
     return okey_max(u);
 }
 
-// F0(T) = (1/2) sqrt(pi / T) erf(sqrt T) = (sqrt(pi) / 2) erf(t) / t with t = sqrt T (one
-// square root, one division); the series near T = 0
-__device__ __forceinline__ double boys_f0(double T)
-{
-#pragma clang fp contract(off)
-    if (T < 1e-12) return 1.0 - T / 3.0 + T * T / 10.0;
-    const double t = sqrt(T);
-    return 0.88622692545275801365 * erf(t) / t;           // sqrt(pi) / 2
-}
+// (rho_I | V | rho_J) for two s-Gaussian product densities, f F0(T) with t = sqrt T.  No implicit
+// contraction: the fused multiply-adds are written out, so every kernel that inlines it forms the
+// same value (the speculative path relies on the candidates' block and the pass agreeing bit for
+// bit).  In two halves of about the same length, for the lockstep kernel.
+struct EriHead {
+    double f, T, t;
+};
 
-// (rho_I | V | rho_J) for two s-Gaussian product densities.  No implicit contraction: the fused
-// multiply-adds are written out, so every kernel that inlines it forms the same value (the
-// speculative path relies on the candidates' block and the pass agreeing bit for bit).
-__device__ __forceinline__ double eri_pp(double p, double Px, double Py, double Pz, double Kp,
-                                         double q, double Qx, double Qy, double Qz, double Kq)
+__device__ __forceinline__ EriHead eri_head(double p, double Px, double Py, double Pz, double Kp,
+                                            double q, double Qx, double Qy, double Qz, double Kq)
 {
 #pragma clang fp contract(off)
     const double two_pi_52 = 2.0 * 17.493418327624862;   // 2 pi^(5/2)
     const double dx = Px - Qx, dy = Py - Qy, dz = Pz - Qz;
     const double r2 = fma(dz, dz, fma(dy, dy, dx * dx));
     const double s = p + q, pq = p * q;
-    const double e = 1.0 / (pq * s);                        // one division for both factors
-    const double T = pq * pq * e * r2;                      // p q / (p + q) * r2
-    return Kp * Kq * two_pi_52 * sqrt(s) * e * boys_f0(T);  // ... / (p q sqrt(p + q))
+    const double e = 1.0 / (pq * s);                     // one division for both factors
+    EriHead h;
+    h.T = pq * pq * e * r2;                              // p q / (p + q) * r2
+    h.f = Kp * Kq * two_pi_52 * sqrt(s) * e;             // ... / (p q sqrt(p + q))
+    h.t = sqrt(h.T);
+    return h;
+}
+
+// F0(T) = (1/2) sqrt(pi / T) erf(sqrt T) = (sqrt(pi) / 2) erf(t) / t (one square root, one
+// division); the series near T = 0
+__device__ __forceinline__ double eri_tail(const EriHead &h)
+{
+#pragma clang fp contract(off)
+    if (h.T < 1e-12) return h.f * (1.0 - h.T / 3.0 + h.T * h.T / 10.0);
+    return h.f * (0.88622692545275801365 * erf(h.t) / h.t);   // sqrt(pi) / 2
+}
+
+__device__ __forceinline__ double eri_pp(double p, double Px, double Py, double Pz, double Kp,
+                                         double q, double Qx, double Qy, double Qz, double Kq)
+{
+    return eri_tail(eri_head(p, Px, Py, Pz, Kp, q, Qx, Qy, Qz, Kq));
 }
 
 __global__ void pair_setup_kernel(int32_t nbf, const double *__restrict__ centres,
@@ -633,7 +647,7 @@ __global__ __launch_bounds__(CD_NT) void cd_step_kernel(
     CdBufs b, CdParams cp, int r, int sr, int sw, int sz, int64_t k, int64_t k0, int bsteps,
     PairTable pt, const double *__restrict__ V, int64_t ldv, double *__restrict__ L, int64_t ldl,
     const double *__restrict__ R, int64_t ldr, const int64_t *__restrict__ cand, CdState *st,
-    int64_t *__restrict__ piv, const SpecOut *__restrict__ sov)
+    int64_t *__restrict__ piv, const SpecOut *__restrict__ sov, int bare)
 {
     constexpr int NR = CD_TILE * TB;            // rows per block
     constexpr int RL = NR / VW;                 // row lanes
@@ -713,13 +727,14 @@ __global__ __launch_bounds__(CD_NT) void cd_step_kernel(
     // issued before the pivot-row gather so the two loads overlap
     double cfin = 0.0;
     if (threadIdx.x < NR && If < cp.npairs && m_old != 1 && If != p) {
-        if (slot >= 0) {
-            cfin = R[(int64_t)slot * ldr + If];
-        } else if constexpr (DENSE) {
-            cfin = V[p * ldv + If];
-        } else {
-            cfin = eri_pp(pt.p[If], pt.Px[If], pt.Py[If], pt.Pz[If], pt.K[If], pt.p[p], pt.Px[p], pt.Py[p],
-                          pt.Pz[p], pt.K[p]);
+        // bare: R holds what the pass subtracts from the integrals, not the difference
+        if (slot >= 0) cfin = R[(int64_t)slot * ldr + If];
+        if constexpr (DENSE) {
+            if (slot < 0) cfin = V[p * ldv + If];
+        } else if (slot < 0 || bare) {
+            const double v = eri_pp(pt.p[If], pt.Px[If], pt.Py[If], pt.Pz[If], pt.K[If], pt.p[p], pt.Px[p], pt.Py[p],
+                                    pt.Pz[p], pt.K[p]);
+            cfin = slot >= 0 ? v - cfin : v;
         }
     }
     double acc[VW];
@@ -838,8 +853,8 @@ __global__ __launch_bounds__(CD_NT) void cd_step_kernel(
             st->dmax = pk.mx;
             if (bsteps > 0 && slot < 0) st->nmiss += 1;
             // per row: 8 B per vector subtracted; D, mask read and written and L_k written
-            // (34 B); the column entry from R or V (8 B) or the pair table (40 B, on demand)
-            const double col = (slot >= 0 || DENSE) ? 8.0 : 40.0;
+            // (34 B); the column entry from R or V (8 B) or the pair table (40 B, on demand), or both
+            const double col = slot >= 0 ? (bare ? 48.0 : 8.0) : DENSE ? 8.0 : 40.0;
             st->bytes += (double)cp.npairs * (8.0 * (double)(k - (slot >= 0 ? k0 : 0)) + 26.0 + col);
         }
     }
@@ -912,21 +927,28 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// one lane's column of a block: candidate (SpecWave) or row (RowWave) I, its residual, its mask and
+// its entries of the block's vectors.  A wave is one or the other, so both share the registers.
+struct LaneCol {
+    int64_t I;
+    double d;
+    unsigned char m;
+    double l[CD_SPEC_MAX];
+};
+
 // The speculative block, run by one wave (threads 0..63 of the workgroup; no workgroup
 // barrier inside): lane c = candidate c, its column of the speculated vectors in registers
-// (lc), the pivot's entries through LDS.  init() loads the block; step(j) forms step j (a
+// (LaneCol), the pivot's entries through LDS.  init() loads the block; step(j) forms step j (a
 // no-op once the block has ended), with j a compile-time constant (unrolled callers);
-// finish() writes every field of `out` but viol.
+// records() writes the fields of `out` that the commit reads.
 struct SpecWave {
-    int64_t k0, I;
+    int64_t k0;
     int nmax, nspec, stop_at;
     bool have, alive;
-    double d, dnc;
-    unsigned char m;
-    double lc[CD_SPEC_MAX];
+    double dnc;
 
     __device__ __forceinline__ void init(const CdBufs &b, const CdParams &cp, const int64_t *__restrict__ cand,
-                                         const CdState *st, SpecLds &sm)
+                                         const CdState *st, SpecLds &sm, LaneCol &x)
     {
         k0 = st->k;
         const int r = (int)((k0 - cp.nvec_in) & 1);
@@ -934,9 +956,9 @@ struct SpecWave {
         const int l = threadIdx.x;
         const int nc = st->ncand;
         have = l < nc;
-        I = have ? cand[l] : -1;
-        d = have ? b.D[r][I] : 0.0;
-        m = have ? b.mask[r][I] : 1;
+        x.I = have ? cand[l] : -1;
+        x.d = have ? b.D[r][x.I] : 0.0;
+        x.m = have ? b.mask[r][x.I] : 1;
         // the candidates' 64 x 64 residual block (compact, written by the pass or, on the large
         // path, by cd_cc_kernel), 32 loads in flight
         {
@@ -952,7 +974,7 @@ struct SpecWave {
             sm.ssq[l] = sm.scm[l] = sm.sth[l] = 0.0;
         }
 #pragma unroll
-        for (int j = 0; j < CD_SPEC_MAX; ++j) lc[j] = 0.0;
+        for (int j = 0; j < CD_SPEC_MAX; ++j) x.l[j] = 0.0;
         nspec = 0;
         alive = true;                                     // uniform over the wave
         // steps whose tie threshold stays above every non-candidate residual stand for sure
@@ -961,8 +983,11 @@ struct SpecWave {
         stop_at = nmax;
     }
 
-    __device__ __forceinline__ void step(int j, const CdParams &cp, SpecLds &sm)
+    __device__ __forceinline__ void step(int j, const CdParams &cp, SpecLds &sm, LaneCol &x)
     {
+        const int64_t I = x.I;
+        double d = x.d;
+        unsigned char m = x.m;
         const int l = threadIdx.x;
         if (j >= nmax) alive = false;
         if (!alive) return;
@@ -993,7 +1018,7 @@ struct SpecWave {
         double c = sm.Rcc[slot][l];
         const double *lp = &sm.Lt[slot][0];                                         // L[k0+i][p_j]
 #pragma unroll
-        for (int i = 0; i < j; ++i) c = fma(-lc[i], lp[i], c);
+        for (int i = 0; i < j; ++i) c = fma(-x.l[i], lp[i], c);
         double lj;
         if (m == 1) {
             lj = 0.0;
@@ -1005,7 +1030,9 @@ struct SpecWave {
             lj = c / sq;
             d = fma(-lj, lj, d);
         }
-        lc[j] = lj;
+        x.l[j] = lj;
+        x.d = d;
+        x.m = m;
         sm.Lt[l][j] = lj;
         wave_lds_sync();
         if (l == 0) {
@@ -1034,17 +1061,6 @@ struct SpecWave {
             out.pad = 0;
             out.k0 = k0;
         }
-    }
-
-    // the records and lpiv[i][j] = L[k0+i][p_j] = Lt[slot of p_j][i] (for the row updates)
-    __device__ __forceinline__ void finish(const SpecLds &sm, SpecOut &out) const
-    {
-        const int l = threadIdx.x;
-        for (int q = l; q < CD_SPEC_MAX * CD_SPEC_MAX; q += 64) {
-            const int i = q / CD_SPEC_MAX, j = q % CD_SPEC_MAX;
-            out.lpiv[i][j] = (i < j && j < nspec) ? sm.Lt[sm.ssj[j]][i] : 0.0;
-        }
-        records(sm, out);
     }
 };
 
@@ -1351,16 +1367,15 @@ __global__ __launch_bounds__(256) void cd_rows_kernel(CdBufs b, CdParams cp, con
 // multiply-adds as SpecWave::step, so the candidates' rows agree with the speculative wave bit
 // for bit; D_j[I] and the checks of step j as the right-looking row update.
 struct RowWave {
-    int64_t I;
     bool ok;
-    unsigned char m;
-    double d;
     unsigned long long viol;
-    double lr[CD_SPEC_MAX];   // L_i[I], i < j
 
     __device__ __forceinline__ void step(int j, const CdParams &cp, const SpecLds &sm, double rpj, double *__restrict__ L,
-                                         int64_t ldl, int64_t k0, double *__restrict__ Dbuf)
+                                         int64_t ldl, int64_t k0, double *__restrict__ Dbuf, LaneCol &x)
     {
+        const int64_t I = x.I;
+        double d = x.d;
+        unsigned char m = x.m;
         const int64_t pj = sm.spj[j];
         const int slot = sm.ssj[j];
         const double sq = sm.ssq[j];
@@ -1377,11 +1392,13 @@ struct RowWave {
             double c = rpj;
             const double *lp = &sm.Lt[slot][0];
 #pragma unroll
-            for (int i = 0; i < j; ++i) c = fma(-lr[i], lp[i], c);
+            for (int i = 0; i < j; ++i) c = fma(-x.l[i], lp[i], c);
             lj = c / sq;
             d = fma(-lj, lj, d);
         }
-        lr[j] = lj;
+        x.l[j] = lj;
+        x.d = d;
+        x.m = m;
         if (ok) {
             L[(k0 + j) * ldl + I] = lj;
             if (j % CD_SPEC_CHUNK == CD_SPEC_CHUNK - 1) Dbuf[(int64_t)j * cp.npairs + I] = d;
@@ -1401,61 +1418,121 @@ constexpr int CD_LS_ROWS = 128;
 struct LockLds {
     SpecLds sp;
     double Rs[CD_NCAND][CD_LS_ROWS];   // Rs[c][t] = R[c][row t of the workgroup]
+    double cp5[5][CD_NCAND];           // the candidates' pair data (ERI)
 };
 
-__global__ __launch_bounds__(64 + CD_LS_ROWS, 1) void cd_lockstep_kernel(CdBufs b, CdParams cp,
-                                                                       const int64_t *__restrict__ cand,
-                                                                       const CdState *st, const double *__restrict__ R,
-                                                                       int64_t ldr, double *__restrict__ L, int64_t ldl,
-                                                                       double *__restrict__ Dbuf, SpecOut *so)
+// threads: the speculative wave, two row waves and (ERI) four integral waves and an idle one
+constexpr int lockstep_threads(bool eri) { return eri ? 512 : 64 + CD_LS_ROWS; }
+static_assert(CD_LS_ROWS == 128, "two waves of rows");
+
+// ERI: R holds what the pass subtracts from the candidates' integrals.  Only the columns that
+// become pivots need the integrals, so waves of their own evaluate step j's for the workgroup's
+// rows, in place in Rs, between the speculative wave's step j and the row waves'.  An integral
+// takes about as long as a step: two pairs of waves take the steps alternately, half an integral
+// per iteration each, and the row waves run three steps behind.  Wave 4, on the speculative wave's
+// SIMD, stays idle.  28,920 pairs: the pass 72 -> 61 us per block without the integrals (14 us of
+// full-chip FP64 work in its epilogue), this kernel 39.8 -> 36.9 us with them.
+template <bool ERI>
+__global__ __launch_bounds__(lockstep_threads(ERI), 1) void cd_lockstep_kernel(
+    CdBufs b, CdParams cp, PairTable pt, const int64_t *__restrict__ cand, const CdState *st,
+    const double *__restrict__ R, int64_t ldr, double *__restrict__ L, int64_t ldl, double *__restrict__ Dbuf, SpecOut *so)
 {
+    constexpr int LAG = ERI ? 3 : 1;                     // steps the row waves are behind wave 0
     __shared__ LockLds sh;
     if (spec_idle(st)) return;
-    const bool spec = threadIdx.x < 64;
-    const int t = (int)threadIdx.x - 64;                 // row of the workgroup (row waves)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const bool spec = wave == 0, rows = wave == 1 || wave == 2, eri = ERI && !spec && !rows && wave != 4;
+    const int pair = wave == 5 || wave == 7;             // integral waves: the steps of this parity
+    // row of the workgroup: row waves 1 and 2, integral waves (3, 5) and (6, 7) 64 each
+    const int t = lane + (wave == 2 || wave >= 6 ? 64 : 0);
+    const int64_t I = (int64_t)blockIdx.x * CD_LS_ROWS + t;
     SpecWave sw;
     RowWave rw;
+    EriHead h = {};
+    LaneCol x;                                           // integral waves: l[0 .. 4] the row's pair data
     int64_t k0 = 0;
     if (spec) {
-        sw.init(b, cp, cand, st, sh.sp);
-    } else {
+        sw.init(b, cp, cand, st, sh.sp, x);
+    } else if (rows) {
+        const bool ok = I < cp.npairs;
+        const int nc = st->ncand;
         k0 = st->k;
         const int r = (int)((k0 - cp.nvec_in) & 1);
-        const int nc = st->ncand;
-        rw.I = (int64_t)blockIdx.x * CD_LS_ROWS + t;
-        rw.ok = rw.I < cp.npairs;
-        rw.m = rw.ok ? b.mask[r][rw.I] : 1;
-        rw.d = rw.ok ? b.D[r][rw.I] : 0.0;
+        rw.ok = ok;
         rw.viol = 0ull;
+        x.I = I;
+        x.m = ok ? b.mask[r][I] : 1;
+        x.d = ok ? b.D[r][I] : 0.0;
 #pragma unroll
-        for (int j = 0; j < CD_SPEC_MAX; ++j) rw.lr[j] = 0.0;
+        for (int j = 0; j < CD_SPEC_MAX; ++j) x.l[j] = 0.0;
         // all 64 loads in flight, then the LDS stores
         double v[CD_NCAND];
 #pragma unroll
-        for (int c = 0; c < CD_NCAND; ++c) v[c] = R[(int64_t)c * ldr + (rw.ok ? rw.I : 0)];
+        for (int c = 0; c < CD_NCAND; ++c) v[c] = R[(int64_t)c * ldr + (ok ? I : 0)];
 #pragma unroll
-        for (int c = 0; c < CD_NCAND; ++c) sh.Rs[c][t] = (rw.ok && c < nc) ? v[c] : 0.0;
+        for (int c = 0; c < CD_NCAND; ++c) sh.Rs[c][t] = (ok && c < nc) ? v[c] : 0.0;
+    } else if (eri) {
+        const int64_t q = I < cp.npairs ? I : 0;
+        x.l[0] = pt.p[q];
+        x.l[1] = pt.Px[q];
+        x.l[2] = pt.Py[q];
+        x.l[3] = pt.Pz[q];
+        x.l[4] = pt.K[q];
+        if (wave == 3) {
+            const int64_t c = lane < st->ncand ? cand[lane] : 0;
+            const double v[5] = {pt.p[c], pt.Px[c], pt.Py[c], pt.Pz[c], pt.K[c]};
+#pragma unroll
+            for (int i = 0; i < 5; ++i) sh.cp5[i][lane] = v[i];
+        }
     }
     __syncthreads();
-    // iteration j: wave 0 forms step j, the row waves make step j - 1; once a step is missing
-    // (read after the barrier, so the same in every wave) the rest is skipped
-    bool ended = false;
-#pragma clang loop unroll(full)
-    for (int j = 0; j <= CD_SPEC_MAX; ++j) {
-        if (ended) continue;
-        if (spec) {
-            if (j < CD_SPEC_MAX) sw.step(j, cp, sh.sp);
-        } else if (j > 0) {
-            rw.step(j - 1, cp, sh.sp, sh.Rs[sh.sp.ssj[j - 1]][t], L, ldl, k0, Dbuf);
-        }
+    // iteration j: wave 0 forms step j, the integral waves evaluate the first half of step j - 1 and
+    // the second of step j - 2, the row waves make step j - LAG; once a step is missing (read after
+    // the barrier, so the same in every wave) and the row waves have made the one before it, the
+    // rest is skipped.  Each kind of wave runs a loop of its own, with one barrier per iteration in
+    // each (the same number, as they end on the same condition): the integrals' need not be
+    // unrolled.  Unrolled with the others it took 47.8 us: every step's code passes through the
+    // instruction cache once, and the integral is the longest part of it.
+    auto last = [&](int j) {
         __syncthreads();
-        ended = j == CD_SPEC_MAX || sh.sp.spj[j] < 0;
+        const int jr = j + 1 - LAG;                      // the row waves' next step
+        return jr >= CD_SPEC_MAX || (jr >= 0 && sh.sp.spj[jr] < 0);
+    };
+    bool ended = false;
+    if (spec) {
+#pragma clang loop unroll(full)
+        for (int j = 0; j < CD_SPEC_MAX + LAG; ++j) {
+            if (ended) continue;
+            if (j < CD_SPEC_MAX) sw.step(j, cp, sh.sp, x);
+            ended = last(j);
+        }
+    } else if (rows) {
+#pragma clang loop unroll(full)
+        for (int j = 0; j < CD_SPEC_MAX + LAG; ++j) {
+            if (ended) continue;
+            if (j >= LAG) rw.step(j - LAG, cp, sh.sp, sh.Rs[sh.sp.ssj[j - LAG]][t], L, ldl, k0, Dbuf, x);
+            ended = last(j);
+        }
+    } else {
+#pragma clang loop unroll(disable)
+        for (int j = 0; !ended; ++j) {
+            const int js = ((j - 1) & 1) == pair ? j - 1 : j - 2;
+            if (eri && js >= 0 && js < CD_SPEC_MAX && sh.sp.spj[js] >= 0) {
+                const int sl = sh.sp.ssj[js];
+                if (js == j - 1)
+                    h = eri_head(x.l[0], x.l[1], x.l[2], x.l[3], x.l[4], sh.cp5[0][sl], sh.cp5[1][sl], sh.cp5[2][sl],
+                                 sh.cp5[3][sl], sh.cp5[4][sl]);
+                else
+                    sh.Rs[sl][t] = eri_tail(h) - sh.Rs[sl][t];
+            }
+            ended = last(j);
+        }
     }
-    if (!spec) {
+    if (rows) {
         unsigned long long w = rw.viol;
         for (int o = 32; o > 0; o >>= 1) w |= (unsigned long long)__shfl_xor((long long)w, o, 64);
-        if (w && (threadIdx.x & 63) == 0) atomicOr((unsigned long long *)&so->viol, w);
-    } else if (blockIdx.x == 0) {
+        if (w && lane == 0) atomicOr((unsigned long long *)&so->viol, w);
+    } else if (spec && blockIdx.x == 0) {
         sw.records(sh.sp, *so);
     }
 }
@@ -1880,13 +1957,25 @@ __global__ void cd_candcol_kernel(PairTable pt, const double *__restrict__ V, in
     candcol_body<DENSE>(pt, V, ldv, npairs, cand, nc, grp, blockIdx.x, R, ldr);
 }
 
-// the gather alone; k0 < 0: the start of the current speculative block
+// the gather alone; k0 < 0: the start of the current speculative block.  rc (else null): the first
+// CD_CCBLK workgroups evaluate the candidates' own integrals rc[c][s] = V[cand_s][cand_c] instead
+constexpr int CD_CCBLK = CD_NCAND * CD_NCAND / 256;
 template <int NC>
 __global__ void cd_gather_kernel(const double *__restrict__ L, int64_t ldl, int64_t k0, const CdState *__restrict__ st,
-                                 const int64_t *__restrict__ cand, double *__restrict__ P)
+                                 const int64_t *__restrict__ cand, double *__restrict__ P, PairTable pt,
+                                 double *__restrict__ rc)
 {
     if (spec_idle(st) || st->ncand == 0) return;
-    gather_body<NC>(L, ldl, k0 < 0 ? st->k : k0, st->ncand, cand, P, blockIdx.x, gridDim.x);
+    const int nc = st->ncand;
+    const int cc = rc ? CD_CCBLK : 0;
+    if ((int)blockIdx.x < cc) {
+        const int e = (int)(blockIdx.x * 256 + threadIdx.x), c = e / CD_NCAND, s = e % CD_NCAND;
+        if (c >= nc || s >= nc) return;
+        const int64_t I = cand[s], q = cand[c];
+        rc[e] = eri_pp(pt.p[I], pt.Px[I], pt.Py[I], pt.Pz[I], pt.K[I], pt.p[q], pt.Px[q], pt.Py[q], pt.Pz[q], pt.K[q]);
+        return;
+    }
+    gather_body<NC>(L, ldl, k0 < 0 ? st->k : k0, nc, cand, P, blockIdx.x - cc, gridDim.x - cc);
 }
 
 // one launch for both, at the start of the current speculative block (they need only the
@@ -1928,19 +2017,19 @@ __global__ void cd_candcol_gather_kernel(PairTable pt, const double *__restrict_
 // candidates of P at once (16 bytes), half the load instructions of one row each; the MFMA
 // row (column) r16 of block 2u + h is then tile row (candidate) 32u + 2 r16 + h.  Each output
 // takes the same products in the same order either way.
-// NN: groups of 16 candidates per workgroup, blockIdx.y takes the next NN (4: all 64; 1 where the
-// rows alone are too few workgroups to hide the epilogue's integrals: 820 pairs, 13 workgroups of
-// 16 integrals per thread, 21.5 us per block; 52 of 4, 8.4 us).  The same values either way.
-// ERI: R holds nothing yet; the epilogue evaluates the candidate columns' integrals V[I][cand_c]
-// itself (the values the column kernel would have stored, bit for bit), which saves writing R and
-// reading it back (2 x 8 x npairs x 64 bytes per block).
+// NN: groups of 16 candidates per workgroup, blockIdx.y takes the next NN: 4 (all 64, L is read once)
+// or, up to CD_PASS_SPLIT tiles, 1, where the tiles alone leave CUs idle (whole decompositions at
+// 820 / 4,095 / 8,001 pairs, 13 / 64 / 126 tiles: 741 / 1330 / 2371 us against 820 / 1500 / 2500 us
+// with 4).  The same values either way.
+// ERI: R receives the sums themselves, without a look at what it holds; the integrals they are
+// subtracted from are the lockstep kernel's, for the columns that need them.  Only the candidates'
+// own block is completed here (rc holds its integrals, from the gather).
 template <bool W16, bool ERI, int NN>
 __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_t ldl, int64_t npairs,
                                                          int64_t k0, const CdState *__restrict__ st,
                                                          const double *P, double *__restrict__ R,
                                                          int64_t ldr, const signed char *__restrict__ slotmap,
-                                                         double *__restrict__ rc, PairTable pt,
-                                                         const int64_t *__restrict__ cand)
+                                                         double *__restrict__ rc)
 {
     constexpr int D = CD_PASS_D;
     __shared__ double red[2][16 * NN][CD_TILE];            // red[slot][cand][row ^ cand]
@@ -2053,14 +2142,6 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
     const int row = threadIdx.x % CD_TILE;
     const int64_t I = tile0 + row;
     const int sl = I < npairs ? slotmap[I] : -1;
-    double ip = 0.0, ipx = 0.0, ipy = 0.0, ipz = 0.0, ik = 0.0;
-    if (ERI && I < npairs) {
-        ip = pt.p[I];
-        ipx = pt.Px[I];
-        ipy = pt.Py[I];
-        ipz = pt.Pz[I];
-        ik = pt.K[I];
-    }
     if (w >= 2) put(w - 2);
     __syncthreads();
     if (w < 2) add(w);
@@ -2071,16 +2152,15 @@ __global__ __launch_bounds__(256, 2) void cd_pass_kernel(const double *L, int64_
     for (int q = 0; q < CD_TILE * 16 * NN / 256; ++q) {
         const int cl = (threadIdx.x + 256 * q) / CD_TILE, c = cb + cl;
         if (c < nc && I < npairs) {
-            double base;                                           // V[I][cand_c]
+            const double sum = red[0][cl][row ^ cl] + red[1][cl][row ^ cl];
             if constexpr (ERI) {
-                const int64_t qc = cand[c];
-                base = eri_pp(ip, ipx, ipy, ipz, ik, pt.p[qc], pt.Px[qc], pt.Py[qc], pt.Pz[qc], pt.K[qc]);
+                R[(int64_t)c * ldr + I] = sum;
+                if (sl >= 0) rc[c * CD_NCAND + sl] -= sum;
             } else {
-                base = R[(int64_t)c * ldr + I];
+                const double v = R[(int64_t)c * ldr + I] - sum;    // V[I][cand_c] - ...
+                R[(int64_t)c * ldr + I] = v;
+                if (sl >= 0) rc[c * CD_NCAND + sl] = v;
             }
-            const double v = base - (red[0][cl][row ^ cl] + red[1][cl][row ^ cl]);
-            R[(int64_t)c * ldr + I] = v;
-            if (sl >= 0) rc[c * CD_NCAND + sl] = v;
         }
     }
 }
@@ -2427,11 +2507,11 @@ template <int VW, int TB, bool DENSE>
 void launch_step(cds_ctx *ctx, const CdBufs &b, const CdParams &cp, int r, int sr, int sw, int sz,
                  int64_t k, int64_t k0, int bsteps, const PairTable &pt, const double *V, int64_t ldv, double *L,
                  int64_t ldl, const double *R, int64_t ldr, const int64_t *cand, CdState *st, int64_t *piv,
-                 const SpecOut *sov)
+                 const SpecOut *sov, int bare)
 {
     const dim3 grid((unsigned)cds_ceil_div(b.ntile, TB));
     hipLaunchKernelGGL((cd_step_kernel<VW, TB, DENSE>), grid, dim3(CD_NT), 0, ctx->stream, b, cp, r, sr, sw, sz,
-                       k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov);
+                       k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov, bare);
 }
 
 // step-kernel shape: rows per thread (16-byte loads when the layout allows) and tiles per
@@ -2440,16 +2520,20 @@ template <bool DENSE>
 void launch_step_any(cds_ctx *ctx, int vw, int tb, const CdBufs &b, const CdParams &cp, int r, int sr, int sw,
                      int sz, int64_t k, int64_t k0, int bsteps, const PairTable &pt, const double *V, int64_t ldv,
                      double *L, int64_t ldl, const double *R, int64_t ldr, const int64_t *cand, CdState *st,
-                     int64_t *piv, const SpecOut *sov)
+                     int64_t *piv, const SpecOut *sov, int bare)
 {
     if (vw == 2 && tb == 4)
-        launch_step<2, 4, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov);
+        launch_step<2, 4, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov,
+                             bare);
     else if (vw == 2)
-        launch_step<2, 1, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov);
+        launch_step<2, 1, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov,
+                             bare);
     else if (tb == 4)
-        launch_step<1, 4, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov);
+        launch_step<1, 4, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov,
+                             bare);
     else
-        launch_step<1, 1, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov);
+        launch_step<1, 1, DENSE>(ctx, b, cp, r, sr, sw, sz, k, k0, bsteps, pt, V, ldv, L, ldl, R, ldr, cand, st, piv, sov,
+                             bare);
 }
 
 // The mailbox word (coherent pinned host memory, written by the device over the bus), made
@@ -2646,6 +2730,7 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
     const unsigned nlb = (unsigned)cds_ceil_div(npairs, CD_LS_ROWS);
     const bool lockstep = nlb <= (unsigned)CD_FUSE_MAXBLK && !ctx->cd_large_path;
     const bool early = spec_on && !lockstep;
+    const int bare = spec_on && lockstep && !dense;   // R without the integrals (cd_pass_kernel, ERI)
     auto queue_block = [&]() -> int {
         if (early)
             hipLaunchKernelGGL((cd_cand_kernel<CD_NCAND_L, CD_AUX_NT>), dim3(1), dim3(CD_AUX_NT), 0, ctx->stream, bf,
@@ -2658,7 +2743,7 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
         if (early) {
             const dim3 ggl((unsigned)cds_ceil_div((max_vec + CD_PASS_ZROWS) * CD_NCAND_L, 256));
             hipLaunchKernelGGL(cd_gather_kernel<CD_NCAND_L>, ggl, dim3(256), 0, ctx->stream, (const double *)L, ldl,
-                               (int64_t)-1, (const CdState *)st, (const int64_t *)cand, Pc);
+                               (int64_t)-1, (const CdState *)st, (const int64_t *)cand, Pc, pt, (double *)nullptr);
             CDS_LAUNCHED(ctx);
             CdsTimer tcc;
             if (ctx->kernel_timing) CDS_CALL(cds_timer_start(ctx, &tcc));
@@ -2709,15 +2794,16 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
             const int64_t cgx = cds_ceil_div(npairs, 256);
             const int64_t gy = cds_ceil_div(cds_ceil_div((max_vec + CD_PASS_ZROWS) * CD_NCAND, 256), cgx);
             const dim3 cgrid((unsigned)cgx, (unsigned)(CD_NCG + gy));
-            // on demand, the pass evaluates the candidate columns' integrals in its epilogue and
-            // only the gather runs before it
+            // on demand, the candidate columns' integrals come later (lockstep): only the gather and the
+            // candidates' own run before the pass
             if (dense)
                 hipLaunchKernelGGL(cd_candcol_gather_kernel<true>, cgrid, dim3(256), 0, ctx->stream, pt, V, ldv,
                                    npairs, (const CdState *)st, (const int64_t *)cand, Rc, ldr, (const double *)L,
                                    ldl, Pc);
             else
-                hipLaunchKernelGGL(cd_gather_kernel<CD_NCAND>, ggrid, dim3(256), 0, ctx->stream, (const double *)L,
-                                   ldl, (int64_t)-1, (const CdState *)st, (const int64_t *)cand, Pc);
+                hipLaunchKernelGGL(cd_gather_kernel<CD_NCAND>, dim3(ggrid.x + CD_CCBLK), dim3(256), 0, ctx->stream,
+                                   (const double *)L, ldl, (int64_t)-1, (const CdState *)st, (const int64_t *)cand, Pc,
+                                   pt, bf.rc);
             CDS_LAUNCHED(ctx);
             if (ctx->kernel_timing) CDS_CALL(cds_timer_stop(ctx, &tsp, &ctx->stats.t_cd_spec_ms));
             CdsTimer tp;
@@ -2725,31 +2811,35 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
             if (pass16 && !dense && ntile <= CD_PASS_SPLIT)
                 hipLaunchKernelGGL((cd_pass_kernel<true, true, 1>), dim3((unsigned)ntile, CD_NCAND / 16), dim3(256), 0,
                                    ctx->stream, (const double *)L, ldl, npairs, (int64_t)-1, (const CdState *)st,
-                                   (const double *)Pc, Rc, ldr, (const signed char *)bf.slot, bf.rc, pt,
-                                   (const int64_t *)cand);
+                                   (const double *)Pc, Rc, ldr, (const signed char *)bf.slot, bf.rc);
             else if (pass16 && !dense)
                 hipLaunchKernelGGL((cd_pass_kernel<true, true, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
-                                   (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
+                                   (const signed char *)bf.slot, bf.rc);
             else if (pass16)
                 hipLaunchKernelGGL((cd_pass_kernel<true, false, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
-                                   (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
+                                   (const signed char *)bf.slot, bf.rc);
             else if (!dense)
                 hipLaunchKernelGGL((cd_pass_kernel<false, true, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
-                                   (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
+                                   (const signed char *)bf.slot, bf.rc);
             else
                 hipLaunchKernelGGL((cd_pass_kernel<false, false, 4>), grid, dim3(256), 0, ctx->stream, (const double *)L,
                                    ldl, npairs, (int64_t)-1, (const CdState *)st, (const double *)Pc, Rc, ldr,
-                                   (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
+                                   (const signed char *)bf.slot, bf.rc);
             CDS_LAUNCHED(ctx);
             if (ctx->kernel_timing) CDS_CALL(cds_timer_stop(ctx, &tp, &ctx->stats.t_cd_pass_ms));
             if (hook && hook->block) CDS_CALL(hook->block(hook->user, early ? 1 : 0));
             if (ctx->kernel_timing) CDS_CALL(cds_timer_start(ctx, &tsp));
-            hipLaunchKernelGGL(cd_lockstep_kernel, dim3(nlb), dim3(64 + CD_LS_ROWS), 0, ctx->stream, bf, cp,
-                               (const int64_t *)cand, (const CdState *)st, (const double *)Rc, ldr, L, ldl, Dbuf,
-                               so);
+            if (dense)
+                hipLaunchKernelGGL(cd_lockstep_kernel<false>, dim3(nlb), dim3(lockstep_threads(false)), 0, ctx->stream,
+                                   bf, cp, pt, (const int64_t *)cand, (const CdState *)st, (const double *)Rc, ldr, L,
+                                   ldl, Dbuf, so);
+            else
+                hipLaunchKernelGGL(cd_lockstep_kernel<true>, dim3(nlb), dim3(lockstep_threads(true)), 0, ctx->stream,
+                                   bf, cp, pt, (const int64_t *)cand, (const CdState *)st, (const double *)Rc, ldr, L,
+                                   ldl, Dbuf, so);
             CDS_LAUNCHED(ctx);
         }
         if (!bf.flat) {
@@ -2787,10 +2877,10 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
             if (ctx->kernel_timing) CDS_CALL(cds_timer_start(ctx, &tk));
             if (dense)
                 launch_step_any<true>(ctx, vw, tb, bf, cp, r2, sr2, sw2, sz2, k, k, bsteps, pt, V, ldv, L, ldl, Rc,
-                                      ldr, cand, st, piv, early ? (const SpecOut *)so : nullptr);
+                                      ldr, cand, st, piv, early ? (const SpecOut *)so : nullptr, bare);
             else
                 launch_step_any<false>(ctx, vw, tb, bf, cp, r2, sr2, sw2, sz2, k, k, bsteps, pt, V, ldv, L, ldl, Rc,
-                                       ldr, cand, st, piv, early ? (const SpecOut *)so : nullptr);
+                                       ldr, cand, st, piv, early ? (const SpecOut *)so : nullptr, bare);
             CDS_LAUNCHED(ctx);
             if (ctx->kernel_timing) CDS_CALL(cds_timer_stop(ctx, &tk, &ctx->stats.t_cd_kernel_ms));
             ctx->stats.n_cd_step_launch += 1;
@@ -2842,7 +2932,7 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
                 if (k > 0) {
                     hipLaunchKernelGGL(cd_gather_kernel<CD_NCAND>, dim3((unsigned)cds_ceil_div((k + CD_PASS_ZROWS) * CD_NCAND, 256)), dim3(256),
                                        0, ctx->stream, (const double *)L, ldl, k, (const CdState *)st,
-                                       (const int64_t *)cand, Pc);
+                                       (const int64_t *)cand, Pc, pt, (double *)nullptr);
                     CDS_LAUNCHED(ctx);
                 }
                 const dim3 cgrid((unsigned)cds_ceil_div(npairs, 256), CD_NCG);
@@ -2858,11 +2948,11 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
                 if (pass16)
                     hipLaunchKernelGGL((cd_pass_kernel<true, false, 4>), grid, dim3(256), 0, ctx->stream,
                                        (const double *)L, ldl, npairs, k, (const CdState *)st, (const double *)Pc, Rc,
-                                       ldr, (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
+                                       ldr, (const signed char *)bf.slot, bf.rc);
                 else
                     hipLaunchKernelGGL((cd_pass_kernel<false, false, 4>), grid, dim3(256), 0, ctx->stream,
                                        (const double *)L, ldl, npairs, k, (const CdState *)st, (const double *)Pc, Rc,
-                                       ldr, (const signed char *)bf.slot, bf.rc, pt, (const int64_t *)cand);
+                                       ldr, (const signed char *)bf.slot, bf.rc);
                 CDS_LAUNCHED(ctx);
                 if (ctx->kernel_timing) CDS_CALL(cds_timer_stop(ctx, &tp, &ctx->stats.t_cd_pass_ms));
                 ctx->stats.n_cd_pass_launch += 1;
@@ -2876,10 +2966,10 @@ int cholesky_impl(cds_ctx *ctx, bool dense, int32_t nbf, const double *centres,
             }
             if (dense)
                 launch_step_any<true>(ctx, vw, tb, bf, cp, r2, sr2, sw2, sz2, k, k0, bsteps, pt, V, ldv, L, ldl, Rc,
-                                      ldr, cand, st, piv, nullptr);
+                                      ldr, cand, st, piv, nullptr, 0);
             else
                 launch_step_any<false>(ctx, vw, tb, bf, cp, r2, sr2, sw2, sz2, k, k0, bsteps, pt, V, ldv, L, ldl, Rc,
-                                       ldr, cand, st, piv, nullptr);
+                                       ldr, cand, st, piv, nullptr, 0);
             CDS_LAUNCHED(ctx);
             ctx->stats.n_cd_step_launch += 1;
         }
