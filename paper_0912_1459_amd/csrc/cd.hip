@@ -352,7 +352,10 @@ __device__ __forceinline__ unsigned wave_max_u32_dpp(unsigned v)
 __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k)
 {
     const unsigned hi = wave_max_u32_dpp((unsigned)(k >> 32));
-    const unsigned lo = wave_max_u32_dpp((unsigned)(k >> 32) == hi ? (unsigned)k : 0u);
+    const unsigned long long at = __ballot((unsigned)(k >> 32) == hi);
+    // one lane has it: its low half (usual); else the largest of theirs
+    const unsigned lo = __popcll(at) == 1 ? (unsigned)__builtin_amdgcn_readlane((int)k, __ffsll((long long)at) - 1)
+                                          : wave_max_u32_dpp((unsigned)(k >> 32) == hi ? (unsigned)k : 0u);
     return ((unsigned long long)hi << 32) | lo;
 }
 __device__ __forceinline__ int64_t i64_min(int64_t a, int64_t b) { return b < a ? b : a; }
@@ -992,29 +995,22 @@ struct SpecWave {
         if (j >= nmax) alive = false;
         if (!alive) return;
         const bool elig = have && m == 0;
-        const double sql = sqrt(d);                                 // off the serial path
         const double cmax = okey_max(wave_max_key(elig ? okey(d) : 0ull));   // as fmax, on integer keys
-        if (cmax == -INFINITY || cmax <= cp.delta) alive = false;   // termination: per-step path
-        if (!alive) return;
         const double thr = cmax - tie_window(cmax, cp.tau);
         if (!(thr > dnc) && j + CD_SPEC_MARGIN < stop_at) stop_at = j + CD_SPEC_MARGIN;
-        if (j >= stop_at) alive = false;
-        if (!alive) return;
         // pivot: the lowest row index within the tie window; usually one lane is in it
-        const unsigned long long win = __ballot(elig && d >= thr);
-        int64_t pm;
-        if (__popcll(win) == 1) {
-            const int wl = __ffsll((long long)win) - 1;
-            pm = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(I >> 32), wl) << 32) |
-                           (uint32_t)__builtin_amdgcn_readlane((int)(I & 0xffffffff), wl));
-        } else {
-            pm = wave_min_i64_dpp((elig && d >= thr) ? I : INT64_MAX);
-        }
-        if (win == 0 || pm == INT64_MAX) alive = false;             // non-finite residuals
+        const bool in = elig && d >= thr;
+        unsigned long long win = __ballot(in);
+        // the block ends at a termination (the per-step path's call; cmax may be -inf) and at
+        // non-finite residuals (win empty)
+        if (!(cmax > cp.delta) || j >= stop_at || win == 0) alive = false;
         if (!alive) return;
-        const unsigned long long bs = __ballot(have && I == pm);
-        const int slot = __ffsll((long long)bs) - 1;
-        const double sq = readlane_f64(sql, slot);
+        if (__popcll(win) != 1) {
+            const int64_t pm = wave_min_i64_dpp(in ? I : INT64_MAX);
+            win = __ballot(in && I == pm);
+        }
+        const int slot = __ffsll((long long)win) - 1;
+        const double sq = sqrt(readlane_f64(d, slot));              // runs beside the sum below
         double c = sm.Rcc[slot][l];
         const double *lp = &sm.Lt[slot][0];                                         // L[k0+i][p_j]
 #pragma unroll
@@ -1034,13 +1030,12 @@ struct SpecWave {
         x.d = d;
         x.m = m;
         sm.Lt[l][j] = lj;
-        wave_lds_sync();
-        if (l == 0) {
+        if (l == slot) {
             sm.ssj[j] = slot;
             sm.ssq[j] = sq;
             sm.scm[j] = cmax;
             sm.sth[j] = thr;
-            sm.spj[j] = pm;                   // step j is formed
+            sm.spj[j] = I;                    // step j is formed
         }
         nspec = j + 1;
     }
@@ -1431,7 +1426,9 @@ static_assert(CD_LS_ROWS == 128, "two waves of rows");
 // takes about as long as a step: two pairs of waves take the steps alternately, half an integral
 // per iteration each, and the row waves run three steps behind.  Wave 4, on the speculative wave's
 // SIMD, stays idle.  28,920 pairs: the pass 72 -> 61 us per block without the integrals (14 us of
-// full-chip FP64 work in its epilogue), this kernel 39.8 -> 36.9 us with them.
+// full-chip FP64 work in its epilogue), this kernel 39.8 -> 36.9 us with them.  Wave 0's latency is
+// the step time (the others wait 40 % of it): its step without the square root before the search,
+// with one branch and the pivot's lane straight from the ballot, 36.9 -> 34.3 us.
 template <bool ERI>
 __global__ __launch_bounds__(lockstep_threads(ERI), 1) void cd_lockstep_kernel(
     CdBufs b, CdParams cp, PairTable pt, const int64_t *__restrict__ cand, const CdState *st,
@@ -1504,7 +1501,8 @@ __global__ __launch_bounds__(lockstep_threads(ERI), 1) void cd_lockstep_kernel(
         for (int j = 0; j < CD_SPEC_MAX + LAG; ++j) {
             if (ended) continue;
             if (j < CD_SPEC_MAX) sw.step(j, cp, sh.sp, x);
-            ended = last(j);
+            __syncthreads();
+            ended = j + 1 - LAG >= min(sw.nspec, CD_SPEC_MAX);   // as last(j)
         }
     } else if (rows) {
 #pragma clang loop unroll(full)
