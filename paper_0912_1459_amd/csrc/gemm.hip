@@ -548,11 +548,11 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
         src[q] = mat + ((batch * sb + row * srow) * ES) + ((pc ^ (rr & 7)) * 16);
     }
     int64_t koff = 0, left = nb;                                // next stage: byte offset, stages left in its entry
-    auto stage_load = [&](int buf) __attribute__((always_inline)) {
+    auto stage_load = [&](int buf, bool all) __attribute__((always_inline)) {
         unsigned char *dst = lds + buf * GD_STAGE + sl * GD_SLICE + (4 * (wave & 3)) * 1024;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (q < nld) cds_lds_dma16(src[q] + koff, dst + q * 1024);
+            if (all || q < nld) cds_lds_dma16(src[q] + koff, dst + q * 1024);
         koff += kstep;
         if (--left == 0) {
             left = nb;
@@ -580,12 +580,12 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
     auto run = [&](auto NAc, auto FULLc) __attribute__((always_inline)) {
         constexpr int NA = decltype(NAc)::value, NJ = 8 / NA, NV = 16 / ES;
         constexpr bool full = decltype(FULLc)::value;
-        stage_load(0);
+        stage_load(0, full);                                   // (no branches around whole tiles' loads)
         for (int64_t st = 0; st < ns; ++st) {
             __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): this wave's loads of stage st
             __builtin_amdgcn_s_barrier();                      // every wave's; and stage st - 1 is read
             asm volatile("" ::: "memory");
-            if (st + 1 < ns) stage_load((int)((st + 1) & 1));
+            if (st + 1 < ns) stage_load((int)((st + 1) & 1), full);
             const unsigned char *cur = lds + (st & 1) * GD_STAGE;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
