@@ -9,7 +9,8 @@
 // Since G = Bsel Bvo^T, with W = dSigma/dG and the scale omega_bar_s P_s of each target:
 //   Bsel_bar[s] = scale_s W[s] Bvo
 //   Bvo_bar     = sum_s W[s]^T (scale_s Bsel[s])
-// and the energies enter through the denominators and e_q itself.  Only W^T is written, [v][(s, r)]:
+// and the energies enter through the denominators and e_q itself (FP32: the scale is in the stored
+// weights).  Only W^T is written, [v][(s, r)]:
 // the first product reads it m-contiguous, the second K-contiguous.
 // Transform adjoint: B^K = C^T L^K C gives C_bar = sum_K L^K C (Bbar^K + Bbar^K^T).  Bbar has only the
 // rows of the targets and the virtual-occupied block, so with the rows x = occupied orbitals and
@@ -80,6 +81,7 @@ struct WArgs {
     int nmo, nocc, nvirt;
     int64_t nvo, ldw;
     const double *eps, *omega;      // omega: [sc]
+    const double *scale;            // [sc], or null: the weights' factor
     double *epsA;           // [sc][nvirt][nocc + 1]: part A by virtual a: each e_i, then e_a
     double *epsBi;          // [sc][pairs of virtual tiles][nocc]: part B, each e_i
     double *epsBv;          // [sc][pairs][2 * WB]: part B, e_a of the pair's two tiles
@@ -101,7 +103,7 @@ __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
         eo[i] = e.eps[i];
         ei[i] = 0.0;
     }
-    const double d0 = e.omega[s] + e.eps[nocc + a];
+    const double d0 = e.omega[s] + e.eps[nocc + a], gs = e.scale ? e.scale[s] : 1.0;
     const GT *G = (const GT *)e.G + (int64_t)s * e.nmo * e.nvo + (int64_t)a * nocc;     // + i*nvo + j
     GT *WT = (GT *)e.WT + (int64_t)a * nocc * e.ldw + (int64_t)s * e.nmo;               // + j*ldw + i
     double ea = 0.0;
@@ -134,10 +136,10 @@ __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
                 const double id = in ? 1.0 / (d0 - eo[i] - eo[j]) : 0.0;
                 const double uu = (2.0 * x - xt) * x, ut = (2.0 * xt - x) * xt;
                 tv[u] = in ? (uu + ut) * id * id : 0.0;
-                wv[u] = (4.0 * xt - 2.0 * x) * id;
+                wv[u] = gs * (4.0 * xt - 2.0 * x) * id;
                 // off the diagonal tile both partners are counted here
                 ea -= in ? (IB == JB ? uu : uu + ut) * id * id : 0.0;
-                if (in) WT[(int64_t)j * e.ldw + i] = (GT)((4.0 * x - 2.0 * xt) * id);
+                if (in) WT[(int64_t)j * e.ldw + i] = (GT)(gs * (4.0 * x - 2.0 * xt) * id);
             }
             __syncthreads();
 #pragma unroll
@@ -194,7 +196,7 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
     double ea[WB];                                                   // e_a of the pair's first tile
     for (int a = 0; a < WB; ++a) ea[a] = 0.0;
     double eb = 0.0;                                                 // e_b, b = b0 + hi
-    const double w0 = e.omega[s], vb = ev[min(b0 + hi, nvirt - 1)];
+    const double w0 = e.omega[s], vb = ev[min(b0 + hi, nvirt - 1)], gs = e.scale ? e.scale[s] : 1.0;
     for (int i0 = 0; i0 < nocc; i0 += WB) {
         // thread (b, i) = (hi, lo): every a of the first tile and both partners
         const int i = i0 + lo, b = b0 + hi;
@@ -217,8 +219,8 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
             si -= diag ? u : u + ut;
             ea[a] += u + ut;
             eb += u + ut;
-            y1[a * WB_A + hi * WB + lo] = (4.0 * y[a] - 2.0 * yt[a]) * id;
-            y2[a * WB_A + hi * WB + lo] = (4.0 * yt[a] - 2.0 * y[a]) * id;
+            y1[a * WB_A + hi * WB + lo] = gs * (4.0 * y[a] - 2.0 * yt[a]) * id;
+            y2[a * WB_A + hi * WB + lo] = gs * (4.0 * yt[a] - 2.0 * y[a]) * id;
         }
         sb[lo][hi] = si;
         __syncthreads();
@@ -323,7 +325,7 @@ __global__ __launch_bounds__(256) void eps_bar_kernel(const double *__restrict__
     if (threadIdx.x == 0) out[r] = acc;
 }
 
-// B[row][n] = scale[row / per] sum_b part[b][row][n] in order, n < nvec; 0 for nvec <= n < ldk
+// B[row][n] = scale[row / per] (1 without scale) sum_b part[b][row][n] in order, n < nvec; 0 for nvec <= n < ldk
 template <typename T>
 __global__ __launch_bounds__(256) void sum_scaled_kernel(const T *__restrict__ part, int nb, int64_t rows, int64_t nvec,
                                                          int64_t per, const double *__restrict__ scale,
@@ -335,7 +337,7 @@ __global__ __launch_bounds__(256) void sum_scaled_kernel(const T *__restrict__ p
     double v = 0.0;
     if (n < nvec) {
         for (int b = 0; b < nb; ++b) v += (double)part[(int64_t)b * rows * nvec + row * nvec + n];
-        v *= scale[row / per];
+        if (scale) v *= scale[row / per];
     }
     B[t] = (T)v;
 }
@@ -486,11 +488,13 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
     // K padding of the products (their stage holds 16 FP64 or 32 FP32 k): the sum over v in S parts of
     // vp (the tiles of Bsel_bar alone do not fill the chip: 360 of 512 workgroups for 480 orbitals,
     // 12 targets, 930 vectors), the sum over (s, r) to kcp.  S: the fewest rounds of 512 workgroups
-    // per part, each part adding a pass over its result
+    // per part, each part adding a pass over its result.  FP32 sums in one part: its rounding is that
+    // of one sum over v of weights rounded with their scale, so the weights pass runs a second time
+    // there, once the pole strengths are known
     const int64_t ks = es == 8 ? 16 : 32;
     auto up = [&](int64_t n) { return cds_ceil_div(n, ks) * ks; };
     int S = 1;
-    {
+    if (es == 8) {
         const int64_t tiles = cds_ceil_div((int64_t)csz * nmo, 128) * cds_ceil_div(nvec, 128);
         double best = 0.0;
         for (int c = 1; c <= 16 && (c == 1 || nvo / c >= 512); ++c) {
@@ -537,11 +541,16 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
         } else {
             hipLaunchKernelGGL(weights_a_kernel<float>, ga, dim3(256), 0, ctx->stream, w);
             hipLaunchKernelGGL(weights_b_kernel<float>, gb, dim3(256), 0, ctx->stream, w);
-            CDS_CALL(zero_cols(ctx, (float *)WT, nvo, kp, kc));
-            CDS_CALL(zero_cols(ctx, (float *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
         }
         hipLaunchKernelGGL(scale_kernel, dim3((unsigned)nsc), dim3(256), 0, ctx->stream, (const double *)w.epsA,
                            (const double *)w.epsBi, nocc, nvirt, npairs, (const double *)d_obar + s0, d_scale + s0);
+        if (es == 4) {
+            w.scale = d_scale + s0;
+            hipLaunchKernelGGL(weights_a_kernel<float>, ga, dim3(256), 0, ctx->stream, w);
+            hipLaunchKernelGGL(weights_b_kernel<float>, gb, dim3(256), 0, ctx->stream, w);
+            CDS_CALL(zero_cols(ctx, (float *)WT, nvo, kp, kc));
+            CDS_CALL(zero_cols(ctx, (float *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
+        }
         CDS_LAUNCHED(ctx);
         // Bsel_bar[s0..] = scale W Bvo :  (nsc*nmo) x nvec, reduction over nvo in S parts
         GemmDesc d1 = {};
@@ -558,11 +567,11 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
                                (int64_t)nmo, (const double *)d_scale + s0, (double *)out, ldk);
         else
             hipLaunchKernelGGL(sum_scaled_kernel<float>, gs, dim3(256), 0, ctx->stream, (const float *)part, S, kc, nvec,
-                               (int64_t)nmo, (const double *)d_scale + s0, (float *)out, ldk);
+                               (int64_t)nmo, (const double *)nullptr, (float *)out, ldk);
         CDS_LAUNCHED(ctx);
         // Bvo_bar += W^T (scale Bsel[s0..]) : nvo x nvec, reduction over nsc*nmo
         CDS_CALL(cds_transpose(ctx, (int)es, kc, nvec, (const unsigned char *)Bs + (size_t)s0 * nmo * ldk * es, ldk,
-                               BsT, kp, d_scale + s0, nmo));
+                               BsT, kp, es == 8 ? d_scale + s0 : nullptr, nmo));
         GemmDesc d2 = {};
         d2.M = nvo; d2.N = nvec; d2.K = kp; d2.batch = 1;
         d2.A = WT; d2.sAm = kp; d2.sAk = 1;
