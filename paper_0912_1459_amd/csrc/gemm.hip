@@ -317,12 +317,12 @@ __global__ __launch_bounds__(NT, PREC == CDS_PREC_FP64 ? 1 : 2) void gemm_kernel
     // epilogue: C = alpha * acc + beta * C (or the split planes of alpha * acc)
     O *C = reinterpret_cast<O *>(a.C) + batch * a.sCb;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < 4; ++j) {
+        const int64_t n = n0 + wn + 16 * j + r16;
+        if (n >= a.N) continue;
+        const int64_t no = col_off(a, n);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t n = n0 + wn + 16 * j + r16;
-            if (n >= a.N) continue;
-            const int64_t no = col_off(a, n);
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 // f32/bf16 MFMA: lane group g holds rows 4g..4g+3; f64: rows g, g+4, g+8, g+12
@@ -339,7 +339,7 @@ __global__ __launch_bounds__(NT, PREC == CDS_PREC_FP64 ? 1 : 2) void gemm_kernel
                 if (a.beta != 0.0) v += a.beta * (double)(*dst);
                 *dst = (O)v;
             }
-        }
+    }
 }
 
 // ---- large split-bf16 GEMM -------------------------------------------------------

@@ -204,14 +204,15 @@ __global__ __launch_bounds__(256) void copy_out_all_kernel(const double *__restr
     }
 }
 
-__global__ void zero_pad_kernel(int64_t nrows, int64_t ldk, int64_t nvec, int64_t kend, void *B, int prec,
-                                int64_t plane)
+__global__ void zero_pad_kernel(int64_t nvo, int64_t nselr, int64_t ldk, int64_t nvec, int64_t kend, void *Bvo, void *Bsel,
+                                int prec)
 {
-    int64_t npad = kend - nvec;
-    int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nrows * npad) return;
-    int64_t r = t / npad, c = nvec + (t - r * npad);
-    put(B, prec, r * ldk + c, plane, 0.0);
+    const int64_t npad = kend - nvec;
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= (nvo + nselr) * npad) return;
+    const int64_t r = t / npad, c = nvec + (t - r * npad);
+    if (r < nvo) put(Bvo, prec, r * ldk + c, nvo * ldk, 0.0);
+    else put(Bsel, prec, (r - nvo) * ldk + c, nselr * ldk, 0.0);
 }
 
 size_t wsize(int prec) { return prec == CDS_PREC_FP64 ? 8 : (prec == CDS_PREC_FP32 ? 4 : 4); }
@@ -379,11 +380,10 @@ int tr_setup(cds_ctx *ctx, const TrPlan &p)
 int tr_pad(cds_ctx *ctx, const TrPlan &p, int64_t nvec, int64_t kend)
 {
     if (kend > nvec) {
-        int64_t n1 = p.nvo * (kend - nvec), n2 = p.nselr * (kend - nvec);
-        hipLaunchKernelGGL(zero_pad_kernel, dim3((unsigned)cds_ceil_div(n1, 256)), dim3(256), 0, ctx->stream, p.nvo,
-                           p.ldk, nvec, kend, p.Bvo, p.prec, p.nvo * p.ldk);
-        hipLaunchKernelGGL(zero_pad_kernel, dim3((unsigned)cds_ceil_div(n2, 256)), dim3(256), 0, ctx->stream,
-                           p.nselr, p.ldk, nvec, kend, p.Bsel, p.prec, p.nselr * p.ldk);
+        // both blocks in one launch (two of them cost a small transform 2 of 57 us)
+        const int64_t n = (p.nvo + p.nselr) * (kend - nvec);
+        hipLaunchKernelGGL(zero_pad_kernel, dim3((unsigned)cds_ceil_div(n, 256)), dim3(256), 0, ctx->stream, p.nvo,
+                           p.nselr, p.ldk, nvec, kend, p.Bvo, p.Bsel, p.prec);
         CDS_LAUNCHED(ctx);
     }
     return CDS_OK;
