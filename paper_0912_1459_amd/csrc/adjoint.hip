@@ -23,6 +23,7 @@
 #include "cds_internal.h"
 
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 int cds_gemm_ex(cds_ctx *ctx, int prec, const GemmDesc &d, const void *Alo, const void *Blo);
@@ -362,29 +363,48 @@ __global__ void coef_adj_kernel(const double *__restrict__ C, int nbf, int nmo, 
     }
 }
 
-// out[z oz + kb ok + x] = in[z iz + x ix + kb] (FP64) for kb < nkb, x < nx, and 0 for nx <= x < nxp:
-// 32 x 32 tiles through LDS, every load of a thread in flight before its stores
+// out[z oz + kb ok + x] = in[z iz + x ix + kb] (FP64) for kb < nkb, x < nx, and 0 for nx <= x < nxp, for
+// the six pieces of a batch's cotangents in one launch, z running through them (gradients of 47
+// orbitals, FP32, against the full symmetric cotangent: 610 / 537 us with six launches, with one
+// launch and one copy of the solve's inputs 630 / 678 us on a slower box): 32 x 32 tiles through LDS,
+// every load of a thread in flight before its stores
+struct BarPiece {
+    const void *in;
+    int64_t iz, ix, oz, ok;
+    int nz, nx, nxp;
+    double *out;
+};
+constexpr int BAR_PIECES = 6;
+struct BarArgs {
+    BarPiece p[BAR_PIECES];
+};
+
 template <typename BT>
-__global__ __launch_bounds__(256) void bar_transpose_kernel(const BT *__restrict__ in, int64_t iz, int64_t ix, int nkb,
-                                                            int nx, int nxp, int64_t oz, int64_t ok,
-                                                            double *__restrict__ out)
+__global__ __launch_bounds__(256) void bar_transpose_kernel(BarArgs a, int nkb, int nz)
 {
     __shared__ double t[32][33];
     const int x0 = blockIdx.y * 32, k0 = blockIdx.x * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    const BT *src = in + blockIdx.z * iz;
-    double v[4];
+    for (int zz = blockIdx.z; zz < nz; zz += gridDim.z) {
+        int z = zz, q = 0;
+        while (z >= a.p[q].nz) z -= a.p[q++].nz;
+        const BarPiece &e = a.p[q];
+        if (x0 >= e.nxp) continue;                                   // (the same for the whole workgroup)
+        const BT *src = (const BT *)e.in + z * e.iz;
+        double v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int x = x0 + ty + 8 * u, k = k0 + tx;
-        v[u] = x < nx && k < nkb ? (double)src[x * ix + k] : 0.0;
-    }
+        for (int u = 0; u < 4; ++u) {
+            const int x = x0 + ty + 8 * u, k = k0 + tx;
+            v[u] = x < e.nx && k < nkb ? (double)src[x * e.ix + k] : 0.0;
+        }
+        __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[ty + 8 * u][tx] = v[u];
-    __syncthreads();
+        for (int u = 0; u < 4; ++u) t[ty + 8 * u][tx] = v[u];
+        __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k = k0 + ty + 8 * u, x = x0 + tx;
-        if (k < nkb && x < nxp) out[blockIdx.z * oz + k * ok + x] = t[tx][ty + 8 * u];
+        for (int u = 0; u < 4; ++u) {
+            const int k = k0 + ty + 8 * u, x = x0 + tx;
+            if (k < nkb && x < e.nxp) e.out[z * e.oz + k * e.ok + x] = t[tx][ty + 8 * u];
+        }
     }
 }
 
@@ -470,14 +490,16 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
     }
     double *d_omega = (double *)tp;
     double *d_obar = d_omega + nsel;
-    double *d_scale = d_obar + nsel;
-    int32_t *d_sel = (int32_t *)(d_scale + nsel);
+    int32_t *d_sel = (int32_t *)(d_obar + nsel);       // (to here: one copy from the host)
+    double *d_scale = (double *)(d_sel + nsel + nsel % 2);
     double *epsA = (double *)(tp + (small + 7) / 8 * 8);
     double *epsBi = epsA + (size_t)nsel * nvirt * (nocc + 1);
     double *epsBv = epsBi + (size_t)nsel * npairs * nocc;
-    CDS_HIP(ctx, hipMemcpyAsync(d_omega, h_omega, (size_t)nsel * 8, hipMemcpyHostToDevice, ctx->stream));
-    CDS_HIP(ctx, hipMemcpyAsync(d_obar, h_omega_bar, (size_t)nsel * 8, hipMemcpyHostToDevice, ctx->stream));
-    CDS_HIP(ctx, hipMemcpyAsync(d_sel, h_sel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
+    std::vector<unsigned char> hin((size_t)nsel * 20);
+    std::memcpy(hin.data(), h_omega, (size_t)nsel * 8);
+    std::memcpy(hin.data() + (size_t)nsel * 8, h_omega_bar, (size_t)nsel * 8);
+    std::memcpy(hin.data() + (size_t)nsel * 16, h_sel, (size_t)nsel * 4);
+    CDS_HIP(ctx, hipMemcpyAsync(d_omega, hin.data(), hin.size(), hipMemcpyHostToDevice, ctx->stream));
 
     // chunks of targets: G and W^T each nsc * nmo * nvo, at most 12 GiB each (few, large chunks: the
     // product over nvo below has only nsc * nmo / 128 tile rows)
@@ -644,18 +666,10 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
     CDS_LAUNCHED(ctx);
     const size_t bes = prec == CDS_PREC_FP64 ? 8 : 4;
     // out[z][kb][x] from the rows z * iz + x * ix of a cotangent block, columns k0 ..
-    auto bars = [&](const void *blk, int64_t row0, int64_t iz, int64_t ix, int nz, int nx, int nxp, double *out, int64_t oz,
-                    int64_t ok, int64_t k0, int nkb) -> int {
-        const dim3 g((unsigned)cds_ceil_div(nkb, 32), (unsigned)cds_ceil_div(nxp, 32), (unsigned)nz);
-        const void *src = (const unsigned char *)blk + (size_t)(row0 * ldk + k0) * bes;
-        if (prec == CDS_PREC_FP64)
-            hipLaunchKernelGGL(bar_transpose_kernel<double>, g, dim3(256), 0, ctx->stream, (const double *)src, iz * ldk,
-                               ix * ldk, nkb, nx, nxp, oz, ok, out);
-        else
-            hipLaunchKernelGGL(bar_transpose_kernel<float>, g, dim3(256), 0, ctx->stream, (const float *)src, iz * ldk,
-                               ix * ldk, nkb, nx, nxp, oz, ok, out);
-        CDS_LAUNCHED(ctx);
-        return CDS_OK;
+    auto bar = [&](const void *blk, int64_t row0, int64_t iz, int64_t ix, int nz, int nx, int nxp, double *out, int64_t oz,
+                   int64_t ok, int64_t k0) {
+        return BarPiece{(const unsigned char *)blk + (size_t)(row0 * ldk + k0) * bes, iz * ldk, ix * ldk, oz, ok, nz, nx, nxp,
+                        out};
     };
     // sum over the vectors of a batch: out[m][n] (+)= sum_kb sum_k A[m][kb][k] B[n][kb][k]
     auto summed = [&](int64_t N, int64_t K, int nkb, int64_t run, const double *A, int64_t sAm, int64_t sAb,
@@ -685,18 +699,29 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
         gt.alpha = 1.0; gt.beta = 0.0;
         CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, gt, nullptr, nullptr));
         // the cotangents with x along the rows (Zv: virtual columns a, occupied rows then targets; Zo:
-        // the targets' occupied columns), then C_bar_r += sum T Z
+        // the targets' occupied columns) and with r along the rows (Zr, Zs)
         const int64_t zs = (int64_t)nkb * xp;
-        CDS_CALL(bars(Bvo_bar, 0, nocc, 1, nvirt, nocc, xo, Zv, zs, xp, k0, nkb));
-        CDS_CALL(bars(Bsel_bar, nocc, 1, nmo, nvirt, nsel, selp, Zv + xo, zs, xp, k0, nkb));
-        CDS_CALL(bars(Bsel_bar, 0, 1, nmo, nocc, nsel, selp, Zo, (int64_t)nkb * selp, selp, k0, nkb));
+        const BarArgs ba = {{bar(Bvo_bar, 0, nocc, 1, nvirt, nocc, xo, Zv, zs, xp, k0),
+                             bar(Bsel_bar, nocc, 1, nmo, nvirt, nsel, selp, Zv + xo, zs, xp, k0),
+                             bar(Bsel_bar, 0, 1, nmo, nocc, nsel, selp, Zo, (int64_t)nkb * selp, selp, k0),
+                             bar(Bvo_bar, 0, 1, nocc, nocc, nvirt, ap, Zr, (int64_t)nkb * ap, ap, k0),
+                             bar(Bsel_bar, nocc, nmo, 1, nsel, nvirt, ap, Zs, (int64_t)nkb * cp, cp, k0),
+                             bar(Bsel_bar, 0, nmo, 1, nsel, nocc, cp - ap, Zs + ap, (int64_t)nkb * cp, cp, k0)}};
+        int nz = 0, nxm = 0;
+        for (const BarPiece &e : ba.p) {
+            nz += e.nz;
+            nxm = std::max(nxm, e.nxp);
+        }
+        const dim3 gb((unsigned)cds_ceil_div(nkb, 32), (unsigned)cds_ceil_div(nxm, 32), (unsigned)std::min(nz, 65535));
+        if (prec == CDS_PREC_FP64)
+            hipLaunchKernelGGL(bar_transpose_kernel<double>, gb, dim3(256), 0, ctx->stream, ba, nkb, nz);
+        else
+            hipLaunchKernelGGL(bar_transpose_kernel<float>, gb, dim3(256), 0, ctx->stream, ba, nkb, nz);
+        CDS_LAUNCHED(ctx);
+        // C_bar_r += sum T Z
         CDS_CALL(summed(nvirt, xp, nkb, rv, T, zs, xp, Zv, zs, xp, k0 > 0, Pv));
         CDS_CALL(summed(nocc, selp, nkb, ro, T + xo, zs, xp, Zo, (int64_t)nkb * selp, selp, k0 > 0, Po));
-        // the cotangents with r along the rows, Y[x][kb][nu] = sum_r Z[x][kb][r] C[nu][r], then
-        // C_bar_x += sum L Y
-        CDS_CALL(bars(Bvo_bar, 0, 1, nocc, nocc, nvirt, ap, Zr, (int64_t)nkb * ap, ap, k0, nkb));
-        CDS_CALL(bars(Bsel_bar, nocc, nmo, 1, nsel, nvirt, ap, Zs, (int64_t)nkb * cp, cp, k0, nkb));
-        CDS_CALL(bars(Bsel_bar, 0, nmo, 1, nsel, nocc, cp - ap, Zs + ap, (int64_t)nkb * cp, cp, k0, nkb));
+        // Y[x][kb][nu] = sum_r Z[x][kb][r] C[nu][r], then C_bar_x += sum L Y
         GemmDesc gy = {};
         gy.M = (int64_t)nocc * nkb; gy.N = np_; gy.K = ap; gy.batch = 1;
         gy.A = Zr; gy.sAm = ap; gy.sAk = 1;
