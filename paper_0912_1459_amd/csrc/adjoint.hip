@@ -345,7 +345,8 @@ __global__ __launch_bounds__(256) void sum_scaled_kernel(const T *__restrict__ p
 
 // CX[x][nu] = C[nu][sel or occupied orbital of row x] (x < nocc: occupied x; xo <= x < xo + nsel:
 // target x - xo; other rows and nu >= nbf: 0), and Ccat[nu][c] = C[nu][nocc + c] for c < nvirt,
-// C[nu][c - ap] for ap <= c < ap + nocc, else 0
+// C[nu][c - ap] for ap <= c < ap + nocc, else 0 (and 0 for nbf <= nu < np_: the product with it
+// reads np_ rows, and columns of Y that are not 0 there would meet the zeros of L as NaN)
 __global__ void coef_adj_kernel(const double *__restrict__ C, int nbf, int nmo, int nocc, int nsel,
                                 const int32_t *__restrict__ sel, int np_, int xo, int xp, int ap, int cp,
                                 double *__restrict__ CX, double *__restrict__ Ccat)
@@ -355,11 +356,11 @@ __global__ void coef_adj_kernel(const double *__restrict__ C, int nbf, int nmo, 
         const int x = (int)(t / np_), nu = (int)(t - (int64_t)x * np_);
         const int q = x < nocc ? x : (x >= xo && x < xo + nsel ? sel[x - xo] : -1);
         CX[t] = q >= 0 && nu < nbf ? C[(int64_t)nu * nmo + q] : 0.0;
-    } else if (t - n1 < (int64_t)nbf * cp) {
+    } else if (t - n1 < (int64_t)np_ * cp) {
         const int64_t u = t - n1;
         const int nu = (int)(u / cp), c = (int)(u - (int64_t)nu * cp);
         const int q = c < nmo - nocc ? nocc + c : (c >= ap && c < ap + nocc ? c - ap : -1);
-        Ccat[u] = q >= 0 ? C[(int64_t)nu * nmo + q] : 0.0;
+        Ccat[u] = q >= 0 && nu < nbf ? C[(int64_t)nu * nmo + q] : 0.0;
     }
 }
 
@@ -652,7 +653,7 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
     const size_t nzr = (size_t)nocc * kb * ap, nzs = (size_t)nsel * kb * cp;              // Zr[i][kb][a], Zs[s][kb][c]
     CDS_CALL(cds_ws(ctx, WS_AD_TMP2, (nzv + nzo + nzr + nzs) * 8, &wz));
     CDS_CALL(cds_ws(ctx, WS_AD_T1, (size_t)xp * kb * np_ * 8, &wy));                      // Y[x][kb][nu]
-    const size_t ncx = (size_t)xp * np_, nccat = (size_t)nbf * cp, nsum = (size_t)nbf * (nmo + xp);
+    const size_t ncx = (size_t)xp * np_, nccat = (size_t)np_ * cp, nsum = (size_t)nbf * (nmo + xp);
     CDS_CALL(cds_ws(ctx, WS_TR_CX, (ncx + nccat + nsum) * 8 + (size_t)nsel * 4 + 64, &wc));
     CDS_CALL(cds_ws(ctx, WS_AD_TMP, (size_t)npart * 8, &wp));
     double *Lu = (double *)wl, *T = (double *)wt, *Y = (double *)wy, *part = (double *)wp;
