@@ -449,9 +449,11 @@ __global__ __launch_bounds__(GB_NT, 1) void gemm_bf16x3_big_kernel(Args a, unsig
             wait_vm<0>();
         }
         __builtin_amdgcn_s_barrier();          // ... and every wave's
+        asm volatile("" ::: "memory");         // no LDS access moves over a barrier
         compute(cur);
         __builtin_amdgcn_s_waitcnt(0xC07F);    // lgkmcnt(0): this wave's reads of cur are done
         __builtin_amdgcn_s_barrier();          // cur may be refilled
+        asm volatile("" ::: "memory");
     }
 
     float *C = reinterpret_cast<float *>(a.C) + batch * a.sCb;

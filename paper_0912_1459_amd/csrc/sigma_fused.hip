@@ -403,9 +403,11 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
                     wait_vm<0>();
                 }
                 __builtin_amdgcn_s_barrier();         // ... and every wave's
+                asm volatile("" ::: "memory");        // no LDS access moves over a barrier
                 compute(cur, NAc, FULLc);
                 __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS reads are done
                 __builtin_amdgcn_s_barrier();         // cur may be refilled
+                asm volatile("" ::: "memory");
             };
             stage_load(lds, 0);
             step(lds, lds + STG, 0);
@@ -427,9 +429,11 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
             asm volatile("" ::: "memory");            // no LDS read moves above the barrier
             if (st + NB - 1 < ns) stage_load(lds + ((st + NB - 1) % NB) * STG, st + NB - 1);
             compute(lds + (st % NB) * STG, NAc, FULLc);
+            // lgkmcnt(0): this wave's LDS reads are done before the next barrier frees the buffer (the
+            // MFMAs that use them are not ordered against the barrier)
+            __builtin_amdgcn_s_waitcnt(0xC07F);
         }
-        __builtin_amdgcn_s_waitcnt(0xC07F);           // lgkmcnt(0): this wave's LDS reads are done
-        __builtin_amdgcn_s_barrier();                 // ... and every wave's: the ring is free
+        __builtin_amdgcn_s_barrier();                 // every wave is done: the ring is free
         asm volatile("" ::: "memory");
     };
     typedef std::integral_constant<bool, true> T_;
