@@ -79,7 +79,8 @@ struct FArgs {
     int nsc;                                    // targets of this launch
     int s0;                                     // first target (row block of Bsel) of this launch
     int nTA, nTB, nPA, nPB;                     // tiles and tile pairs of parts A and B
-    int nLA, nLB;                               // tile pairs per fixed index in this launch
+    int nLA, nLB;                               // tile pairs per fixed index in this kind of task
+    int64_t t0;                                 // first task of this launch
     int64_t tpt;                                // tasks per target
     int64_t sizeA, sizeB;                       // residue entries per virtual a / occupied i
     int64_t nres;                               // residue entries per target
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(fused_threads(DG), 4) void sigma_fused_kernel(FArgs
         const int64_t full = ((int64_t)gridDim.x / G) * G;
         if (tid < full) tid = (tid / G) * G + (tid % 8) * WG_XCD + (tid / 8) % WG_XCD;
     }
-    const Task k = task_of_launch<DG>(a, tid);
+    const Task k = task_of_launch<DG>(a, a.t0 + tid);
     constexpr bool diag = DG;
     const int n = k.fam ? a.nvirt : a.nocc;
     const int s = a.s0 + k.sl;
@@ -715,10 +716,16 @@ static int launch_kind(cds_ctx *ctx, int prec, FArgs a, int T)
     const int64_t nblk = (int64_t)a.nsc * ((int64_t)a.nocc * a.nLB + (int64_t)a.nvirt * a.nLA);
     if (nblk == 0) return CDS_OK;
     if (nblk > 0x7fffffffLL) return cds_fail(ctx, CDS_EINVAL, "fused contraction: %lld tasks", (long long)nblk);
-    if (prec == CDS_PREC_FP64) launch_fused_t<CDS_PREC_FP64, MODE, DG>(ctx, a, (unsigned)nblk, T);
-    else if (prec == CDS_PREC_FP32) launch_fused_t<CDS_PREC_FP32, MODE, DG>(ctx, a, (unsigned)nblk, T);
-    else launch_fused_t<CDS_PREC_BF16X3, MODE, DG>(ctx, a, (unsigned)nblk, T);
-    CDS_LAUNCHED(ctx);
+    // launches of 2^31 threads at most (a launch of 2^32 or more runs only their remainder, without an
+    // error: 128 occupied, 1024 virtuals, 1300 targets have 4,659,200 off-diagonal tasks)
+    constexpr int64_t most = ((int64_t)1 << 31) / fused_threads(DG);
+    for (a.t0 = 0; a.t0 < nblk; a.t0 += most) {
+        const unsigned n = (unsigned)std::min(most, nblk - a.t0);
+        if (prec == CDS_PREC_FP64) launch_fused_t<CDS_PREC_FP64, MODE, DG>(ctx, a, n, T);
+        else if (prec == CDS_PREC_FP32) launch_fused_t<CDS_PREC_FP32, MODE, DG>(ctx, a, n, T);
+        else launch_fused_t<CDS_PREC_BF16X3, MODE, DG>(ctx, a, n, T);
+        CDS_LAUNCHED(ctx);
+    }
     return CDS_OK;
 }
 
