@@ -125,6 +125,9 @@ int cds_timers_flush(cds_ctx *ctx);   // synchronizes the stream
 
 static inline int64_t cds_npairs(int64_t nbf) { return nbf * (nbf + 1) / 2; }
 __host__ __device__ static inline int64_t cds_ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// workgroups of 256 threads for n items by a kernel that strides over the grid: a launch of 2^32
+// threads or more runs only their remainder, without an error
+static inline unsigned cds_stride_grid(int64_t n) { return (unsigned)std::min<int64_t>(cds_ceil_div(n, 256), 1 << 22); }
 static inline bool cds_aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // ---- shared device helpers -------------------------------------------------

@@ -207,12 +207,12 @@ __global__ __launch_bounds__(256) void copy_out_all_kernel(const double *__restr
 __global__ void zero_pad_kernel(int64_t nvo, int64_t nselr, int64_t ldk, int64_t nvec, int64_t kend, void *Bvo, void *Bsel,
                                 int prec)
 {
-    const int64_t npad = kend - nvec;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (nvo + nselr) * npad) return;
-    const int64_t r = t / npad, c = nvec + (t - r * npad);
-    if (r < nvo) put(Bvo, prec, r * ldk + c, nvo * ldk, 0.0);
-    else put(Bsel, prec, (r - nvo) * ldk + c, nselr * ldk, 0.0);
+    const int64_t npad = kend - nvec, n = (nvo + nselr) * npad;
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)gridDim.x * 256) {
+        const int64_t r = t / npad, c = nvec + (t - r * npad);
+        if (r < nvo) put(Bvo, prec, r * ldk + c, nvo * ldk, 0.0);
+        else put(Bsel, prec, (r - nvo) * ldk + c, nselr * ldk, 0.0);
+    }
 }
 
 size_t wsize(int prec) { return prec == CDS_PREC_FP64 ? 8 : (prec == CDS_PREC_FP32 ? 4 : 4); }
@@ -382,7 +382,7 @@ int tr_pad(cds_ctx *ctx, const TrPlan &p, int64_t nvec, int64_t kend)
     if (kend > nvec) {
         // both blocks in one launch (two of them cost a small transform 2 of 57 us)
         const int64_t n = (p.nvo + p.nselr) * (kend - nvec);
-        hipLaunchKernelGGL(zero_pad_kernel, dim3((unsigned)cds_ceil_div(n, 256)), dim3(256), 0, ctx->stream, p.nvo,
+        hipLaunchKernelGGL(zero_pad_kernel, dim3(cds_stride_grid(n)), dim3(256), 0, ctx->stream, p.nvo,
                            p.nselr, p.ldk, nvec, kend, p.Bvo, p.Bsel, p.prec);
         CDS_LAUNCHED(ctx);
     }

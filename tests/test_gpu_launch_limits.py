@@ -28,3 +28,27 @@ def test_sigma_of_more_tasks_than_one_launch_holds():
     b = C.sigma2(B, eps, om, ctx=ctx)
     assert np.isfinite(a[0]).all()
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
+
+
+def _nan(*shape):
+    """Memory of this size that holds NaN goes back to the allocator."""
+    torch.cuda.empty_cache()
+    torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+
+
+def test_transform_padding_of_more_than_2_32_entries():
+    # 529 + 1564 rows of 2^21 - 3 padding entries each (17.6 GB in FP32), in one launch of both blocks
+    import paper_0912_1459_amd.core as C
+    n, nocc, nsel, nvec, ldk = 46, 23, 34, 3, 2 ** 21
+    g = torch.Generator(device="cuda").manual_seed(2)
+    L = torch.randn((nvec, n * (n + 1) // 2), generator=g, dtype=torch.float64, device="cuda")
+    Cm = torch.randn((n, n), generator=g, dtype=torch.float64, device="cuda")
+    ref = C.transform(L, nvec, Cm, nocc, np.arange(nsel), "fp32")
+    _nan(nsel * n, ldk)
+    print("transform, rows of 2^21", flush=True)
+    B = C.transform(L, nvec, Cm, nocc, np.arange(nsel), "fp32", ldk=ldk)
+    for x, r in ((B.Bsel, ref.Bsel), (B.Bvo, ref.Bvo)):
+        assert torch.equal(x[:, :nvec], r[:, :nvec])
+        assert not bool(x[:, nvec:].any())
+    del B, x
+    torch.cuda.empty_cache()
