@@ -86,7 +86,7 @@ struct WArgs {
     double *epsA;           // [sc][nvirt][nocc + 1]: part A by virtual a: each e_i, then e_a
     double *epsBi;          // [sc][pairs of virtual tiles][nocc]: part B, each e_i
     double *epsBv;          // [sc][pairs][2 * WB]: part B, e_a of the pair's two tiles
-    int npairs;
+    int npairs, p0;         // pairs of virtual tiles, first pair of this launch
 };
 
 // part A (fixed virtual a = blockIdx.x, target blockIdx.y), X[i][j] = (qi|aj), d = w + e_a - e_i - e_j:
@@ -184,7 +184,8 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
     __shared__ double y1[WB * WB_A], y2[WB * WB_A];
     __shared__ double sb[WB][WB + 1];
     const int s = blockIdx.y, nocc = e.nocc, nvirt = e.nvirt;
-    int TA = 0, p = blockIdx.x;
+    const int pr = e.p0 + (int)blockIdx.x;                           // the pair
+    int TA = 0, p = pr;
     const int nt = (nvirt + WB - 1) / WB;
     while (p >= nt - TA) p -= nt - TA++;
     const int TB = TA + p;
@@ -241,7 +242,7 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
         if (threadIdx.x < WB && i0 + (int)threadIdx.x < nocc) {
             double v = 0.0;
             for (int c = 0; c < WB; ++c) v += sb[threadIdx.x][c];
-            e.epsBi[((int64_t)s * e.npairs + blockIdx.x) * nocc + i0 + threadIdx.x] = v;
+            e.epsBi[((int64_t)s * e.npairs + pr) * nocc + i0 + threadIdx.x] = v;
         }
     }
     // e_a: over the 256 threads; e_b: over the 16 threads of b (off the diagonal: the second tile)
@@ -254,10 +255,24 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
         double v = 0.0, x = 0.0;
         for (int c = 0; c < 256; ++c) v += y1[threadIdx.x * WB_A + c];
         for (int c = 0; c < WB; ++c) x += y2[threadIdx.x * WB + c];
-        double *dst = e.epsBv + ((int64_t)s * e.npairs + blockIdx.x) * 2 * WB;
+        double *dst = e.epsBv + ((int64_t)s * e.npairs + pr) * 2 * WB;
         dst[threadIdx.x] = v;
         dst[WB + threadIdx.x] = diag ? 0.0 : x;
     }
+}
+
+// both parts for nsc targets; part B's pairs in launches of at most 2^31 threads (92,673 virtuals
+// have 2^24 pairs)
+template <typename GT>
+int weights(cds_ctx *ctx, WArgs w, int nsc)
+{
+    hipLaunchKernelGGL(weights_a_kernel<GT>, dim3((unsigned)w.nvirt, (unsigned)nsc), dim3(256), 0, ctx->stream, w);
+    constexpr int most = 1 << 23;
+    for (w.p0 = 0; w.p0 < w.npairs; w.p0 += most)
+        hipLaunchKernelGGL(weights_b_kernel<GT>, dim3((unsigned)std::min(most, w.npairs - w.p0), (unsigned)nsc), dim3(256), 0,
+                           ctx->stream, w);
+    CDS_LAUNCHED(ctx);
+    return CDS_OK;
 }
 
 // scale[s] = omega_bar_s / (1 - Sigma'_s): Sigma' is the sum of part A's e_a and part B's e_i partials
@@ -332,15 +347,15 @@ __global__ __launch_bounds__(256) void sum_scaled_kernel(const T *__restrict__ p
                                                          int64_t per, const double *__restrict__ scale,
                                                          T *__restrict__ B, int64_t ldk)
 {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= rows * ldk) return;
-    const int64_t row = t / ldk, n = t - row * ldk;
-    double v = 0.0;
-    if (n < nvec) {
-        for (int b = 0; b < nb; ++b) v += (double)part[(int64_t)b * rows * nvec + row * nvec + n];
-        if (scale) v *= scale[row / per];
+    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < rows * ldk; t += (int64_t)gridDim.x * 256) {
+        const int64_t row = t / ldk, n = t - row * ldk;
+        double v = 0.0;
+        if (n < nvec) {
+            for (int b = 0; b < nb; ++b) v += (double)part[(int64_t)b * rows * nvec + row * nvec + n];
+            if (scale) v *= scale[row / per];
+        }
+        B[t] = (T)v;
     }
-    B[t] = (T)v;
 }
 
 // CX[x][nu] = C[nu][sel or occupied orbital of row x] (x < nocc: occupied x; xo <= x < xo + nsel:
@@ -555,22 +570,18 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
         w.epsBi = epsBi + (size_t)s0 * npairs * nocc;
         w.epsBv = epsBv + (size_t)s0 * npairs * 2 * WB;
         w.npairs = npairs;
-        const dim3 ga((unsigned)nvirt, (unsigned)nsc), gb((unsigned)npairs, (unsigned)nsc);
         if (es == 8) {
-            hipLaunchKernelGGL(weights_a_kernel<double>, ga, dim3(256), 0, ctx->stream, w);
-            hipLaunchKernelGGL(weights_b_kernel<double>, gb, dim3(256), 0, ctx->stream, w);
+            CDS_CALL(weights<double>(ctx, w, nsc));
             CDS_CALL(zero_cols(ctx, (double *)WT, nvo, kp, kc));
             CDS_CALL(zero_cols(ctx, (double *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
         } else {
-            hipLaunchKernelGGL(weights_a_kernel<float>, ga, dim3(256), 0, ctx->stream, w);
-            hipLaunchKernelGGL(weights_b_kernel<float>, gb, dim3(256), 0, ctx->stream, w);
+            CDS_CALL(weights<float>(ctx, w, nsc));
         }
         hipLaunchKernelGGL(scale_kernel, dim3((unsigned)nsc), dim3(256), 0, ctx->stream, (const double *)w.epsA,
                            (const double *)w.epsBi, nocc, nvirt, npairs, (const double *)d_obar + s0, d_scale + s0);
         if (es == 4) {
             w.scale = d_scale + s0;
-            hipLaunchKernelGGL(weights_a_kernel<float>, ga, dim3(256), 0, ctx->stream, w);
-            hipLaunchKernelGGL(weights_b_kernel<float>, gb, dim3(256), 0, ctx->stream, w);
+            CDS_CALL(weights<float>(ctx, w, nsc));
             CDS_CALL(zero_cols(ctx, (float *)WT, nvo, kp, kc));
             CDS_CALL(zero_cols(ctx, (float *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
         }
@@ -583,7 +594,7 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
         d1.C = part; d1.sCm = nvec; d1.sCn = 1; d1.sCb = kc * nvec;
         d1.alpha = 1.0; d1.beta = 0.0;
         CDS_CALL(cds_gemm_ex(ctx, gprec, d1, nullptr, nullptr));
-        const dim3 gs((unsigned)cds_ceil_div(kc * ldk, 256));
+        const dim3 gs(cds_stride_grid(kc * ldk));
         void *out = (unsigned char *)Bsel_bar + (size_t)s0 * nmo * ldk * es;
         if (es == 8)
             hipLaunchKernelGGL(sum_scaled_kernel<double>, gs, dim3(256), 0, ctx->stream, (const double *)part, S, kc, nvec,

@@ -52,3 +52,31 @@ def test_transform_padding_of_more_than_2_32_entries():
         assert not bool(x[:, nvec:].any())
     del B, x
     torch.cuda.empty_cache()
+
+
+def test_adjoint_of_more_than_2_32_entries():
+    # Bsel_bar of 2116 rows of 2^21 (17.7 GB in FP32)
+    import paper_0912_1459_amd.core as C
+    from paper_0912_1459_amd import _lib as A
+    n, nocc, nsel, nvec, ldk = 46, 23, 46, 5, 2 ** 21
+    g = torch.Generator(device="cuda").manual_seed(3)
+    r = lambda rows: torch.randn((rows, 64), generator=g, dtype=torch.float32, device="cuda") * 0.02
+    S, V = r(nsel * n), r((n - nocc) * nocc)
+    S[:, nvec:] = 0
+    V[:, nvec:] = 0
+    eps = torch.cat([torch.linspace(-1.5, -0.3, nocc, dtype=torch.float64), torch.linspace(0.1, 3.0, n - nocc, dtype=torch.float64)])
+    eps, om, wb, sel = eps.cuda(), np.linspace(-0.2, 0.05, nsel), np.linspace(-1.0, 1.0, nsel), np.arange(nsel, dtype=np.int32)
+    ref = C.qp_adjoint(C.BBlocks(A.PREC_FP32, S, V, nvec, 64, n, nocc, sel), eps, om, wb)
+    SL, VL = (torch.zeros((x.shape[0], ldk), dtype=torch.float32, device="cuda") for x in (S, V))
+    SL[:, :64] = S
+    VL[:, :64] = V
+    x = torch.full((nsel * n, ldk), float("nan"), dtype=torch.float32, device="cuda")
+    del x
+    print("adjoint, rows of 2^21", flush=True)
+    got = C.qp_adjoint(C.BBlocks(A.PREC_FP32, SL, VL, nvec, ldk, n, nocc, sel), eps, om, wb)
+    for x, r in zip(got[:2], ref[:2]):
+        assert torch.equal(x[:, :nvec], r[:, :nvec])
+        assert not bool(x[:, nvec:].any())
+    assert torch.equal(got[2], ref[2])
+    del got, x, SL, VL
+    torch.cuda.empty_cache()
