@@ -253,8 +253,11 @@ __global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__
             }
         }
         __syncthreads();
-        // (a matrix that is not finite leaves here too: its comparison is false both ways)
-        if (!(red[0][0] > 1e-30 * red[1][0])) break;
+        // a matrix of infinities leaves here, undiagonalised (inf <= inf); one with a NaN does not: its
+        // rotations make the energy and the vector NaN, all of it within two sweeps (the first makes
+        // two whole rows and columns NaN, the second every pair they are in)
+        if (red[0][0] <= 1e-30 * red[1][0] || red[0][0] == 0.0) break;
+        if (sweep == 2 && red[1][0] != red[1][0]) break;
         for (int r = 0; r < m - 1; ++r) {
             // round r: (m-1, r) and ((r + i) mod (m-1), (r - i) mod (m-1)), i = 1 .. half - 1
             auto pair = [&](int i, int &p, int &q) {
