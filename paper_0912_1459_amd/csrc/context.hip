@@ -44,6 +44,7 @@ int cds_ws(cds_ctx *ctx, int slot, size_t bytes, void **out)
         hipError_t e = hipMalloc(&ctx->ws[slot], want);
         if (e != hipSuccess) {
             ctx->ws[slot] = nullptr;
+            (void)hipGetLastError();              // or the next launch check reports it
             return cds_fail(ctx, CDS_ENOMEM, "workspace slot %d: hipMalloc(%zu) failed: %s", slot,
                             want, hipGetErrorString(e));
         }

@@ -146,7 +146,14 @@ extern "C" int cds_mp2(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t ldk, in
     while (na > 1 && (size_t)na * nocc * nvo * gs > MP_CHUNK_BYTES) na = (na + 1) / 2;
     CDS_REQUIRE(ctx, (size_t)na * nocc * nvo * gs <= MP_CHUNK_BYTES, "one virtual's integrals exceed the chunk cap");
     void *Gw, *Sw;
-    CDS_CALL(cds_ws(ctx, WS_MP_G, (size_t)na * nocc * nvo * gs, &Gw));
+    // smaller chunks where the device has no room for these
+    int rc = cds_ws(ctx, WS_MP_G, (size_t)na * nocc * nvo * gs, &Gw);
+    while (rc == CDS_ENOMEM && na > 1) {
+        na = (na + 1) / 2;
+        rc = cds_ws(ctx, WS_MP_G, (size_t)na * nocc * nvo * gs, &Gw);
+    }
+    CDS_CALL(rc);
+    ctx->err.clear();
     CDS_CALL(cds_ws(ctx, WS_MP_S, ((size_t)nvirt * nvirt + 1) * 8, &Sw));
     double *S = (double *)Sw;
     double *dout = S + (size_t)nvirt * nvirt;
