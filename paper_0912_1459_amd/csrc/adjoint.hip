@@ -648,25 +648,38 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
     const int ap = up16(nvirt), cp = ap + up16(nocc);                // columns: virtual, then occupied
     // vectors per batch: the largest of the batch's arrays stays below 1 GiB
     const int64_t per = 8 * std::max<int64_t>((int64_t)nbf * np_, std::max<int64_t>((int64_t)xp * np_, (int64_t)nmo * xp));
-    const int kb = (int)std::min<int64_t>(std::min<int64_t>(nvec, 8192), std::max<int64_t>(1, (int64_t)(1ull << 30) / per));
+    int kb = (int)std::min<int64_t>(std::min<int64_t>(nvec, 8192), std::max<int64_t>(1, (int64_t)(1ull << 30) / per));
     // runs of vectors per product, so that each product launches about 1024 tiles
     auto run_of = [&](int64_t n) {
         const int64_t tiles = cds_ceil_div(nbf, 128) * cds_ceil_div(n, 128);
         return std::max<int64_t>(1, kb * tiles / 1024);
     };
-    const int64_t rv = run_of(nvirt), ro = run_of(nocc), r2 = run_of(xp);
     auto runs = [](int64_t nkb, int64_t run) { return cds_ceil_div(nkb, run); };
-    const int64_t npart = std::max({runs(kb, rv) * nbf * nvirt, runs(kb, ro) * nbf * nocc, runs(kb, r2) * nbf * xp});
+    int64_t rv, ro, r2;
+    size_t nzv, nzo, nzr, nzs;                                                          // see below
     void *wl, *wt, *wz, *wy, *wc, *wp;
-    CDS_CALL(cds_ws(ctx, WS_TR_UNPACK, (size_t)kb * nbf * np_ * 8, &wl));
-    CDS_CALL(cds_ws(ctx, WS_TR_T, (size_t)kb * nbf * xp * 8, &wt));                       // T[mu][kb][x]
-    const size_t nzv = (size_t)nvirt * kb * xp, nzo = (size_t)nocc * kb * selp;           // Zv[a][kb][x], Zo[r][kb][s]
-    const size_t nzr = (size_t)nocc * kb * ap, nzs = (size_t)nsel * kb * cp;              // Zr[i][kb][a], Zs[s][kb][c]
-    CDS_CALL(cds_ws(ctx, WS_AD_TMP2, (nzv + nzo + nzr + nzs) * 8, &wz));
-    CDS_CALL(cds_ws(ctx, WS_AD_T1, (size_t)xp * kb * np_ * 8, &wy));                      // Y[x][kb][nu]
+    auto alloc = [&]() -> int {
+        rv = run_of(nvirt), ro = run_of(nocc), r2 = run_of(xp);
+        nzv = (size_t)nvirt * kb * xp, nzo = (size_t)nocc * kb * selp;                  // Zv[a][kb][x], Zo[r][kb][s]
+        nzr = (size_t)nocc * kb * ap, nzs = (size_t)nsel * kb * cp;                     // Zr[i][kb][a], Zs[s][kb][c]
+        const int64_t npart = std::max({runs(kb, rv) * nbf * nvirt, runs(kb, ro) * nbf * nocc, runs(kb, r2) * nbf * xp});
+        CDS_CALL(cds_ws(ctx, WS_TR_UNPACK, (size_t)kb * nbf * np_ * 8, &wl));
+        CDS_CALL(cds_ws(ctx, WS_TR_T, (size_t)kb * nbf * xp * 8, &wt));                 // T[mu][kb][x]
+        CDS_CALL(cds_ws(ctx, WS_AD_TMP2, (nzv + nzo + nzr + nzs) * 8, &wz));
+        CDS_CALL(cds_ws(ctx, WS_AD_T1, (size_t)xp * kb * np_ * 8, &wy));                // Y[x][kb][nu]
+        return cds_ws(ctx, WS_AD_TMP, (size_t)npart * 8, &wp);
+    };
+    // smaller batches where the device has no room for these
+    int rc = alloc();
+    while (rc == CDS_ENOMEM && kb > 1) {
+        for (const int slot : {WS_TR_UNPACK, WS_TR_T, WS_AD_TMP2, WS_AD_T1, WS_AD_TMP}) CDS_CALL(cds_ws_release(ctx, slot));
+        kb = (kb + 1) / 2;
+        rc = alloc();
+    }
+    CDS_CALL(rc);
+    ctx->err.clear();
     const size_t ncx = (size_t)xp * np_, nccat = (size_t)np_ * cp, nsum = (size_t)nbf * (nmo + xp);
     CDS_CALL(cds_ws(ctx, WS_TR_CX, (ncx + nccat + nsum) * 8 + (size_t)nsel * 4 + 64, &wc));
-    CDS_CALL(cds_ws(ctx, WS_AD_TMP, (size_t)npart * 8, &wp));
     double *Lu = (double *)wl, *T = (double *)wt, *Y = (double *)wy, *part = (double *)wp;
     double *Zv = (double *)wz, *Zo = Zv + nzv, *Zr = Zo + nzo, *Zs = Zr + nzr;
     double *CX = (double *)wc, *Ccat = CX + ncx, *Pv = Ccat + nccat, *Po = Pv + (size_t)nbf * nvirt, *P2 = Po + (size_t)nbf * nocc;

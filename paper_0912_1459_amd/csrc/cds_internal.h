@@ -112,6 +112,8 @@ int cds_fail(cds_ctx *ctx, int code, const char *fmt, ...);
 
 // device workspace of at least `bytes` in `slot` (contents not preserved on growth)
 int cds_ws(cds_ctx *ctx, int slot, size_t bytes, void **out);
+// gives a slot's buffer back (waits for the context's streams)
+int cds_ws_release(cds_ctx *ctx, int slot);
 // pinned host scratch of at least `bytes`
 int cds_pinned(cds_ctx *ctx, size_t bytes, void **out);
 // begin context entry: checks ctx, sets device, clears the error text

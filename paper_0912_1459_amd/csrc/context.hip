@@ -28,17 +28,22 @@ int cds_enter(cds_ctx *ctx)
     return CDS_OK;
 }
 
+int cds_ws_release(cds_ctx *ctx, int slot)
+{
+    if (!ctx->ws[slot]) return CDS_OK;
+    CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    if (ctx->stream2) CDS_HIP(ctx, hipStreamSynchronize(ctx->stream2));
+    CDS_HIP(ctx, hipFree(ctx->ws[slot]));
+    ctx->ws[slot] = nullptr;
+    ctx->ws_bytes[slot] = 0;
+    return CDS_OK;
+}
+
 int cds_ws(cds_ctx *ctx, int slot, size_t bytes, void **out)
 {
     if (bytes == 0) bytes = 256;
     if (ctx->ws_bytes[slot] < bytes) {
-        if (ctx->ws[slot]) {
-            CDS_HIP(ctx, hipStreamSynchronize(ctx->stream));
-            if (ctx->stream2) CDS_HIP(ctx, hipStreamSynchronize(ctx->stream2));
-            CDS_HIP(ctx, hipFree(ctx->ws[slot]));
-            ctx->ws[slot] = nullptr;
-            ctx->ws_bytes[slot] = 0;
-        }
+        CDS_CALL(cds_ws_release(ctx, slot));
         size_t want = bytes + bytes / 8;          // grow with headroom
         want = (want + 255) & ~(size_t)255;
         hipError_t e = hipMalloc(&ctx->ws[slot], want);

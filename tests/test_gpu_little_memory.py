@@ -50,3 +50,21 @@ def test_mp2_in_smaller_chunks():
         assert ctx.workspace_bytes() < 7 << 29
         assert C.mp2_energy(B, eps, ctx=ctx) == e
     assert e == ref
+
+
+def test_transform_adjoint_in_smaller_batches():
+    # 300 functions, 60 occupied, 2000 vectors: 2.4 GB for a batch of 1398 vectors, 1.2 for 699
+    import paper_0912_1459_amd.core as C
+    n, nocc, nvec, sel = 300, 60, 2000, [58, 59, 60]
+    g = torch.Generator(device="cuda").manual_seed(4)
+    r = lambda *s: torch.randn(s, generator=g, dtype=torch.float64, device="cuda")
+    L, Cm, gs, gv = r(nvec, n * (n + 1) // 2), r(n, n), r(len(sel) * n, nvec), r((n - nocc) * nocc, nvec)
+    with C.Context(0) as ctx:
+        ref = C.transform_adjoint(L, nvec, Cm, nocc, sel, gs, gv, nvec, ctx=ctx)
+        mag = C.transform_adjoint(L.abs(), nvec, Cm.abs(), nocc, sel, gs.abs(), gv.abs(), nvec, ctx=ctx)
+    print("transform adjoint, 1.5 GiB left", flush=True)
+    with C.Context(0) as ctx, _Full(3 << 29):
+        out = C.transform_adjoint(L, nvec, Cm, nocc, sel, gs, gv, nvec, ctx=ctx)
+        assert ctx.workspace_bytes() < 3 << 29
+        assert torch.equal(C.transform_adjoint(L, nvec, Cm, nocc, sel, gs, gv, nvec, ctx=ctx), out)
+    assert bool(((out - ref).abs() <= 1e-12 * mag).all())
