@@ -75,7 +75,10 @@ __device__ __forceinline__ double block_sum(double v, double *sh)
 // Weights and energy partials of a chunk of targets.  Both kernels read every integral once, both
 // exchange partners together, and write W^T in runs of consecutive r: HBM traffic is one read of G
 // and one write of W^T.  (Separate kernels for Sigma', W with a thread per row, and a transposed
-// copy of W took 3.2 ms for 480 orbitals, 12 targets FP64; these take 1.1 ms.)
+// copy of W took 3.2 ms for 480 orbitals, 12 targets FP64; these take 1.1 ms.)  FP32 weights are
+// rounded with their scale, which needs the partials of the whole target first: two passes there,
+// the first without the weights, the second without the partials.
+enum : int { W_WEIGHTS = 1, W_PARTIALS = 2 };
 struct WArgs {
     const void *G;          // integrals of the chunk [sc][nmo][nvo]
     void *WT;               // weights [nvo][kc_pad], column s * nmo + r
@@ -93,7 +96,7 @@ struct WArgs {
 // 32 x 32 tile pairs (IB <= JB) of X and its transpose through LDS.  W_ij = (4 x - 2 x') / d; with
 // u = (2 x - x') x and t_ij = (u_ij + u_ji) / d^2 (symmetric), e_i gets sum_j t_ij and e_a
 // -sum_ij u_ij / d^2.
-template <typename GT>
+template <typename GT, int WHAT>
 __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
 {
     __shared__ double sh[4];
@@ -140,21 +143,22 @@ __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
                 wv[u] = gs * (4.0 * xt - 2.0 * x) * id;
                 // off the diagonal tile both partners are counted here
                 ea -= in ? (IB == JB ? uu : uu + ut) * id * id : 0.0;
-                if (in) WT[(int64_t)j * e.ldw + i] = (GT)(gs * (4.0 * x - 2.0 * xt) * id);
+                if (WHAT & W_WEIGHTS && in) WT[(int64_t)j * e.ldw + i] = (GT)(gs * (4.0 * x - 2.0 * xt) * id);
             }
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                t1[tx][ty + 8 * u] = tv[u];
-                t2[tx][ty + 8 * u] = wv[u];                              // W_ji at [i][j]
+                if (WHAT & W_PARTIALS) t1[tx][ty + 8 * u] = tv[u];
+                if (WHAT & W_WEIGHTS) t2[tx][ty + 8 * u] = wv[u];        // W_ji at [i][j]
             }
             __syncthreads();
-            if (IB != JB)
+            if (WHAT & W_WEIGHTS && IB != JB)
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int i = IB * 32 + ty + 8 * u, j = JB * 32 + tx;
                     if (i < nocc && j < nocc) WT[(int64_t)i * e.ldw + j] = (GT)t2[ty + 8 * u][tx];
                 }
+            if (!(WHAT & W_PARTIALS)) continue;
             // row sums of t to e_i, and off the diagonal tile its column sums to e_j
             if (threadIdx.x < 32) {
                 double v = 0.0;
@@ -166,6 +170,7 @@ __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
                 if (JB * 32 + (int)threadIdx.x - 64 < nocc) ei[JB * 32 + threadIdx.x - 64] += v;
             }
         }
+    if (!(WHAT & W_PARTIALS)) return;
     __syncthreads();
     double *dst = e.epsA + ((int64_t)s * e.nvirt + a) * (nocc + 1);
     for (int i = threadIdx.x; i < nocc; i += 256) dst[i] = ei[i];
@@ -178,7 +183,7 @@ __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
 // u_ba) / d^2.
 constexpr int WB = 16, WB_A = WB * WB + 1;      // LDS: [a][b][i], rows of a padded to an odd stride
 
-template <typename GT>
+template <typename GT, int WHAT>
 __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
 {
     __shared__ double y1[WB * WB_A], y2[WB * WB_A];
@@ -221,14 +226,16 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
             si -= diag ? u : u + ut;
             ea[a] += u + ut;
             eb += u + ut;
-            y1[a * WB_A + hi * WB + lo] = gs * (4.0 * y[a] - 2.0 * yt[a]) * id;
-            y2[a * WB_A + hi * WB + lo] = gs * (4.0 * yt[a] - 2.0 * y[a]) * id;
+            if (WHAT & W_WEIGHTS) {
+                y1[a * WB_A + hi * WB + lo] = gs * (4.0 * y[a] - 2.0 * yt[a]) * id;
+                y2[a * WB_A + hi * WB + lo] = gs * (4.0 * yt[a] - 2.0 * y[a]) * id;
+            }
         }
-        sb[lo][hi] = si;
+        if (WHAT & W_PARTIALS) sb[lo][hi] = si;
         __syncthreads();
         // W^T rows (b, i), 16 consecutive a; rows (a, i), 16 consecutive b (thread (i, r) = (hi, lo))
         const int io = i0 + hi;
-        if (io < nocc) {
+        if (WHAT & W_WEIGHTS && io < nocc) {
 #pragma unroll 4
             for (int c = 0; c < WB; ++c)
                 if (a0 + lo < nvirt && b0 + c < nvirt)
@@ -239,12 +246,13 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
                     if (b0 + lo < nvirt && a0 + c < nvirt)
                         WT[((int64_t)(a0 + c) * nocc + io) * e.ldw + b0 + lo] = (GT)y2[c * WB_A + lo * WB + hi];
         }
-        if (threadIdx.x < WB && i0 + (int)threadIdx.x < nocc) {
+        if (WHAT & W_PARTIALS && threadIdx.x < WB && i0 + (int)threadIdx.x < nocc) {
             double v = 0.0;
             for (int c = 0; c < WB; ++c) v += sb[threadIdx.x][c];
             e.epsBi[((int64_t)s * e.npairs + pr) * nocc + i0 + threadIdx.x] = v;
         }
     }
+    if (!(WHAT & W_PARTIALS)) return;
     // e_a: over the 256 threads; e_b: over the 16 threads of b (off the diagonal: the second tile)
     __syncthreads();
 #pragma unroll
@@ -263,13 +271,13 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
 
 // both parts for nsc targets; part B's pairs in launches of at most 2^31 threads (92,673 virtuals
 // have 2^24 pairs)
-template <typename GT>
+template <typename GT, int WHAT>
 int weights(cds_ctx *ctx, WArgs w, int nsc)
 {
-    hipLaunchKernelGGL(weights_a_kernel<GT>, dim3((unsigned)w.nvirt, (unsigned)nsc), dim3(256), 0, ctx->stream, w);
+    hipLaunchKernelGGL((weights_a_kernel<GT, WHAT>), dim3((unsigned)w.nvirt, (unsigned)nsc), dim3(256), 0, ctx->stream, w);
     constexpr int most = 1 << 23;
     for (w.p0 = 0; w.p0 < w.npairs; w.p0 += most)
-        hipLaunchKernelGGL(weights_b_kernel<GT>, dim3((unsigned)std::min(most, w.npairs - w.p0), (unsigned)nsc), dim3(256), 0,
+        hipLaunchKernelGGL((weights_b_kernel<GT, WHAT>), dim3((unsigned)std::min(most, w.npairs - w.p0), (unsigned)nsc), dim3(256), 0,
                            ctx->stream, w);
     CDS_LAUNCHED(ctx);
     return CDS_OK;
@@ -571,17 +579,17 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
         w.epsBv = epsBv + (size_t)s0 * npairs * 2 * WB;
         w.npairs = npairs;
         if (es == 8) {
-            CDS_CALL(weights<double>(ctx, w, nsc));
+            CDS_CALL((weights<double, W_WEIGHTS | W_PARTIALS>(ctx, w, nsc)));
             CDS_CALL(zero_cols(ctx, (double *)WT, nvo, kp, kc));
             CDS_CALL(zero_cols(ctx, (double *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
         } else {
-            CDS_CALL(weights<float>(ctx, w, nsc));
+            CDS_CALL((weights<float, W_PARTIALS>(ctx, w, nsc)));
         }
         hipLaunchKernelGGL(scale_kernel, dim3((unsigned)nsc), dim3(256), 0, ctx->stream, (const double *)w.epsA,
                            (const double *)w.epsBi, nocc, nvirt, npairs, (const double *)d_obar + s0, d_scale + s0);
         if (es == 4) {
             w.scale = d_scale + s0;
-            CDS_CALL(weights<float>(ctx, w, nsc));
+            CDS_CALL((weights<float, W_WEIGHTS>(ctx, w, nsc)));
             CDS_CALL(zero_cols(ctx, (float *)WT, nvo, kp, kc));
             CDS_CALL(zero_cols(ctx, (float *)WT + nvo * kp, nvp - nvo, kp, (int64_t)0));
         }
