@@ -114,19 +114,23 @@ __global__ __launch_bounds__(256) void weights_a_kernel(WArgs e)
     const int nb = (nocc + 31) / 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     for (int IB = 0; IB < nb; ++IB)
         for (int JB = IB; JB < nb; ++JB) {
-            double v1[4], v2[4];
+            // all loads out before the first is waited for: no branch around them (see part B)
+            GT v1[4], v2[4];
+            bool in1[4], in2[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int r = ty + 8 * u;
                 const int i1 = IB * 32 + r, j1 = JB * 32 + tx, i2 = JB * 32 + r, j2 = IB * 32 + tx;
-                v1[u] = i1 < nocc && j1 < nocc ? (double)G[(int64_t)i1 * e.nvo + j1] : 0.0;   // X[i1][j1]
-                v2[u] = i2 < nocc && j2 < nocc ? (double)G[(int64_t)i2 * e.nvo + j2] : 0.0;   // X[i2][j2]
+                in1[u] = i1 < nocc && j1 < nocc;
+                in2[u] = i2 < nocc && j2 < nocc;
+                v1[u] = G[in1[u] ? (int64_t)i1 * e.nvo + j1 : 0];                             // X[i1][j1]
+                v2[u] = G[in2[u] ? (int64_t)i2 * e.nvo + j2 : 0];                             // X[i2][j2]
             }
             __syncthreads();
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                t1[ty + 8 * u][tx] = v1[u];
-                t2[ty + 8 * u][tx] = v2[u];
+                t1[ty + 8 * u][tx] = in1[u] ? (double)v1[u] : 0.0;
+                t2[ty + 8 * u][tx] = in2[u] ? (double)v2[u] : 0.0;
             }
             __syncthreads();
             // element (i, j) = (IB*32 + tx, JB*32 + cj): the weights of both partners, W_ij along i
@@ -209,12 +213,15 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
         const int i = i0 + lo, b = b0 + hi;
         const bool inb = i < nocc && b < nvirt;
         const double wi = w0 + e.eps[min(i, nocc - 1)] - vb;
-        double y[WB], yt[WB];
+        // all loads out before the first is waited for: no branch around them (a branch holds the
+        // conversion of a masked FP32 load too, so that each waited for its own: both passes 16.1 ms
+        // for 960 orbitals, 16 targets, where the one FP64 pass took 6.2)
+        GT yv[WB], yw[WB];
 #pragma unroll
         for (int a = 0; a < WB; ++a) {
             const bool in = inb && a0 + a < nvirt;
-            y[a] = in ? (double)G[(int64_t)(nocc + a0 + a) * e.nvo + (int64_t)b * nocc + i] : 0.0;
-            yt[a] = in ? (double)G[(int64_t)(nocc + b) * e.nvo + (int64_t)(a0 + a) * nocc + i] : 0.0;
+            yv[a] = G[in ? (int64_t)(nocc + a0 + a) * e.nvo + (int64_t)b * nocc + i : 0];
+            yw[a] = G[in ? (int64_t)(nocc + b) * e.nvo + (int64_t)(a0 + a) * nocc + i : 0];
         }
         double si = 0.0;
         __syncthreads();                                             // the tiles of the last round are written out
@@ -222,13 +229,14 @@ __global__ __launch_bounds__(256) void weights_b_kernel(WArgs e)
         for (int a = 0; a < WB; ++a) {
             const bool in = inb && a0 + a < nvirt;
             const double id = in ? 1.0 / (wi - ev[min(a0 + a, nvirt - 1)]) : 0.0;
-            const double u = (2.0 * y[a] - yt[a]) * y[a] * id * id, ut = (2.0 * yt[a] - y[a]) * yt[a] * id * id;
+            const double y = in ? (double)yv[a] : 0.0, yt = in ? (double)yw[a] : 0.0;
+            const double u = (2.0 * y - yt) * y * id * id, ut = (2.0 * yt - y) * yt * id * id;
             si -= diag ? u : u + ut;
             ea[a] += u + ut;
             eb += u + ut;
             if (WHAT & W_WEIGHTS) {
-                y1[a * WB_A + hi * WB + lo] = gs * (4.0 * y[a] - 2.0 * yt[a]) * id;
-                y2[a * WB_A + hi * WB + lo] = gs * (4.0 * yt[a] - 2.0 * y[a]) * id;
+                y1[a * WB_A + hi * WB + lo] = gs * (4.0 * y - 2.0 * yt) * id;
+                y2[a * WB_A + hi * WB + lo] = gs * (4.0 * yt - 2.0 * y) * id;
             }
         }
         if (WHAT & W_PARTIALS) sb[lo][hi] = si;
