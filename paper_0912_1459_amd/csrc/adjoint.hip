@@ -19,7 +19,8 @@
 //   C_bar_r += sum_K sum_x T^K_x Z^K[x][r]   and   C_bar_x += sum_K L^K Y^K_x,
 // 4 n nx (n + nvirt) operations per vector against 4 n^3 for the full symmetric Bbar (n = 480, 120
 // occupied: 0.45 of it; 960: 0.26), every product K-contiguous.  Both sums run over the vectors
-// inside the products, a run of vectors per workgroup, and the runs are added in order.
+// inside the products, a run of vectors per workgroup, and the runs are added in order.  Small
+// systems form the full symmetric Bbar instead (transform_adjoint_full).
 #include "cds_internal.h"
 
 #include <cmath>
@@ -440,6 +441,35 @@ __global__ __launch_bounds__(256) void bar_transpose_kernel(BarArgs a, int nkb, 
     }
 }
 
+// The full symmetric cotangent of small systems: S[kb][p][q] = Bbar^K[p][q] + Bbar^K[q][p] (FP64),
+// Bbar scattered from the sel and vo blocks, and 0 for the columns nbf <= nu < np_ of Wt[kb][p][nu],
+// which the product that forms Wt does not write
+template <typename BT>
+__global__ __launch_bounds__(256) void sym_bar_kernel(const BT *__restrict__ bsel, const BT *__restrict__ bvo, int64_t ldk,
+                                                      int64_t k0, int nkb, int nbf, int np_, int nmo, int nocc, int nsel,
+                                                      const int32_t *__restrict__ sel, double *__restrict__ S,
+                                                      double *__restrict__ Wt)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int per = nmo * (nmo + np_ - nbf);
+    if (t >= (int64_t)per * nkb) return;
+    const int kb = (int)(t / per), e = (int)(t - (int64_t)kb * per);
+    const int p = e / (nmo + np_ - nbf), q = e - p * (nmo + np_ - nbf);
+    if (q >= nmo) {
+        Wt[((int64_t)kb * nmo + p) * np_ + nbf + q - nmo] = 0.0;
+        return;
+    }
+    const int64_t K = k0 + kb;
+    double v = 0.0;
+    for (int s = 0; s < nsel; ++s) {
+        if (sel[s] == p) v += (double)bsel[((int64_t)s * nmo + q) * ldk + K];
+        if (sel[s] == q) v += (double)bsel[((int64_t)s * nmo + p) * ldk + K];
+    }
+    if (p >= nocc && q < nocc) v += (double)bvo[((int64_t)(p - nocc) * nocc + q) * ldk + K];
+    if (q >= nocc && p < nocc) v += (double)bvo[((int64_t)(q - nocc) * nocc + p) * ldk + K];
+    S[((int64_t)kb * nmo + p) * nmo + q] = v;
+}
+
 // C_bar[mu][r] from the summed products: virtual columns Pv, occupied columns Po, and the columns
 // of P2 (occupied x at x, target s at xo + s)
 __global__ void cbar_kernel(const double *__restrict__ Pv, const double *__restrict__ Po, const double *__restrict__ P2,
@@ -641,6 +671,66 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
     return CDS_OK;
 }
 
+namespace {
+
+// C_bar = sum_K L^K (C S^K), S^K = Bbar^K + Bbar^K^T in full: two products and three small kernels
+int transform_adjoint_full(cds_ctx *ctx, int prec, int nbf, int64_t nvec, const double *L, int64_t ldl, const double *C, int nmo,
+                           int nocc, int nsel, const int32_t *h_sel, int64_t ldk, const void *Bsel_bar, const void *Bvo_bar,
+                           double *C_bar)
+{
+    const int np_ = (int)(cds_ceil_div(nbf, 32) * 32);
+    // vectors per batch: enough that the first product launches about 2048 tiles, the unpacked batch
+    // below 1 GiB (C_bar sums the vectors in order whatever the batch)
+    const int64_t tiles = cds_ceil_div(nmo, 128) * cds_ceil_div(nbf, 128);
+    int64_t kbw = std::max<int64_t>(64, cds_ceil_div(2048, tiles));
+    kbw = std::min<int64_t>(kbw, std::max<int64_t>(1, (int64_t)((1ull << 30) / ((size_t)nbf * np_ * 8))));
+    const int kb = (int)std::min<int64_t>(kbw, nvec);
+    void *wl, *ws, *wk, *wsel, *wp;
+    CDS_CALL(cds_ws(ctx, WS_TR_UNPACK, (size_t)kb * nbf * np_ * 8, &wl));
+    CDS_CALL(cds_ws(ctx, WS_AD_TMP2, (size_t)kb * nmo * nmo * 8, &ws));
+    CDS_CALL(cds_ws(ctx, WS_TR_T, (size_t)kb * nmo * np_ * 8, &wk));
+    CDS_CALL(cds_ws(ctx, WS_TR_CX, (size_t)nsel * 4 + 64, &wsel));
+    CDS_CALL(cds_ws(ctx, WS_AD_TMP, (size_t)kb * nbf * nmo * 8, &wp));
+    CDS_HIP(ctx, hipMemcpyAsync(wsel, h_sel, (size_t)nsel * 4, hipMemcpyHostToDevice, ctx->stream));
+    for (int64_t k0 = 0; k0 < nvec; k0 += kb) {
+        const int nkb = (int)std::min<int64_t>(kb, nvec - k0);
+        CDS_CALL(cds_unpack64(ctx, L, ldl, k0, nkb, nbf, np_, (double *)wl));
+        const dim3 g((unsigned)cds_ceil_div((int64_t)nkb * nmo * (nmo + np_ - nbf), 256));
+        if (prec == CDS_PREC_FP64)
+            hipLaunchKernelGGL(sym_bar_kernel<double>, g, dim3(256), 0, ctx->stream, (const double *)Bsel_bar,
+                               (const double *)Bvo_bar, ldk, k0, nkb, nbf, np_, nmo, nocc, nsel, (const int32_t *)wsel,
+                               (double *)ws, (double *)wk);
+        else
+            hipLaunchKernelGGL(sym_bar_kernel<float>, g, dim3(256), 0, ctx->stream, (const float *)Bsel_bar,
+                               (const float *)Bvo_bar, ldk, k0, nkb, nbf, np_, nmo, nocc, nsel, (const int32_t *)wsel,
+                               (double *)ws, (double *)wk);
+        CDS_LAUNCHED(ctx);
+        // Wt[kb][p][nu] = sum_r S[kb][p][r] C[nu][r]   (S symmetric; both operands K-contiguous)
+        GemmDesc g1 = {};
+        g1.M = nmo; g1.N = nbf; g1.K = nmo; g1.batch = nkb;
+        g1.A = ws; g1.sAm = nmo; g1.sAk = 1; g1.sAb = (int64_t)nmo * nmo;
+        g1.B = C; g1.sBn = nmo; g1.sBk = 1; g1.sBb = 0;
+        g1.C = wk; g1.sCm = np_; g1.sCn = 1; g1.sCb = (int64_t)nmo * np_;
+        g1.alpha = 1.0; g1.beta = 0.0;
+        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, g1, nullptr, nullptr));
+        // part[kb][mu][p] = sum_nu Lu[kb][mu][nu] Wt[kb][p][nu], then C_bar (+)= sum_kb part[kb]
+        GemmDesc g2 = {};
+        g2.M = nbf; g2.N = nmo; g2.K = np_; g2.batch = nkb;
+        g2.A = wl; g2.sAm = np_; g2.sAk = 1; g2.sAb = (int64_t)nbf * np_;
+        g2.B = wk; g2.sBn = np_; g2.sBk = 1; g2.sBb = (int64_t)nmo * np_;
+        g2.C = wp; g2.sCm = nmo; g2.sCn = 1; g2.sCb = (int64_t)nbf * nmo;
+        g2.alpha = 1.0; g2.beta = 0.0;
+        CDS_CALL(cds_gemm_ex(ctx, CDS_PREC_FP64, g2, nullptr, nullptr));
+        const int64_t ne = (int64_t)nbf * nmo;
+        hipLaunchKernelGGL(sum_parts_kernel, dim3((unsigned)cds_ceil_div(ne, 256)), dim3(256), 0, ctx->stream,
+                           (const double *)wp, nkb, ne, k0 > 0 ? 1 : 0, C_bar);
+        CDS_LAUNCHED(ctx);
+    }
+    return CDS_OK;
+}
+
+}  // namespace
+
 extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, int64_t nvec,
                                      const double *L, int64_t ldl, const double *C, int32_t nmo,
                                      int32_t nocc, int32_t nsel, const int32_t *h_sel, int64_t ldk,
@@ -658,6 +748,16 @@ extern "C" int cds_transform_adjoint(cds_ctx *ctx, int32_t prec, int32_t nbf, in
     CdsTimer tall;
     CDS_CALL(cds_timer_start(ctx, &tall));
     const int nvirt = nmo - nocc;
+    // Small systems take the full symmetric cotangent: five launches against twelve, and products that
+    // one tile per vector holds save nothing by leaving rows out.  Per call, full / rows only, nocc =
+    // n / 4, 2 targets: 8 functions, 24 vectors 32 / 58 us; 45, 135: 55 / 102; 96, 288: 113 / 196; 128,
+    // 896: 370 / 447; 130, 130: 210 / 171 (nmo off the multiples of 16 takes the general product);
+    // 144, 432 (5.2e9 operations): 317 / 330; 160, 480 (7.9e9): 370 / 373; 192, 576 (16e9): 703 / 536
+    if (nbf <= 128 || (nmo % 16 == 0 && 4.0 * nmo * nbf * (double)nbf * (double)nvec < 5.5e9)) {
+        CDS_CALL(transform_adjoint_full(ctx, prec, nbf, nvec, L, ldl, C, nmo, nocc, nsel, h_sel, ldk, Bsel_bar, Bvo_bar, C_bar));
+        CDS_CALL(cds_timer_stop(ctx, &tall, &ctx->stats.t_adjoint_ms));
+        return CDS_OK;
+    }
     auto up16 = [](int64_t n) { return (int)(cds_ceil_div(n, 16) * 16); };
     const int np_ = (int)(cds_ceil_div(nbf, 32) * 32);
     const int xo = up16(nocc), selp = up16(nsel), xp = xo + selp;    // rows x: occupied, then targets
