@@ -225,7 +225,8 @@ __global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__
                                                          const int *__restrict__ act, double conv, int it, DyRoots d)
 {
     __shared__ double A[DY_MAXSEL + 1][DY_MAXSEL + 2], V[DY_MAXSEL + 1][DY_MAXSEL + 2];
-    __shared__ double rc[(DY_MAXSEL + 1) / 2], rs[(DY_MAXSEL + 1) / 2], red[2][256], ov[DY_MAXSEL + 1], un[DY_MAXSEL + 1];
+    __shared__ double rc[(DY_MAXSEL + 1) / 2], rs[(DY_MAXSEL + 1) / 2], red[2][DY_MAXSEL + 1], ov[DY_MAXSEL + 1], un[DY_MAXSEL + 1];
+    __shared__ uchar2 pq[DY_MAXSEL][(DY_MAXSEL + 1) / 2];      // round r's i-th pair
     __shared__ int jbest;
     const int t = blockIdx.x, k = act[t], tid = threadIdx.x;
     for (int e = tid; e < n * n; e += 256) {
@@ -234,6 +235,12 @@ __global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__
         V[i][j] = i == j ? 1.0 : 0.0;
     }
     const int m = n + (n & 1), half = m / 2;      // players of the round robin (an odd n sits one out)
+    // round r: (m-1, r) and ((r + i) mod (m-1), (r - i) mod (m-1)), i = 1 .. half - 1
+    for (int e = tid; e < (m - 1) * half; e += 256) {
+        const int r = e / half, i = e - r * half;
+        const int x = i == 0 ? m - 1 : (r + i) % (m - 1), y = i == 0 ? r : (r + m - 1 - i) % (m - 1);
+        pq[r][i] = make_uchar2((unsigned char)min(x, y), (unsigned char)max(x, y));
+    }
     for (int sweep = 0; sweep < 100; ++sweep) {
         __syncthreads();
         double off = 0.0, tot = 0.0;
@@ -243,31 +250,26 @@ __global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__
             tot += x;
             if (i != j) off += x;
         }
-        red[0][tid] = off;
-        red[1][tid] = tot;
-        for (int o = 128; o > 0; o >>= 1) {
-            __syncthreads();
-            if (tid < o) {
-                red[0][tid] += red[0][tid + o];
-                red[1][tid] += red[1][tid + o];
-            }
+        // fixed order: lanes by butterfly, then the four waves
+        for (int o = 32; o > 0; o >>= 1) {
+            off += __shfl_xor(off, o, 64);
+            tot += __shfl_xor(tot, o, 64);
+        }
+        if ((tid & 63) == 0) {
+            red[0][tid >> 6] = off;
+            red[1][tid >> 6] = tot;
         }
         __syncthreads();
+        off = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+        tot = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
         // a matrix of infinities leaves here, undiagonalised (inf <= inf); one with a NaN does not: its
         // rotations make the energy and the vector NaN, all of it within two sweeps (the first makes
         // two whole rows and columns NaN, the second every pair they are in)
-        if (red[0][0] <= 1e-30 * red[1][0] || red[0][0] == 0.0) break;
-        if (sweep == 2 && red[1][0] != red[1][0]) break;
+        if (off <= 1e-30 * tot || off == 0.0) break;
+        if (sweep == 2 && tot != tot) break;
         for (int r = 0; r < m - 1; ++r) {
-            // round r: (m-1, r) and ((r + i) mod (m-1), (r - i) mod (m-1)), i = 1 .. half - 1
-            auto pair = [&](int i, int &p, int &q) {
-                const int x = i == 0 ? m - 1 : (r + i) % (m - 1), y = i == 0 ? r : (r + m - 1 - i) % (m - 1);
-                p = min(x, y);
-                q = max(x, y);
-            };
             if (tid < half) {
-                int p, q;
-                pair(tid, p, q);
+                const int p = pq[r][tid].x, q = pq[r][tid].y;
                 double c = 1.0, s = 0.0;
                 if (q < n && A[p][q] != 0.0) {
                     const double theta = (A[q][q] - A[p][p]) / (2.0 * A[p][q]);
@@ -281,8 +283,7 @@ __global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__
             __syncthreads();
             for (int e = tid; e < half * n * 2; e += 256) {      // columns p, q of A and V
                 const int i = e / (2 * n), rem = e - i * 2 * n, x = rem >> 1;
-                int p, q;
-                pair(i, p, q);
+                const int p = pq[r][i].x, q = pq[r][i].y;
                 if (q >= n || rs[i] == 0.0) continue;
                 double(*M)[DY_MAXSEL + 2] = rem & 1 ? V : A;
                 const double a = M[x][p], b = M[x][q];
@@ -292,8 +293,7 @@ __global__ __launch_bounds__(256) void dyson_step_kernel(int n, const double *__
             __syncthreads();
             for (int e = tid; e < half * n; e += 256) {          // rows p, q of A
                 const int i = e / n, x = e - i * n;
-                int p, q;
-                pair(i, p, q);
+                const int p = pq[r][i].x, q = pq[r][i].y;
                 if (q >= n || rs[i] == 0.0) continue;
                 const double a = A[p][x], b = A[q][x];
                 A[p][x] = rc[i] * a - rs[i] * b;
@@ -525,11 +525,14 @@ extern "C" int cds_dyson_solve(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t
     CDS_HIP(ctx, hipMemcpyAsync(d_sel, hp, (size_t)n * 4, hipMemcpyHostToDevice, ctx->stream));
     const double *hw = (const double *)hp, *hP = hw + n, *hU = hP + n;
     const int *hs = (const int *)(hU + (size_t)n * n), *hi = hs + n;
-    int nact = n;
+    int nact = n, nlist = -1;                     // roots still iterating, and in the device's list
     for (int it = 1; it <= max_iter && nact > 0; ++it) {
-        hipLaunchKernelGGL(dyson_list_kernel, dim3(1), dim3(64), 0, ctx->stream, n, it == 1 ? 1 : 0, eps,
-                           (const int *)d_sel, d_eS, R, d_act);
-        CDS_LAUNCHED(ctx);
+        if (nlist != nact) {                      // (a root that ended never comes back)
+            hipLaunchKernelGGL(dyson_list_kernel, dim3(1), dim3(64), 0, ctx->stream, n, it == 1 ? 1 : 0, eps,
+                               (const int *)d_sel, d_eS, R, d_act);
+            CDS_LAUNCHED(ctx);
+            nlist = nact;
+        }
         for (int b0 = 0; b0 < nact; b0 += DY_TT) {
             const int nt = std::min(DY_TT, nact - b0);
             CDS_CALL(dy_sums(ctx, S, nt, R.w, d_act + b0));
