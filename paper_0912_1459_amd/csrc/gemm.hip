@@ -505,7 +505,11 @@ constexpr int GD_NT = 512, GD_SLICE = 16384, GD_STAGE = 2 * GD_SLICE;
 // of 128 m; the fragments are read element by element, 16 lanes along m, with the 16-m blocks of a
 // row permuted by k / 2 (k / 4) & 7 so that the lane groups' rows fall into distinct banks.  The
 // lanes hold the same k as with a K-contiguous A.
-template <int PREC, bool KA>
+// BACC: runs of batch entries may be summed (GemmDesc::bacc).  Its count of the stages left in an entry
+// stays out of the loop of FP64 products that sum none (960 orbitals: 598 -> 592 us per product, 586 in
+// a kernel with the tiles in row order and no other options), but not of FP32 ones, which are slower
+// without it (transform of 1024 orbitals 4.33 -> 4.39 ms).
+template <int PREC, bool KA, bool BACC>
 __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per, unsigned gx, unsigned gy, int th, int tw)
 {
     typedef typename Tr<PREC>::E E;
@@ -517,13 +521,13 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
     const unsigned t = xcd_order<64>(blockIdx.x, gridDim.x), bt = t / per;   // two workgroups on each of 32 CUs
     unsigned tm, tn;
     tile_at(t - bt * per, a.tri, gx, gy, th, tw, tm, tn);
-    const int64_t n0 = (int64_t)tn * tw, m0 = (int64_t)tm * th, batch = bt * a.bacc;
+    const int64_t n0 = (int64_t)tn * tw, m0 = (int64_t)tm * th, batch = BACC ? bt * a.bacc : bt;
     if (below(a, m0, n0 + tw - 1)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, r16 = lane & 15;
     const int64_t nb = a.K / Tr<PREC>::KB;                      // stages per batch entry, and in all
-    const int64_t ns = nb * min(a.bacc, a.batch - batch);
+    const int64_t ns = BACC ? nb * min(a.bacc, a.batch - batch) : nb;
     // this wave's four loads per stage: slice sl (0 A, 1 B), rows 8 q + lane / 8 for q in
     // [4 (wave & 3), 4 (wave & 3) + 4), position lane % 8 holding the swizzled logical chunk
     const int sl = wave >> 2;
@@ -556,7 +560,7 @@ __global__ __launch_bounds__(GD_NT, 4) void gemm_dma_kernel(Args a, unsigned per
         for (int q = 0; q < 4; ++q)
             if (all || q < nld) cds_lds_dma16(src[q] + koff, dst + q * 1024);
         koff += kstep;
-        if (--left == 0) {
+        if (BACC && --left == 0) {
             left = nb;
             koff += sb * ES - nb * kstep;
         }
@@ -701,7 +705,9 @@ int launch(cds_ctx *ctx, Args &a)
             };
             const int th = edge(a.M, gy), tw = edge(a.N, gx);
             const unsigned per = (unsigned)count_tiles(a.tri, (unsigned)gx, (unsigned)gy, th, tw);
-            const auto kern = a.ka ? gemm_dma_kernel<PREC, true> : gemm_dma_kernel<PREC, false>;
+            constexpr bool F32 = PREC == CDS_PREC_FP32;
+            const auto kern = a.bacc > 1 ? (a.ka ? gemm_dma_kernel<PREC, true, true> : gemm_dma_kernel<PREC, false, true>)
+                                         : (a.ka ? gemm_dma_kernel<PREC, true, F32> : gemm_dma_kernel<PREC, false, F32>);
             hipLaunchKernelGGL(kern, dim3(per * (unsigned)cds_ceil_div(a.batch, a.bacc)), dim3(GD_NT), 0, ctx->stream, a, per,
                                (unsigned)gx, (unsigned)gy, th, tw);
             CDS_LAUNCHED(ctx);
