@@ -11,10 +11,11 @@
 // with the denominator w + e0 - e_r - e_c (e0 = e_a, resp. e_i).  The exchange partner of
 // Y[r][c] is Y[c][r] and both share the denominator, so every unordered pair {r, c}
 // contributes R / d once, R = 2 (Y_rc^2 + Y_cr^2 - Y_rc Y_cr) (r != c) or Y_rr^2.
-// A workgroup owns one pair of 128-row tiles (TR <= TC) of one matrix: off the diagonal it
-// forms Y[TR][TC] and, in the same registers' layout, Y[TC][TR]^T as Q[TR] P[TC]^T (both
-// partners of an element sit in one lane); on the diagonal it forms Y[TR][TR] and reads each
-// partner through an LDS transpose.  Operand slices (128 rows x 64 bytes per stage and plane) go
+// A workgroup owns one pair of 128-row tiles (TR <= TC) of one matrix: off the diagonal one set of
+// waves forms Y[TR][TC] and another, in the same registers' layout, Y[TC][TR]^T as Q[TR] P[TC]^T, so
+// that both partners of an element sit in the same lane of two waves, which hand each other half of
+// their blocks through LDS; on the diagonal it forms Y[TR][TR] and reads each partner from the lower
+// triangle, packed in LDS.  Operand slices (128 rows x 64 bytes per stage and plane) go
 // straight from global memory into a ring of LDS stages (global_load_lds_dwordx4; four stages of
 // 32 KB in FP64 and FP32, two of 64 KB in split bf16), one barrier per stage, the 16-byte chunks
 // of a row XOR-swizzled so the fragment reads of consecutive rows hit distinct banks; 16 x 16
@@ -698,13 +699,14 @@ template <int PREC, int MODE, bool DG>
 static void launch_fused_t(cds_ctx *ctx, const FArgs &a, unsigned nblk, int T)
 {
     const dim3 g(nblk), b(fused_threads(DG));
+    // (eight energies' sums do not fit beside a diagonal task's FP64 accumulators: four per pass there)
+    constexpr int TT = DG && PREC == CDS_PREC_FP64 ? 4 : 8;
     if (MODE == 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 1, 1, DG>), g, b, 0, ctx->stream, a);
     else if (MODE == 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 2, 1, DG>), g, b, 0, ctx->stream, a);
     else if (T <= 1) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 1, DG>), g, b, 0, ctx->stream, a);
     else if (T <= 2) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 2, DG>), g, b, 0, ctx->stream, a);
-    else if (T <= 4 || (DG && PREC == CDS_PREC_FP64))   // eight energies' sums do not fit beside FP64 accumulators
-        hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 4, DG>), g, b, 0, ctx->stream, a);
-    else hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 8, DG>), g, b, 0, ctx->stream, a);
+    else if (T <= 4) hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, 4, DG>), g, b, 0, ctx->stream, a);
+    else hipLaunchKernelGGL((sigma_fused_kernel<PREC, 0, TT, DG>), g, b, 0, ctx->stream, a);
 }
 
 // the tasks of one kind (diagonal tile pairs, or the others)
