@@ -1679,7 +1679,7 @@ __device__ unsigned long long radix_boundary(const unsigned long long (&u)[KPT],
 
 // The same boundary from one histogram where it lies within a factor of 256 of the largest key
 // (top 32 bits `top`): bins of 2^15 key steps (3 %) below the largest, and the few keys of the
-// boundary's bin ranked among themselves by one wave.  Keys further down are not counted (they
+// boundary's bin ranked among themselves, a thread per key.  Keys further down are not counted (they
 // would all meet in one bin).  Otherwise, or with more than SEL_LIST keys in that bin, the radix
 // passes.  The selection with four passes
 // of 256 bins each, its rows' marks and residuals loaded one after the other, took 17.1 us at 820

@@ -42,8 +42,10 @@ constexpr int DIAG_SLOTS = FT * (FT + 1) / 2;   // residues of a diagonal task
 constexpr int OFF_SLOTS = FT * FT;              // residues of an off-diagonal task
 constexpr int WP = 8;                           // waves per product
 constexpr int fused_threads(bool dg) { return (dg ? WP : 2 * WP) * 64; }
-// targets of a group of tasks that run together on an XCD.  960 orbitals, 16 targets: whole
-// split-bf16 solve 14.4 ms with a group of one, 13.0 (2), 12.5 (4), 13.3 (8), 13.8 ms (16)
+// targets of a group of tasks that run together on an XCD.  Split-bf16 residues and first evaluation
+// with groups of 1 / 2 / 4 / 8, ms: 960 orbitals, 16 targets 11.6 / 10.8 / 10.6 / 10.9, 3 targets
+// 2.33 / 2.22 / 2.14 / 2.15; 480, 48 targets 7.79 / 7.38 / 6.94 / 7.02, 5 targets 0.89 / 0.86 / 0.86 /
+// 0.84.  FP64 and FP32 differ by less than 1.2 % at these and at 240 and 300 orbitals
 constexpr int TGS = 4;
 constexpr int FTT = 8;                          // trial energies per epilogue pass (at most)
 
