@@ -582,6 +582,7 @@ extern "C" int cds_qp_adjoint(cds_ctx *ctx, int32_t prec, int64_t nvec, int64_t 
         const int64_t tiles = cds_ceil_div((int64_t)csz * nmo, 128) * cds_ceil_div(nvec, 128);
         double best = 0.0;
         for (int c = 1; c <= 16 && (c == 1 || nvo / c >= 512); ++c) {
+            if (c > 1 && c * up(cds_ceil_div(nvo, c)) > (int64_t)65535 * 32) continue;   // (cds_transpose's rows)
             const double cost = (double)cds_ceil_div(tiles * c, 512) / c * (1.0 + 0.01 * c);
             if (c == 1 || cost < best) {
                 best = cost;

@@ -80,3 +80,37 @@ def test_adjoint_of_more_than_2_32_entries():
     assert torch.equal(got[2], ref[2])
     del got, x, SL, VL
     torch.cuda.empty_cache()
+
+
+def test_adjoint_of_the_most_pairs():
+    # 1020 occupied, 2056 virtuals: 2,097,120 = 65535 * 32 rows of Bvo, the most that a transpose takes;
+    # the parts of the sum over them must not be padded past that.  Checked by what holds exactly:
+    # a common shift of the energies (sum of eps_bar = omega_bar), and Sigma's degree two in either
+    # block (sum of Bsel_bar Bsel = sum of Bvo_bar Bvo = 2 omega_bar P Sigma).  The sums have 4e9
+    # positive and negative terms: 1e-9 of the largest is far above their rounding
+    import paper_0912_1459_amd.core as C
+    from paper_0912_1459_amd import _lib as A
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 130 << 30:
+        pytest.skip("needs 130 GiB of device memory")
+    nocc, nvirt, nvec, ldk = 1020, 2056, 2, 64
+    g = torch.Generator(device="cuda").manual_seed(6)
+
+    def block(rows):
+        x = torch.zeros((rows, ldk), dtype=torch.float64, device="cuda")
+        x[:, :nvec] = torch.rand((rows, nvec), generator=g, dtype=torch.float64, device="cuda") * 1e-2
+        return x
+    S, V = block(nocc + nvirt), block(nvirt * nocc)
+    eps = torch.cat([torch.linspace(-1.5, -0.3, nocc, dtype=torch.float64), torch.linspace(0.1, 3.0, nvirt, dtype=torch.float64)]).cuda()
+    B = C.BBlocks(A.PREC_FP64, S, V, nvec, ldk, nocc + nvirt, nocc, np.array([nocc - 1], np.int32))
+    om, wb = np.array([-0.2]), np.array([0.75])
+    print("adjoint of 2,097,120 pairs", flush=True)
+    with C.Context(0) as ctx:
+        gs, gv, ge = C.qp_adjoint(B, eps, om, wb, ctx=ctx)
+        s, ds = C.sigma2(B, eps, om[:, None], ctx=ctx)
+    want = 2.0 * wb[0] / (1.0 - ds[0, 0]) * s[0, 0]
+    for x, y in ((gs, S), (gv, V)):
+        assert abs(float((x * y).sum()) - want) <= 1e-9 * float((x * y).abs().sum())
+    assert abs(float(ge.sum()) - wb[0]) <= 1e-9 * float(ge.abs().sum())
+    del gs, gv, S, V, B
+    torch.cuda.empty_cache()
